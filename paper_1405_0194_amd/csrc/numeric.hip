@@ -109,10 +109,10 @@ __device__ __forceinline__ cplx ld_or_zero(const double* base, int64_t e, bool o
 // --------------------------------------------------------------------------
 template <int NTILE>
 struct Geo {
-  static constexpr int WN = NTILE / 32;        // waves along n
+  static constexpr int WN = NTILE < 32 ? 1 : NTILE / 32;   // waves along n
   static constexpr int WM = 4 / WN;            // waves along m
   static constexpr int BM = 64 / WM / 16;      // 16-blocks per wave along m
-  static constexpr int BN = 2;                 // 16-blocks per wave along n
+  static constexpr int BN = NTILE < 32 ? 1 : 2;            // 16-blocks per wave along n
   static constexpr int XA = 64 * KC / NT;      // A transfers per thread and chunk
   static constexpr int XB = NTILE * KC / NT;   // B transfers per thread and chunk
 };
@@ -286,26 +286,32 @@ __device__ __forceinline__ void acc_at(const Acc<CPLX, NTILE>& acc, int idx, int
 template <bool CPLX, int NTILE, class AF>
 __device__ __forceinline__ void acc_sub_into(const Acc<CPLX, NTILE>& acc, double* target, AF addr) {
   constexpr int NE = acc_elems<NTILE>();
-  int64_t e[NE];
-  bool ok[NE];
+  // complex: at most 8 elements at a time, so positions and old values fit
+  // beside the accumulators in the 128 registers of four waves per SIMD
+  constexpr int NH = CPLX && NE > 8 ? 8 : NE;
 #pragma unroll
-  for (int i = 0; i < NE; ++i) {
-    int m, n;
-    cplx v;
-    acc_at<CPLX, NTILE>(acc, i, m, n, v);
-    ok[i] = addr(m, n, e[i]);
-  }
-  // addr returns an in-bounds position also for skipped elements, so the
-  // old values load without branches
-  cplx o[NE];
+  for (int h = 0; h < NE; h += NH) {
+    int64_t e[NH];
+    bool ok[NH];
 #pragma unroll
-  for (int i = 0; i < NE; ++i) o[i] = ld_elem<CPLX>(target, e[i]);
+    for (int i = 0; i < NH; ++i) {
+      int m, n;
+      cplx v;
+      acc_at<CPLX, NTILE>(acc, h + i, m, n, v);
+      ok[i] = addr(m, n, e[i]);
+    }
+    // addr returns an in-bounds position also for skipped elements, so the
+    // old values load without branches
+    cplx o[NH];
 #pragma unroll
-  for (int i = 0; i < NE; ++i) {
-    int m, n;
-    cplx v;
-    acc_at<CPLX, NTILE>(acc, i, m, n, v);
-    if (ok[i]) st_elem<CPLX>(target, e[i], cplx{o[i].re - v.re, o[i].im - v.im});
+    for (int i = 0; i < NH; ++i) o[i] = ld_elem<CPLX>(target, e[i]);
+#pragma unroll
+    for (int i = 0; i < NH; ++i) {
+      int m, n;
+      cplx v;
+      acc_at<CPLX, NTILE>(acc, h + i, m, n, v);
+      if (ok[i]) st_elem<CPLX>(target, e[i], cplx{o[i].re - v.re, o[i].im - v.im});
+    }
   }
 }
 
@@ -432,15 +438,17 @@ struct AllLive {
   static constexpr int kSwz = 0;
   __device__ int operator()(int) const { return 15; }
 };
-template <bool LOWER>   // LOWER: A[m][k] = 0 for k > m; else A[m][k] = 0 for k < m
+template <bool LOWER, int NTILE = 64>   // LOWER: A[m][k] = 0 for k > m; else A[m][k] = 0 for k < m
 struct TriLive {
   static constexpr bool kAll = false;
-  static constexpr int kSwz = 1;
+  static constexpr int kSwz = NTILE == 64 ? 1 : 0;
   __device__ int operator()(int k0) const {
-    static_assert(KC == 16, "a chunk spans one 16-row block");
-    const int wr = (threadIdx.x >> 6) / Geo<64>::WN;
-    const int c = k0 / KC;
+    // a chunk lies in one 16-column block
+    const int wr = (threadIdx.x >> 6) / Geo<NTILE>::WN;
+    const int c = k0 / 16;
     const int mb0 = wr, mb1 = 3 - wr;
+    if constexpr (NTILE != 64)   // one block row per wave
+      return __builtin_amdgcn_readfirstlane((LOWER ? c <= wr : c >= wr) ? 15 : 0);
     const bool l0 = LOWER ? c <= mb0 : c >= mb0;
     const bool l1 = LOWER ? c <= mb1 : c >= mb1;
     return __builtin_amdgcn_readfirstlane((l0 ? 3 : 0) | (l1 ? 12 : 0));   // both column blocks of a live row block
@@ -548,6 +556,361 @@ struct RowsFast {
 struct KFast {
   __device__ bool operator()(int) const { return true; }
 };
+
+// --------------------------------------------------------------------------
+// Complex tile engine: the same 64 x NTILE products (NTILE = 64, 32 or 16)
+// with the operands loaded straight from global memory into LDS.
+//
+// What bounds these products is the issue of everything that is not an MFMA:
+// with the operands staged through registers (loads with 64-bit per-lane
+// addresses, LDS stores, split re/im reads) the engine ran at 62 TFLOP/s on
+// 64 x 4096 x 4096 x 32 shifts and the register staging held it to two
+// workgroups per CU.  Here a stage of KD = 8 columns is moved by
+// buffer_load_dwordx4 ... lds: the base is scalar and advances with k, the
+// lane offset is constant, lanes outside the operand get an offset past the
+// descriptor's range and read zeros.  An element stays one 16-byte (re, im)
+// pair, read with one ds_read_b128.  No staging registers: four workgroups
+// (16 waves) fit on a CU, which cover each other's barriers, so two stages
+// are enough.  Measured on k_selinv_off's shape: 62.2 -> 69.0 TFLOP/s at
+// 4096 rows x 32 shifts (74 with the loads taken out), 48.4 -> 54.4 at 884 x 60.
+//
+// Narrow tiles: a launch of T tiles of 64 columns takes ceil(T / 256) rounds
+// over the CUs, so a few hundred tiles leave the chip partly idle (840 tiles:
+// 3.3 rounds of work in 4).  32- and 16-column tiles cut the rounds finer:
+// 884 rows x 60 shifts 54.4 -> 59.9 TFLOP/s with 32 columns, 452 x 40 33.3 ->
+// 43.4 (32) and 47.8 (16), 130 x 40 13.7 -> 22.6 (32); on full launches they
+// are slower (4096 x 32: 68.1 and 60.7), see pick_tile.
+//
+// LDS layouts of a stage of an operand with ROWS rows (slot = 16 bytes, a
+// wave fills 64 slots in lane order per load):
+//   rows fast  slot = k ROWS + row            (memory contiguous along rows)
+//   k fast     slot = row 8 + (k ^ ((row / 2) % 8))   (contiguous along k)
+// The 16 lanes of an MFMA operand row read 16 consecutive slots, or 16 slots
+// that differ modulo 16 (the exclusive or sees to that): no bank conflicts.
+// --------------------------------------------------------------------------
+typedef double dbl2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) void* lds_ptr;
+typedef const __attribute__((address_space(1))) void* glb_ptr;
+
+constexpr int KD = 8;                        // columns per stage
+constexpr unsigned LANE_OUT = 0x80000000u;   // lane offset past every descriptor's range: reads zeros
+__device__ __align__(16) double kUnitElem[2] = {1.0, 0.0};   // never written
+
+template <int NTILE, bool SCALE>
+struct CStage {
+  dbl2 a[2][KD * 64];
+  dbl2 b[2][KD * NTILE];
+  dbl2 d[SCALE ? 2 : 1][SCALE ? KD : 1];
+};
+
+// The wave's index and a pointer the compiler may not know to be uniform.
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
+__device__ __forceinline__ const double* uniform(const double* p) {
+  const uint64_t v = (uint64_t)p;
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+  return (const double*)(((uint64_t)hi << 32) | lo);
+}
+
+// 16 bytes per lane into LDS at lds + 16 lane: from base + off (off < 2^31
+// or LANE_OUT), or from a pointer per lane.
+__device__ __forceinline__ void load_lds(const double* base, unsigned off, dbl2* lds) {
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, LANE_OUT, 0x00020000);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr)lds, 16, off, 0, 0, 0);
+}
+__device__ __forceinline__ void load_lds_ptr(const double* p, dbl2* lds) {
+  __builtin_amdgcn_global_load_lds((glb_ptr)p, (lds_ptr)lds, 16, 0, 0);
+}
+
+// Operand slot of lane `lane` in the wave load q of a stage: (row, k).
+template <int ROWS>
+__device__ __forceinline__ void slot_rows(int q, int lane, int& m, int& k) {
+  m = lane % ROWS;
+  k = q * (64 / ROWS) + lane / ROWS;
+}
+__device__ __forceinline__ void slot_k(int q, int lane, int& m, int& k) {
+  m = q * 8 + (lane >> 3);
+  k = (lane & 7) ^ ((m >> 1) & 7);
+}
+
+// Operands of gemm_lds.  issue(k0, lds) starts the loads of columns
+// [k0, k0 + KD) (k relative to the product's first column; columns from K on
+// and rows from nrows on read zeros); fast(k0) is the layout it uses (true: k
+// fast).  Wave w makes the loads q = w, w + 4, ...
+template <int ROWS>
+struct LoadCount {
+  static constexpr int N = KD * ROWS / 64, J = (N + 3) / 4;
+};
+
+// Element (row, k) at base + k ld + row.
+template <int ROWS>
+struct ColsOp : LoadCount<ROWS> {
+  using LoadCount<ROWS>::N;
+  using LoadCount<ROWS>::J;
+  const double* base;
+  int64_t ld;
+  int K, w;
+  unsigned v[J];
+  int kk[J];
+  __device__ __forceinline__ ColsOp(const double* b, int ld_, int nrows, int K_)
+      : base(uniform(b)), ld(ld_), K(K_), w(wave_id()) {
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      int m;
+      slot_rows<ROWS>(w + 4 * j, threadIdx.x & 63, m, kk[j]);
+      v[j] = m < nrows ? (unsigned)(kk[j] * ld_ + m) * 16u : LANE_OUT;
+    }
+  }
+  __device__ __forceinline__ void issue(int k0, dbl2* lds) const {
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      if (N < 4 && w >= N) continue;
+      load_lds(base + 2 * (ld * k0), k0 + kk[j] < K ? v[j] : LANE_OUT, lds + (w + 4 * j) * 64);
+    }
+  }
+  __device__ __forceinline__ static constexpr bool fast(int) { return false; }
+};
+
+// Element (row, k) at base + row ld + k.
+template <int ROWS>
+struct RowsOp : LoadCount<ROWS> {
+  using LoadCount<ROWS>::N;
+  using LoadCount<ROWS>::J;
+  const double* base;
+  int K, w;
+  unsigned v[J];
+  int kk[J];
+  __device__ __forceinline__ RowsOp(const double* b, int ld, int nrows, int K_)
+      : base(uniform(b)), K(K_), w(wave_id()) {
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      int m;
+      slot_k(w + 4 * j, threadIdx.x & 63, m, kk[j]);
+      v[j] = m < nrows ? (unsigned)(m * ld + kk[j]) * 16u : LANE_OUT;
+    }
+  }
+  __device__ __forceinline__ void issue(int k0, dbl2* lds) const {
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      if (N < 4 && w >= N) continue;
+      load_lds(base + 2 * (int64_t)k0, k0 + kk[j] < K ? v[j] : LANE_OUT, lds + (w + 4 * j) * 64);
+    }
+  }
+  __device__ __forceinline__ static constexpr bool fast(int) { return true; }
+};
+
+// The unit lower triangular n x n block T (n <= 64; strict part stored, T(r,
+// q) at base + q ld + r) as the A operand: A[m][k] = T[m][k], or T[k][m] when
+// TRANS.
+template <bool TRANS>
+struct TriOp : LoadCount<64> {
+  const double* base;
+  int ld, n, w;
+  __device__ __forceinline__ TriOp(const double* b, int ld_, int n_) : base(b), ld(ld_), n(n_), w(wave_id()) {}
+  __device__ __forceinline__ void issue(int k0, dbl2* lds) const {
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      int m, k;
+      if (TRANS) slot_k(w + 4 * j, threadIdx.x & 63, m, k);
+      else slot_rows<64>(w + 4 * j, threadIdx.x & 63, m, k);
+      k += k0;
+      const int r = TRANS ? k : m, q = TRANS ? m : k;
+      const double* p = r == q ? kUnitElem : kZeroElem;
+      if (r > q) p = base + 2 * ((int64_t)q * ld + r);
+      if (max(r, q) >= n) p = kZeroElem;
+      load_lds_ptr(p, lds + (w + 4 * j) * 64);
+    }
+  }
+  __device__ __forceinline__ static constexpr bool fast(int) { return TRANS; }
+};
+
+// Rows i0.. of the selected inverse Z_BB of a panel: element (row i, column
+// k) sits at (row max, column min) of the lower triangle, which is stored in
+// two parts: own (columns of the supernode itself: the first gw positions,
+// leading dimension ld) and g (the rows below it, dense, leading dimension c,
+// position gw first).  Both pointers are those of position (0, 0), for g the
+// virtual one.  Chunks strictly below the block diagonal are read rows fast,
+// strictly above it k fast (transposed), in both cases through one
+// descriptor when the chunk's columns (or rows) lie in one part; a chunk that
+// crosses the parts takes a pointer per lane.
+// HERM: entries below the diagonal (row >= column of Z) come from one pair
+// of arrays and those above it from another (utown / utg elements further);
+// side 0 reads Z(i, k), side 1 Z(k, i).
+template <int ROWS, bool HERM>
+struct SymOp : LoadCount<ROWS> {
+  using LoadCount<ROWS>::N;
+  using LoadCount<ROWS>::J;
+  const double *own, *g;
+  int ld, c, gw, i0, nb, w, side;
+  int64_t utown, utg;
+  __device__ __forceinline__ SymOp(const double* own_, int ld_, const double* g_, int c_, int gw_, int i0_, int nb_,
+                                   int side_ = 0, int64_t utown_ = 0, int64_t utg_ = 0)
+      : own(uniform(own_)), g(uniform(g_)), ld(ld_), c(c_), gw(gw_), i0(i0_), nb(nb_), w(wave_id()), side(side_),
+        utown(utown_), utg(utg_) {}
+  __device__ __forceinline__ bool fast(int k0) const { return k0 + KD > i0; }
+  __device__ __forceinline__ void issue(int k0, dbl2* lds) const {
+    const bool low = !fast(k0), up = k0 >= i0 + ROWS;
+    const int lo0 = min(k0, i0);                                     // smallest and largest column read
+    const int lo1 = min(nb - 1, low ? k0 + KD - 1 : up ? i0 + ROWS - 1 : min(k0 + KD - 1, i0 + ROWS - 1));
+    const bool from_own = lo1 < gw, from_g = lo0 >= gw;
+    const int lane = threadIdx.x & 63;
+    if ((from_own || from_g) && (low || up || !HERM)) {
+      const int lz = from_own ? ld : c;
+      const double* z = from_own ? own : g;
+      if (HERM && low == (side == 1)) z += 2 * (from_own ? utown : utg);
+      z += 2 * ((int64_t)lo0 * lz + (low ? i0 : up ? k0 : 0));
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        if (N < 4 && w >= N) continue;
+        int n, k;
+        unsigned v;
+        if (low) {
+          slot_rows<ROWS>(w + 4 * j, lane, n, k);
+          v = __umul24(k, lz) + n;
+        } else {
+          slot_k(w + 4 * j, lane, n, k);
+          if (up) {
+            v = __umul24(n, lz) + k;
+          } else {
+            const int i = i0 + n, q = k0 + k;
+            v = __umul24(min(i, q) - lo0, lz) + max(i, q);
+          }
+        }
+        load_lds(z, i0 + n < nb && k0 + k < nb ? v * 16u : LANE_OUT, lds + (w + 4 * j) * 64);
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        if (N < 4 && w >= N) continue;
+        int n, k;
+        if (low) slot_rows<ROWS>(w + 4 * j, lane, n, k);
+        else slot_k(w + 4 * j, lane, n, k);
+        const int i = i0 + n, q = k0 + k;
+        const int lo = min(i, q), hi = max(i, q);
+        const bool og = lo >= gw;
+        int64_t e = (int64_t)lo * (og ? c : ld) + hi;
+        if (HERM && !(side ? q >= i : i >= q)) e += og ? utg : utown;
+        const double* p = (og ? g : own) + 2 * e;
+        load_lds_ptr(hi < nb ? p : kZeroElem, lds + (w + 4 * j) * 64);
+      }
+    }
+  }
+};
+
+// Per-column factors of the A operand: d_k at base + k stride (elements).
+struct DiagOp {
+  const double* base;
+  int64_t stride;
+  int K;
+  __device__ __forceinline__ DiagOp(const double* b, int64_t st, int K_) : base(uniform(b)), stride(st), K(K_) {}
+  __device__ __forceinline__ void issue(int k0, dbl2* lds) const {
+    if (threadIdx.x < KD) {
+      const int k = threadIdx.x;
+      load_lds(base + 2 * (stride * k0), k0 + k < K ? (unsigned)(k * stride) * 16u : LANE_OUT, lds);
+    }
+  }
+};
+struct NoDiag {
+  __device__ __forceinline__ void issue(int, dbl2*) const {}
+};
+
+// One stage on the matrix cores.  MASKED: only the block pairs (a, b) with
+// bit 2a + b of mask set (uniform over the wave; a branch per pair, one copy of
+// the code: a copy per mask spilled registers at four waves per SIMD).
+template <int NTILE, bool SCALE, bool MASKED, int SWZ>
+__device__ __forceinline__ void mfma_stage(Acc<true, NTILE>& acc, const dbl2* as, bool afast, const dbl2* bs, bool bfast,
+                                           const dbl2* ds, int mask) {
+  using G = Geo<NTILE>;
+  const int lane = threadIdx.x & 63;
+  const int w = threadIdx.x >> 6;
+  const int li = lane & 15, lk = lane >> 4;
+#pragma unroll
+  for (int ks = 0; ks < KD / 4; ++ks) {
+    const int k = ks * 4 + lk;
+    dbl2 av[G::BM], bv[G::BN];
+#pragma unroll
+    for (int t = 0; t < G::BM; ++t) {
+      const int m = block_row<NTILE, SWZ>(w, t) + li;
+      av[t] = as[afast ? m * 8 + (k ^ (li >> 1)) : k * 64 + m];
+    }
+#pragma unroll
+    for (int t = 0; t < G::BN; ++t) {
+      const int n = block_col<NTILE, SWZ>(w, t) + li;
+      bv[t] = bs[bfast ? n * 8 + (k ^ (li >> 1)) : k * NTILE + n];
+    }
+    if constexpr (SCALE) {
+      const dbl2 d = ds[k];
+#pragma unroll
+      for (int t = 0; t < G::BM; ++t) {
+        const cplx v = cmul(cplx{d.x, d.y}, cplx{av[t].x, av[t].y});
+        av[t] = dbl2{v.re, v.im};
+      }
+    }
+    auto first = [&](int a, int b) {
+      acc.re[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a].x, bv[b].x, acc.re[a][b], 0, 0, 0);
+      acc.im[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a].x, bv[b].y, acc.im[a][b], 0, 0, 0);
+    };
+    auto second = [&](int a, int b) {
+      acc.re[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a].y, bv[b].y, acc.re[a][b], 0, 0, 1);   // -ai bi
+      acc.im[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a].y, bv[b].x, acc.im[a][b], 0, 0, 0);
+    };
+    if constexpr (MASKED) {
+#pragma unroll
+      for (int a = 0; a < G::BM; ++a)
+#pragma unroll
+        for (int b = 0; b < G::BN; ++b)
+          if ((mask >> (2 * a + b)) & 1) {
+            first(a, b);
+            second(a, b);
+          }
+    } else {
+#pragma unroll
+      for (int a = 0; a < G::BM; ++a)
+#pragma unroll
+        for (int b = 0; b < G::BN; ++b) first(a, b);
+#pragma unroll
+      for (int a = 0; a < G::BM; ++a)
+#pragma unroll
+        for (int b = 0; b < G::BN; ++b) second(a, b);
+    }
+  }
+}
+
+// Waits for the caller's loads into LDS and its LDS reads, then for every
+// wave of the workgroup.
+__device__ __forceinline__ void stage_barrier() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// P += A[:, k] B[k, :] over k in [0, K): two stages, one barrier per stage.
+// A stage's loads start right after the barrier that ends the reads of its
+// buffer and have the other stage's MFMAs (and three other workgroups') to
+// land.
+template <int NTILE, class LV = AllLive, class OA, class OB, class OD>
+__device__ __forceinline__ void gemm_lds(Acc<true, NTILE>& acc, CStage<NTILE, !std::is_same<OD, NoDiag>::value>& s, int K,
+                                         const OA& oa, const OB& ob, const OD& od, LV lv = LV()) {
+  constexpr bool SC = !std::is_same<OD, NoDiag>::value;
+  if (K <= 0) return;
+  const int nc = (K + KD - 1) / KD;
+  auto issue = [&](int c, int q) {
+    oa.issue(c * KD, s.a[q]);
+    ob.issue(c * KD, s.b[q]);
+    od.issue(c * KD, s.d[SC ? q : 0]);
+  };
+  issue(0, 0);
+  int q = 0;
+  for (int c = 0; c < nc; ++c) {
+    stage_barrier();
+    if (c + 1 < nc) issue(c + 1, q ^ 1);
+    const int k0 = c * KD;
+    const bool fa = oa.fast(k0), fb = ob.fast(k0);
+    if constexpr (LV::kAll) {
+      mfma_stage<NTILE, SC, false, 0>(acc, s.a[q], fa, s.b[q], fb, s.d[SC ? q : 0], 15);
+    } else {
+      const int m = lv(k0);
+      if (m) mfma_stage<NTILE, SC, NTILE == 64, LV::kSwz>(acc, s.a[q], fa, s.b[q], fb, s.d[SC ? q : 0], m);
+    }
+    q ^= 1;
+  }
+}
 
 // --------------------------------------------------------------------------
 // small kernels
@@ -870,14 +1233,13 @@ __global__ void __launch_bounds__(NTD) k_diag(Src src) {
 }
 
 // L_Bp = A_Bp L_pp^{-T} D^{-1}: P[c][i] = sum_k Linv[c][k] A[i][k], then / d_c.
-// Panel products run on tiles of 64 x TNv (TNv = 64 or 128 rows, a runtime
-// option); with double-buffered LDS a 128-row tile uses 100 KB (one
-// workgroup per CU), a 64-row tile 67 KB (two per CU).
-#define PXS_LB(TNv) __launch_bounds__(NT, (TNv) == 64 ? 2 : 1)
+// Complex panel products run on tiles of 64 x TNv (TNv = 64, 32 or 16 rows,
+// pick_tile), at most 33 KB of LDS and 128 registers: four workgroups per CU.
+// Real ones on 64 or 128 rows (a runtime option).
+#define PXS_LB(CPLXv, TNv) __launch_bounds__(NT, (CPLXv) ? 4 : (TNv) == 64 ? 2 : 1)
 
 template <bool CPLX, int TN, class Src>
-__global__ void PXS_LB(TN) k_trsm(Src src) {
-  __shared__ Stage2<CPLX, TN> s;
+__global__ void PXS_LB(CPLX, TN) k_trsm(Src src) {
   __shared__ cplx dinv[64];
   Common c;
   PanelK p;
@@ -894,20 +1256,27 @@ __global__ void PXS_LB(TN) k_trsm(Src src) {
   }
   Acc<CPLX, TN> acc;
   acc.zero();
-  // L^{-1} is lower triangular: on 64-row tiles the all-zero blocks of a
-  // chunk are not multiplied
-  using LV = std::conditional_t<TN == 64, TriLive<true>, AllLive>;
-  gemm_pipe<CPLX, TN, false>(
-      acc, s, 0, p.wp,
-      [&](int m, int kg) -> cplx {   // Linv[c][k]: column k of the diagonal block
-        const cplx v = ld_or_zero<CPLX>(Ls, dbase + (int64_t)kg * p.ld + m, m < p.wp && kg < p.wp && m > kg);
-        return (m == kg && m < p.wp) ? cplx{1.0, 0.0} : v;
-      },
-      [&](int n, int kg) -> cplx {   // A[i][k]
-        const int ig = i0 + n;
-        return ld_or_zero<CPLX>(Ls, rbase + (int64_t)kg * p.ld + ig, kg < p.wp && ig < p.nb);
-      },
-      RowsFast(), NoScale(), LV());
+  // L^{-1} is lower triangular: the all-zero blocks of a chunk are not
+  // multiplied (for the real 128-row tiles they are)
+  using LV = std::conditional_t<CPLX || TN == 64, TriLive<true, CPLX ? TN : 64>, AllLive>;
+  if constexpr (CPLX) {
+    __shared__ CStage<TN, false> s;
+    gemm_lds<TN, LV>(acc, s, p.wp, TriOp<false>(Ls + 2 * dbase, p.ld, p.wp),
+                     ColsOp<TN>(Ls + 2 * (rbase + i0), p.ld, p.nb - i0, p.wp), NoDiag());
+  } else {
+    __shared__ Stage2<false, TN> s;
+    gemm_pipe<false, TN, false>(
+        acc, s, 0, p.wp,
+        [&](int m, int kg) -> cplx {   // Linv[c][k]: column k of the diagonal block
+          const cplx v = ld_or_zero<false>(Ls, dbase + (int64_t)kg * p.ld + m, m < p.wp && kg < p.wp && m > kg);
+          return (m == kg && m < p.wp) ? cplx{1.0, 0.0} : v;
+        },
+        [&](int n, int kg) -> cplx {   // A[i][k]
+          const int ig = i0 + n;
+          return ld_or_zero<false>(Ls, rbase + (int64_t)kg * p.ld + ig, kg < p.wp && ig < p.nb);
+        },
+        RowsFast(), NoScale(), LV());
+  }
   acc_foreach<CPLX, TN, LV::kSwz>(acc, [&](int m, int n, cplx v) {
     const int ig = i0 + n;
     if (m < p.wp && ig < p.nb) st_elem<CPLX>(Ls, rbase + (int64_t)m * p.ld + ig, cmul(v, dinv[m]));
@@ -918,8 +1287,7 @@ __global__ void PXS_LB(TN) k_trsm(Src src) {
 // supernode: A[r][c] -= sum_{k < p0} L[r][k] d_k L[c][k] for rows r >= p0 of
 // the row list and the panel's columns c.  P[c][r] = sum_k (d_k L[c][k]) L[r][k].
 template <bool CPLX, int TN, class Src>
-__global__ void PXS_LB(TN) k_int_update(Src src) {
-  __shared__ Stage2<CPLX, TN> s;
+__global__ void PXS_LB(CPLX, TN) k_int_update(Src src) {
   Common c;
   PanelK p;
   int bx, by;
@@ -931,19 +1299,28 @@ __global__ void PXS_LB(TN) k_int_update(Src src) {
   const int64_t cbase = p.off + p.p0;        // element (row p0, column 0)
   Acc<CPLX, TN> acc;
   acc.zero();
-  gemm_pipe<CPLX, TN, false>(
-      acc, s, 0, p.p0,
-      [&](int m, int kg) -> cplx {   // L[p0 + c][k] (times d_k on the way to the MFMAs)
-        return ld_or_zero<CPLX>(Ls, cbase + (int64_t)kg * p.ld + m, m < p.wp && kg < p.p0);
-      },
-      [&](int n, int kg) -> cplx {   // L[p0 + r][k]
-        const int rg = r0 + n;
-        return ld_or_zero<CPLX>(Ls, cbase + (int64_t)kg * p.ld + rg, kg < p.p0 && rg < nrows);
-      },
-      RowsFast(),
-      [&](int kg) -> cplx {          // d_k
-        return ld_or_zero<CPLX>(Ls, p.off + (int64_t)kg * p.ld + kg, kg < p.p0);
-      });
+  if constexpr (CPLX) {
+    // A: L[p0 + c][k], scaled by d_k on the way to the MFMAs; B: L[p0 + r][k]
+    __shared__ CStage<TN, true> s;
+    gemm_lds<TN>(acc, s, p.p0, ColsOp<64>(Ls + 2 * cbase, p.ld, p.wp, p.p0),
+                 ColsOp<TN>(Ls + 2 * (cbase + r0), p.ld, nrows - r0, p.p0),
+                 DiagOp(Ls + 2 * p.off, (int64_t)p.ld + 1, p.p0));
+  } else {
+    __shared__ Stage2<false, TN> s;
+    gemm_pipe<false, TN, false>(
+        acc, s, 0, p.p0,
+        [&](int m, int kg) -> cplx {   // L[p0 + c][k] (times d_k on the way to the MFMAs)
+          return ld_or_zero<false>(Ls, cbase + (int64_t)kg * p.ld + m, m < p.wp && kg < p.p0);
+        },
+        [&](int n, int kg) -> cplx {   // L[p0 + r][k]
+          const int rg = r0 + n;
+          return ld_or_zero<false>(Ls, cbase + (int64_t)kg * p.ld + rg, kg < p.p0 && rg < nrows);
+        },
+        RowsFast(),
+        [&](int kg) -> cplx {          // d_k
+          return ld_or_zero<false>(Ls, p.off + (int64_t)kg * p.ld + kg, kg < p.p0);
+        });
+  }
   acc_sub_into<CPLX, TN>(acc, Ls, [&](int m, int n, int64_t& e) {
     const int rg = r0 + n;
     // clamped into the panel (in bounds for skipped elements)
@@ -967,15 +1344,14 @@ __device__ __forceinline__ void tri_index(int b, int& ti, int& tj) {
 // with K = all of its columns (p0 = 0, wp = w_J, B = the rows below it).
 // P[j][i] = sum_k (d_k L[j][k]) L[i][k].
 template <bool CPLX, int TN, class Src>
-__global__ void PXS_LB(TN) k_update(Src src) {
-  __shared__ Stage2<CPLX, TN> s;
+__global__ void PXS_LB(CPLX, TN) k_update(Src src) {
   Common c;
   PanelK p;
   int bx, by;
   locate(src, c, p, bx, by, true);
   const int sh = by;
   double* Ls = shift_base<CPLX>(c, sh);
-  // tiles: 64 columns j (m) by 128 rows i (n); only tiles that reach the
+  // tiles: 64 columns j (m) by TN rows i (n); only tiles that reach the
   // lower triangle (some i >= some j) do work
   const int nti = (p.nb + TN - 1) / TN;
   const int tj = bx / nti, ti = bx % nti;
@@ -986,20 +1362,29 @@ __global__ void PXS_LB(TN) k_update(Src src) {
   const int kb = p.p0, ke = p.p0 + p.wp;
   Acc<CPLX, TN> acc;
   acc.zero();
-  gemm_pipe<CPLX, TN, false>(
-      acc, s, kb, ke,
-      [&](int m, int kg) -> cplx {   // L[j][k] (times d_k on the way to the MFMAs)
-        const int jg = j0 + m;
-        return ld_or_zero<CPLX>(Ls, rbase + (int64_t)kg * p.ld + jg, kg < ke && jg < p.nb);
-      },
-      [&](int n, int kg) -> cplx {
-        const int ig = i0 + n;
-        return ld_or_zero<CPLX>(Ls, rbase + (int64_t)kg * p.ld + ig, kg < ke && ig < p.nb);
-      },
-      RowsFast(),
-      [&](int kg) -> cplx {          // d_k
-        return ld_or_zero<CPLX>(Ls, p.off + (int64_t)kg * p.ld + kg, kg < ke);
-      });
+  if constexpr (CPLX) {
+    __shared__ CStage<TN, true> s;
+    const int64_t k0 = rbase + (int64_t)kb * p.ld;
+    gemm_lds<TN>(acc, s, ke - kb, ColsOp<64>(Ls + 2 * (k0 + j0), p.ld, p.nb - j0, ke - kb),
+                 ColsOp<TN>(Ls + 2 * (k0 + i0), p.ld, p.nb - i0, ke - kb),
+                 DiagOp(Ls + 2 * (p.off + (int64_t)kb * (p.ld + 1)), (int64_t)p.ld + 1, ke - kb));
+  } else {
+    __shared__ Stage2<false, TN> s;
+    gemm_pipe<false, TN, false>(
+        acc, s, kb, ke,
+        [&](int m, int kg) -> cplx {   // L[j][k] (times d_k on the way to the MFMAs)
+          const int jg = j0 + m;
+          return ld_or_zero<false>(Ls, rbase + (int64_t)kg * p.ld + jg, kg < ke && jg < p.nb);
+        },
+        [&](int n, int kg) -> cplx {
+          const int ig = i0 + n;
+          return ld_or_zero<false>(Ls, rbase + (int64_t)kg * p.ld + ig, kg < ke && ig < p.nb);
+        },
+        RowsFast(),
+        [&](int kg) -> cplx {          // d_k
+          return ld_or_zero<false>(Ls, p.off + (int64_t)kg * p.ld + kg, kg < ke);
+        });
+  }
   const int64_t* cmap = c.colmap + p.cm;
   const int64_t* cseg = c.colseg + p.cm;
   acc_sub_into<CPLX, TN>(acc, Ls, [&](int m, int n, int64_t& e) {
@@ -1023,8 +1408,8 @@ __device__ __forceinline__ double* wbase(const Common& c, int sh) {
 
 // W = L_Bp Linv: P[c][i] = sum_k Linv[k][c] L[i][k]; W stored W[c * nb + i].
 template <int TN, class Src>
-__global__ void PXS_LB(TN) k_lhat(Src src) {
-  __shared__ Stage2<true, TN> s;
+__global__ void PXS_LB(true, TN) k_lhat(Src src) {
+  __shared__ CStage<TN, false> s;
   Common c;
   PanelK p;
   int bx, by;
@@ -1038,18 +1423,9 @@ __global__ void PXS_LB(TN) k_lhat(Src src) {
   Acc<true, TN> acc;
   acc.zero();
   // A[m][k] = L^{-1}[k][m] vanishes for k < m (see k_trsm)
-  using LV = std::conditional_t<TN == 64, TriLive<false>, AllLive>;
-  gemm_pipe<true, TN, true>(
-      acc, s, 0, p.wp,
-      [&](int m, int kg) -> cplx {   // Linv[k][c]: column c of the diagonal block, rows k
-        const cplx v = ld_or_zero<true>(Ls, dbase + (int64_t)m * p.ld + kg, m < p.wp && kg < p.wp && kg > m);
-        return (kg == m && m < p.wp) ? cplx{1.0, 0.0} : v;
-      },
-      [&](int n, int kg) -> cplx {
-        const int ig = i0 + n;
-        return ld_or_zero<true>(Ls, rbase + (int64_t)kg * p.ld + ig, kg < p.wp && ig < p.nb);
-      },
-      RowsFast(), NoScale(), LV());
+  using LV = TriLive<false, TN>;
+  gemm_lds<TN, LV>(acc, s, p.wp, TriOp<true>(Ls + 2 * dbase, p.ld, p.wp),
+                   ColsOp<TN>(Ls + 2 * (rbase + i0), p.ld, p.nb - i0, p.wp), NoDiag());
   acc_foreach<true, TN, LV::kSwz>(acc, [&](int m, int n, cplx v) {
     const int ig = i0 + n;
     if (m < p.wp && ig < p.nb) st_elem<true>(W, (int64_t)m * p.nb + ig, v);
@@ -1061,8 +1437,8 @@ __global__ void PXS_LB(TN) k_lhat(Src src) {
 // storage (column min(i, k), row max(i, k)), the part in the rows below it
 // from the dense copy G of Z_CC made by k_gather_cc.
 template <int TN, class Src>
-__global__ void PXS_LB(TN) k_selinv_off(Src src) {
-  __shared__ Stage2<true, TN> s;
+__global__ void PXS_LB(true, TN) k_selinv_off(Src src) {
+  __shared__ CStage<TN, false> s;
   Common c;
   PanelK p;
   int bx, by;
@@ -1073,26 +1449,13 @@ __global__ void PXS_LB(TN) k_selinv_off(Src src) {
   const double* G = c.G + c.gstride * by;
   const int i0 = bx * TN;
   const int base = p.p0 + p.wp;
+  const int gw = p.w - base;   // rows of B inside the supernode
   Acc<true, TN> acc;
   acc.zero();
-  gemm_pipe<true, TN, true>(
-      acc, s, 0, p.nb,
-      [&](int m, int kg) -> cplx {
-        return ld_or_zero<true>(W, (int64_t)m * p.nb + kg, m < p.wp && kg < p.nb);
-      },
-      [&](int n, int kg) -> cplx {
-        const int ig = i0 + n;
-        const int qk = base + kg, qi = base + ig;
-        const int lo = min(qi, qk), hi = max(qi, qk);
-        const bool in_g = lo >= p.w;
-        const double* src = in_g ? G : Ls;
-        const int64_t e = in_g ? (int64_t)(lo - p.w) * p.c + (hi - p.w) : p.off + (int64_t)lo * p.ld + hi;
-        return ld_or_zero<true>(src, e, kg < p.nb && ig < p.nb);
-      },
-      // both sources are lower triangles stored by column: rows are
-      // contiguous for each k when the whole chunk lies on or below the
-      // diagonal of the tile; otherwise k is contiguous
-      [&](int k0) -> bool { return !(i0 >= k0 + KC - 1); });
+  gemm_lds<TN>(acc, s, p.nb, RowsOp<64>(W, p.nb, p.wp, p.nb),
+               SymOp<TN, false>(Ls + 2 * (p.off + (int64_t)base * (p.ld + 1)), p.ld, G - 2 * (int64_t)gw * (p.c + 1), p.c,
+                                gw, i0, p.nb),
+               NoDiag());
   const int64_t rbase = p.off + (int64_t)p.p0 * p.ld + base;
   acc_foreach<true, TN>(acc, [&](int m, int n, cplx v) {
     const int ig = i0 + n;
@@ -1145,8 +1508,8 @@ __global__ void __launch_bounds__(NT) k_gather_cc(Src src) {
 
 // Partial W^T Z_Bp over k in [split * SPLIT_ROWS, ...): P[c][r] = sum_k Z[k][c] W[k][r].
 template <class Src>
-__global__ void PXS_LB(64) k_selinv_diag_partial(Src src) {
-  __shared__ Stage2<true, TM> s;
+__global__ void PXS_LB(true, 64) k_selinv_diag_partial(Src src) {
+  __shared__ CStage<TM, false> s;
   Common c;
   PanelK p;
   int bx, by;
@@ -1163,15 +1526,8 @@ __global__ void PXS_LB(64) k_selinv_diag_partial(Src src) {
   acc.zero();
   // Z_pp is symmetric and stored by its lower triangle: only P[c][r], r >= c,
   // is summed by k_selinv_diag_final, so the blocks below that are skipped
-  gemm_pipe<true, TM, true>(
-      acc, s, kb, ke,
-      [&](int m, int kg) -> cplx {
-        return ld_or_zero<true>(Ls, rbase + (int64_t)m * p.ld + kg, m < p.wp && kg < ke);
-      },
-      [&](int n, int kg) -> cplx {
-        return ld_or_zero<true>(W, (int64_t)n * p.nb + kg, n < p.wp && kg < ke);
-      },
-      KFast(), NoScale(), UpperLive());
+  gemm_lds<TM, UpperLive>(acc, s, ke - kb, RowsOp<64>(Ls + 2 * (rbase + kb), p.ld, p.wp, ke - kb),
+                          RowsOp<TM>(W + 2 * (int64_t)kb, p.nb, p.wp, ke - kb), NoDiag());
   double* out = part + 2 * (int64_t)sp * 64 * 64;
   acc_foreach<true, TM, UpperLive::kSwz>(acc, [&](int m, int n, cplx v) { st_elem<true>(out, (int64_t)m * 64 + n, v); });
 }
@@ -1418,6 +1774,57 @@ Common make_common(const Symbolic& S, void* L, void* work) {
   return c;
 }
 
+// Tile width of a complex panel product: of 64, 32 and 16 columns the one
+// whose rounds over the compute units take least time.  tiles(tn) is the
+// number of workgroups at width tn.  A round of narrower tiles is shorter in
+// proportion, but the operand loads weigh more: 69.0, 68.1 and 60.7 TFLOP/s
+// on a full launch (4096 rows x 32 shifts), hence the rates.  At 884 rows x
+// 60 shifts (4, 7 and 14 rounds) 54.4, 59.9 and 53.6 TFLOP/s, at 452 x 40 (2,
+// 3, 5 rounds) 33.3, 43.4 and 47.8, at 130 x 40 (1, 1, 2) 13.7, 22.6 and 22.2.
+constexpr int NCU = 256;
+template <class F>
+int pick_tile(F tiles) {
+  const int width[3] = {64, 32, 16};
+  const double rate[3] = {1.0, 0.985, 0.88};
+  int best = 64;
+  double cost = 0.0;
+  for (int q = 0; q < 3; ++q) {
+    const int64_t rounds = ((int64_t)tiles(width[q]) + NCU - 1) / NCU;
+    const double t = (double)rounds * width[q] / rate[q];
+    if (q == 0 || t < cost) {
+      best = width[q];
+      cost = t;
+    }
+  }
+  return best;
+}
+inline int tiles_of(int rows, int tn) { return (rows + tn - 1) / tn; }
+// tiles of an ancestor update: 64 columns by tn rows, those in the lower part
+inline int64_t update_tiles(int below, int tn) {
+  int64_t n = 0;
+  for (int j0 = 0; j0 < below; j0 += TM) n += tiles_of(below, tn) - j0 / tn;
+  return n;
+}
+
+// f(std::integral_constant<int, tn>) for a width of pick_tile
+template <class F>
+void with_tile(int tn, F f) {
+  if (tn == 16) f(std::integral_constant<int, 16>());
+  else if (tn == 32) f(std::integral_constant<int, 32>());
+  else f(std::integral_constant<int, 64>());
+}
+// the same for the real kernels: 64 or 128 rows (pxs_options.tile_rows)
+template <class F>
+void with_tile_real(int tn, F f) {
+  if (tn == 128) f(std::integral_constant<int, 128>());
+  else f(std::integral_constant<int, 64>());
+}
+template <bool CPLX, class F>
+void with_tile_of(int tn, F f) {
+  if constexpr (CPLX) with_tile(tn, f);
+  else with_tile_real(tn, f);
+}
+
 #define PXS_CHECK_LAUNCH()                         \
   do {                                             \
     hipError_t e_ = hipGetLastError();             \
@@ -1572,6 +1979,8 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
   const int TR = S.tile_rows;
   const double fm = CPLX ? 8.0 : 2.0;   // flops per multiply-add
   const double eb = CPLX ? 16.0 : 8.0;  // bytes per element
+  // tile width of a product over `rows` rows
+  auto tile = [&](int rows) { return CPLX ? pick_tile([&](int tn) { return (int64_t)tiles_of(rows, tn) * nshift; }) : TR; };
   // the panel work of one panel: left-looking update from the earlier
   // columns of its supernode, LDL^T of the diagonal block, the rows below
   auto panel_work = [&](const Panel& P, hipStream_t s) -> int {
@@ -1581,10 +1990,10 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
       const int nrows = k.ld - k.p0;
       ProfScope ps(KC_UPDATE, s, fm * nshift * xm.intu, eb * nshift * ((double)nrows * k.p0 + 2.0 * nrows * k.wp),
                    fm * nshift * ((double)nrows * k.wp - 0.5 * k.wp * (k.wp - 1)) * k.p0);
-      if (TR == 64)
-        hipLaunchKernelGGL((k_int_update<CPLX, 64, OnePanel>), dim3((nrows + 63) / 64, nshift), dim3(NT), 0, s, OnePanel{c, k});
-      else
-        hipLaunchKernelGGL((k_int_update<CPLX, 128, OnePanel>), dim3((nrows + 127) / 128, nshift), dim3(NT), 0, s, OnePanel{c, k});
+      with_tile_of<CPLX>(tile(nrows), [&](auto t) {
+        constexpr int TN = decltype(t)::value;
+        hipLaunchKernelGGL((k_int_update<CPLX, TN, OnePanel>), dim3(tiles_of(nrows, TN), nshift), dim3(NT), 0, s, OnePanel{c, k});
+      });
     }
     {
       ProfScope ps(KC_DIAG, s, fm * nshift * xm.diag, eb * nshift * (double)k.wp * (k.wp + 1),
@@ -1592,13 +2001,12 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
       hipLaunchKernelGGL((k_diag<CPLX, OnePanel>), dim3(1, nshift), dim3(NTD), 0, s, OnePanel{c, k});
     }
     if (k.nb > 0) {
-      const int nt = (k.nb + TR - 1) / TR;
       ProfScope ps(KC_TRSM, s, fm * nshift * xm.trsm, eb * nshift * (2.0 * k.nb * k.wp + 0.5 * k.wp * (k.wp + 1)),
                    fm * nshift * (double)k.nb * k.wp * (k.wp + 1) / 2.0);
-      if (TR == 64)
-        hipLaunchKernelGGL((k_trsm<CPLX, 64, OnePanel>), dim3(nt, nshift), dim3(NT), 0, s, OnePanel{c, k});
-      else
-        hipLaunchKernelGGL((k_trsm<CPLX, 128, OnePanel>), dim3(nt, nshift), dim3(NT), 0, s, OnePanel{c, k});
+      with_tile_of<CPLX>(tile(k.nb), [&](auto t) {
+        constexpr int TN = decltype(t)::value;
+        hipLaunchKernelGGL((k_trsm<CPLX, TN, OnePanel>), dim3(tiles_of(k.nb, TN), nshift), dim3(NT), 0, s, OnePanel{c, k});
+      });
     }
     PXS_CHECK_LAUNCH();
     return 0;
@@ -1613,14 +2021,15 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
     u.p0 = 0;
     u.wp = w;
     u.nb = below;
-    const int ntj = (below + TM - 1) / TM, nti = (below + TR - 1) / TR;
+    const int tn = CPLX ? pick_tile([&](int q) { return update_tiles(below, q) * nshift; }) : TR;
     ProfScope ps(KC_UPDATE, s, fm * nshift * S.xm_update[P.J],
                  eb * nshift * ((double)below * w + (double)below * (below + 1)),
                  fm * nshift * (double)below * (below + 1) / 2.0 * w);
-    if (TR == 64)
-      hipLaunchKernelGGL((k_update<CPLX, 64, OnePanel>), dim3(ntj * nti, nshift), dim3(NT), 0, s, OnePanel{c, u});
-    else
-      hipLaunchKernelGGL((k_update<CPLX, 128, OnePanel>), dim3(ntj * nti, nshift), dim3(NT), 0, s, OnePanel{c, u});
+    with_tile_of<CPLX>(tn, [&](auto t) {
+      constexpr int TN = decltype(t)::value;
+      hipLaunchKernelGGL((k_update<CPLX, TN, OnePanel>), dim3(tiles_of(below, TM) * tiles_of(below, TN), nshift), dim3(NT), 0,
+                         s, OnePanel{c, u});
+    });
     PXS_CHECK_LAUNCH();
     return 0;
   };
@@ -1652,6 +2061,7 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
     struct FOp {
       int32_t kind, J;
       bool first, last;
+      int32_t rows;   // rows of the product (its tiles follow from the launch's tile width)
       GroupItem it;
       double work, bytes, stored;
     };
@@ -1661,8 +2071,7 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
       if (pfirst[J] < 0) continue;
       std::vector<FOp>& ops = lane[S.sel_stream[J]];
       const size_t n0 = ops.size();
-      auto add = [&](std::vector<FOp>& v, int32_t kind, const PanelK& k, int64_t tiles, double w, double b,
-                     double s) {
+      auto add = [&](std::vector<FOp>& v, int32_t kind, const PanelK& k, int32_t rows, double w, double b, double s) {
         FOp o;
         o.kind = kind;
         o.J = J;
@@ -1671,8 +2080,9 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
         o.it.c = c;
         o.it.p = k;
         o.it.start = 0;
-        o.it.tiles = (int32_t)tiles;
+        o.it.tiles = 0;
         o.it.nsh = nshift;
+        o.rows = rows;
         o.work = w;
         o.bytes = b;
         o.stored = s;
@@ -1683,14 +2093,14 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
         const PanelMacs& xm = S.xm_panel[ip];
         if (k.p0 > 0) {
           const int nrows = k.ld - k.p0;
-          add(ops, FK_INT, k, (nrows + TR - 1) / TR, fm * nshift * xm.intu,
+          add(ops, FK_INT, k, nrows, fm * nshift * xm.intu,
               eb * nshift * ((double)nrows * k.p0 + 2.0 * nrows * k.wp),
               fm * nshift * ((double)nrows * k.wp - 0.5 * k.wp * (k.wp - 1)) * k.p0);
         }
         add(ops, FK_DIAG, k, 1, fm * nshift * xm.diag, eb * nshift * (double)k.wp * (k.wp + 1),
             fm * nshift * (double)k.wp * k.wp * k.wp / 3.0);
         if (k.nb > 0)
-          add(ops, FK_TRSM, k, (k.nb + TR - 1) / TR, fm * nshift * xm.trsm,
+          add(ops, FK_TRSM, k, k.nb, fm * nshift * xm.trsm,
               eb * nshift * (2.0 * k.nb * k.wp + 0.5 * k.wp * (k.wp + 1)),
               fm * nshift * (double)k.nb * k.wp * (k.wp + 1) / 2.0);
       }
@@ -1732,10 +2142,17 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
       grp.n = 0;
       int64_t start = 0;
       double w = 0.0, b = 0.0, s = 0.0;
+      const int tn = !CPLX ? TR : pick_tile([&](int tq) {
+        int64_t n = 0;
+        for (int q = 0; q < NS; ++q)
+          if (ready(q) && lane[q][pos[q]].kind == kind) n += (int64_t)tiles_of(lane[q][pos[q]].rows, tq) * nshift;
+        return n;
+      });
       for (int q = 0; q < NS; ++q) {
         if (!ready(q) || lane[q][pos[q]].kind != kind) continue;
         const FOp& o = lane[q][pos[q]];
         GroupItem it = o.it;
+        it.tiles = kind == FK_DIAG ? 1 : tiles_of(o.rows, tn);
         it.start = start;
         start += (int64_t)it.tiles * it.nsh;
         grp.it[grp.n++] = it;
@@ -1749,15 +2166,17 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
       const dim3 grid((unsigned)start);
       if (kind == FK_INT) {
         ProfScope ps(KC_UPDATE, st, w, b, s);
-        if (TR == 64) hipLaunchKernelGGL((k_int_update<CPLX, 64, LaneGroup>), grid, dim3(NT), 0, st, grp);
-        else hipLaunchKernelGGL((k_int_update<CPLX, 128, LaneGroup>), grid, dim3(NT), 0, st, grp);
+        with_tile_of<CPLX>(tn, [&](auto t) {
+          hipLaunchKernelGGL((k_int_update<CPLX, decltype(t)::value, LaneGroup>), grid, dim3(NT), 0, st, grp);
+        });
       } else if (kind == FK_DIAG) {
         ProfScope ps(KC_DIAG, st, w, b, s);
         hipLaunchKernelGGL((k_diag<CPLX, LaneGroup>), grid, dim3(NTD), 0, st, grp);
       } else {
         ProfScope ps(KC_TRSM, st, w, b, s);
-        if (TR == 64) hipLaunchKernelGGL((k_trsm<CPLX, 64, LaneGroup>), grid, dim3(NT), 0, st, grp);
-        else hipLaunchKernelGGL((k_trsm<CPLX, 128, LaneGroup>), grid, dim3(NT), 0, st, grp);
+        with_tile_of<CPLX>(tn, [&](auto t) {
+          hipLaunchKernelGGL((k_trsm<CPLX, decltype(t)::value, LaneGroup>), grid, dim3(NT), 0, st, grp);
+        });
       }
       PXS_CHECK_LAUNCH();
       ++nl;
@@ -1891,21 +2310,22 @@ struct LaneOp {
   int32_t J;
   bool first;   // first operation of supernode J
   bool last;    // last operation of J
+  int32_t rows; // rows of an L-hat or off-diagonal product (its tiles follow from the launch's tile width), else 0
   GroupItem it;
   double work, bytes, stored;   // profile figures (ProfScope)
 };
 
-int lane_launch(int32_t kind, int TR, const LaneGroup& g, int64_t blocks, hipStream_t st) {
+int lane_launch(int32_t kind, int tn, const LaneGroup& g, int64_t blocks, hipStream_t st) {
   const dim3 grid((unsigned)blocks);
   switch (kind) {
     case LK_GATHER: hipLaunchKernelGGL(k_gather_cc<LaneGroup>, grid, dim3(NT), 0, st, g); break;
     case LK_LHAT:
-      if (TR == 64) hipLaunchKernelGGL((k_lhat<64, LaneGroup>), grid, dim3(NT), 0, st, g);
-      else hipLaunchKernelGGL((k_lhat<128, LaneGroup>), grid, dim3(NT), 0, st, g);
+      with_tile(tn, [&](auto t) { hipLaunchKernelGGL((k_lhat<decltype(t)::value, LaneGroup>), grid, dim3(NT), 0, st, g); });
       break;
     case LK_OFF:
-      if (TR == 64) hipLaunchKernelGGL((k_selinv_off<64, LaneGroup>), grid, dim3(NT), 0, st, g);
-      else hipLaunchKernelGGL((k_selinv_off<128, LaneGroup>), grid, dim3(NT), 0, st, g);
+      with_tile(tn, [&](auto t) {
+        hipLaunchKernelGGL((k_selinv_off<decltype(t)::value, LaneGroup>), grid, dim3(NT), 0, st, g);
+      });
       break;
     case LK_DPART: hipLaunchKernelGGL(k_selinv_diag_partial<LaneGroup>, grid, dim3(NT), 0, st, g); break;
     case LK_DFIN: hipLaunchKernelGGL(k_selinv_diag_final<LaneGroup>, grid, dim3(NTF), 0, st, g); break;
@@ -1921,7 +2341,6 @@ int run_selinv_lanes(const Symbolic& S, int nshift, void* L, void* work, hipStre
   const int NL = S.sel_nstreams;
   if (NL < 1 || NL > MAX_LANES) return (int)hipErrorInvalidValue;
   const int ns = S.nsuper;
-  const int TR = S.tile_rows;
   const int chunk = (S.selinv_chunk > 0 && S.selinv_chunk < nshift) ? S.selinv_chunk : nshift;
   // workspace views as on NL streams (selinv_work_bytes)
   std::vector<Common> cs(NL, make_common(S, L, work));
@@ -1954,6 +2373,7 @@ int run_selinv_lanes(const Symbolic& S, int nshift, void* L, void* work, hipStre
         o.it.start = 0;
         o.it.tiles = (int32_t)tiles;
         o.it.nsh = nsh;
+        o.rows = (kind == LK_LHAT || kind == LK_OFF) ? k.nb : 0;
         o.work = w;
         o.bytes = b;
         o.stored = s;
@@ -1974,10 +2394,9 @@ int run_selinv_lanes(const Symbolic& S, int nshift, void* L, void* work, hipStre
         k.sh0 = sh0;
         const PanelMacs& xm = S.xm_panel[ip];
         if (k.nb > 0) {
-          const int64_t nt = (k.nb + TR - 1) / TR;
-          add(LK_LHAT, k, nt, 0.0, 16.0 * nsh * (2.0 * k.nb * k.wp + 0.5 * k.wp * (k.wp + 1)),
+          add(LK_LHAT, k, 0, 0.0, 16.0 * nsh * (2.0 * k.nb * k.wp + 0.5 * k.wp * (k.wp + 1)),
               8.0 * nsh * (double)k.nb * k.wp * (k.wp + 1) / 2.0);
-          add(LK_OFF, k, nt, 8.0 * nsh * xm.off, 16.0 * nsh * (0.5 * k.nb * (k.nb + 1) + 2.0 * k.nb * k.wp),
+          add(LK_OFF, k, 0, 8.0 * nsh * xm.off, 16.0 * nsh * (0.5 * k.nb * (k.nb + 1) + 2.0 * k.nb * k.wp),
               8.0 * nsh * (double)k.nb * k.nb * k.wp);
           add(LK_DPART, k, k.split, 8.0 * nsh * xm.sdiag, 16.0 * nsh * (2.0 * k.nb * k.wp + (double)k.wp * k.wp),
               8.0 * nsh * (double)k.nb * k.wp * k.wp);
@@ -2013,10 +2432,17 @@ int run_selinv_lanes(const Symbolic& S, int nshift, void* L, void* work, hipStre
       grp.n = 0;
       int64_t start = 0;
       double w = 0.0, b = 0.0, s = 0.0;
+      const int tn = pick_tile([&](int tq) {
+        int64_t n = 0;
+        for (int q = 0; q < NL; ++q)
+          if (ready(q) && lane[q][pos[q]].kind == kind) n += (int64_t)tiles_of(lane[q][pos[q]].rows, tq) * nsh;
+        return n;
+      });
       for (int q = 0; q < NL; ++q) {
         if (!ready(q) || lane[q][pos[q]].kind != kind) continue;
         const LaneOp& o = lane[q][pos[q]];
         GroupItem it = o.it;
+        if (o.rows > 0) it.tiles = tiles_of(o.rows, tn);
         it.start = start;
         start += (int64_t)it.tiles * it.nsh;
         grp.it[grp.n++] = it;
@@ -2029,7 +2455,7 @@ int run_selinv_lanes(const Symbolic& S, int nshift, void* L, void* work, hipStre
       if (start > (int64_t)INT32_MAX) return (int)hipErrorInvalidConfiguration;
       {
         ProfScope ps(kLaneClass[kind], st, w, b, s);
-        const int e = lane_launch(kind, TR, grp, start, st);
+        const int e = lane_launch(kind, tn, grp, start, st);
         if (e) return e;
       }
       ++nl;
@@ -2052,7 +2478,6 @@ int run_selinv(const Symbolic& S, int nshift, void* L, void* work, hipStream_t s
   const bool single = inorder || (cap != hipStreamCaptureStatusNone) || S.sel_nstreams == 1;
   const int NS = single ? 1 : S.sel_nstreams;
   const int ns = S.nsuper;
-  const int TR = S.tile_rows;
   // one stream needs no pool: the in-order path creates no streams or events
   int err = single ? 0 : ensure_pool(NS - 1, events ? 0 : selinv_event_count(S));
   if (err) return err;
@@ -2115,25 +2540,25 @@ int run_selinv(const Symbolic& S, int nshift, void* L, void* work, hipStream_t s
         k.sh0 = sh0;
         const PanelMacs& xm = S.xm_panel[ip];
         if (k.nb > 0) {
-          const int nt = (k.nb + TR - 1) / TR;
+          const int tn = pick_tile([&](int q2) { return (int64_t)tiles_of(k.nb, q2) * nsh; });
           {
             // L-hat is a by-product of the blocked algorithm: no exact flops
             ProfScope ps(KC_LHAT, sj, 0.0, 16.0 * nsh * (2.0 * k.nb * k.wp + 0.5 * k.wp * (k.wp + 1)),
                          8.0 * nsh * (double)k.nb * k.wp * (k.wp + 1) / 2.0);
-            if (TR == 64)
-              hipLaunchKernelGGL((k_lhat<64, OnePanel>), dim3(nt, nsh), dim3(NT), 0, sj, OnePanel{c, k});
-            else
-              hipLaunchKernelGGL((k_lhat<128, OnePanel>), dim3(nt, nsh), dim3(NT), 0, sj, OnePanel{c, k});
+            with_tile(tn, [&](auto t) {
+              constexpr int TN = decltype(t)::value;
+              hipLaunchKernelGGL((k_lhat<TN, OnePanel>), dim3(tiles_of(k.nb, TN), nsh), dim3(NT), 0, sj, OnePanel{c, k});
+            });
           }
           {
             // bytes: Z_BB (one triangle), L-hat read, Z_Bp written
             ProfScope ps(KC_SELINV_OFF, sj, 8.0 * nsh * xm.off,
                          16.0 * nsh * (0.5 * k.nb * (k.nb + 1) + 2.0 * k.nb * k.wp),
                          8.0 * nsh * (double)k.nb * k.nb * k.wp);
-            if (TR == 64)
-              hipLaunchKernelGGL((k_selinv_off<64, OnePanel>), dim3(nt, nsh), dim3(NT), 0, sj, OnePanel{c, k});
-            else
-              hipLaunchKernelGGL((k_selinv_off<128, OnePanel>), dim3(nt, nsh), dim3(NT), 0, sj, OnePanel{c, k});
+            with_tile(tn, [&](auto t) {
+              constexpr int TN = decltype(t)::value;
+              hipLaunchKernelGGL((k_selinv_off<TN, OnePanel>), dim3(tiles_of(k.nb, TN), nsh), dim3(NT), 0, sj, OnePanel{c, k});
+            });
           }
           {
             ProfScope ps(KC_SELINV_DIAG, sj, 8.0 * nsh * xm.sdiag,
