@@ -959,16 +959,14 @@ __global__ void k_absmax_partial(const double* __restrict__ H, const double* __r
     partial[2 * blockIdx.x + 1] = sh[1][0];
   }
 }
+// One wave per quantity (grid-wide partials of at most ABSMAX_BLOCKS blocks):
+// a single thread over the 512 partials took 54 us.
 __global__ void k_absmax_final(const double* partial, int nb, double* out) {
-  if (threadIdx.x == 0) {
-    double mh = 0.0, ms = 0.0;
-    for (int b = 0; b < nb; ++b) {
-      mh = fmax(mh, partial[2 * b]);
-      ms = fmax(ms, partial[2 * b + 1]);
-    }
-    out[0] = mh;
-    out[1] = ms;
-  }
+  const int q = threadIdx.x >> 6, lane = threadIdx.x & 63;   // q: 0 for H, 1 for S
+  double m = 0.0;
+  for (int b = lane; b < nb; b += 64) m = fmax(m, partial[2 * b + q]);
+  for (int s = 32; s > 0; s >>= 1) m = fmax(m, __shfl_xor(m, s));
+  if (lane == 0) out[q] = m;
 }
 
 // A_l = H - w_l S on the input pattern (the rest of the storage is zero).
@@ -1104,30 +1102,121 @@ __device__ __forceinline__ void locate(const LaneGroup& src, Common& c, PanelK& 
   by = local / it.tiles;
 }
 
-// Dense LDL^T of the panel's wp x wp diagonal block in LDS, with L_pp^{-1}
-// accumulated along the way.  Step k (one barrier per step, 512 threads, row
-// r = t % 64 and every eighth column per thread):
-//   trailing update  A[r][j] -= d_k L[r][k] L[j][k]            k+1 < j < r
-//   next column      L[r][k+1] = (A[r][k+1] - d_k L[r][k] L[k+1][k]) / d_{k+1}
-//   pivots           D[j] -= d_k L[j][k]^2                     j > k (two buffers)
-//   inverse          X[r][t] -= L[r][k] X[k][t]  (t < k),  X[r][k] = -L[r][k]
-// X = L^{-1} is built from the elementary eliminations in the columns of A
-// that step k no longer needs; d_{k+1} is recomputed by every thread that
-// needs it from the previous step's values, so the next column's multipliers
-// are formed in the same step (look-ahead) and no second barrier is needed.
-constexpr int NTD = 512;
+// Pivot report of a diagonal block: the smallest flagged column of a shift
+// wins (0 = none yet), whatever the order in which independent subtrees run;
+// negative pivots add up.
+__device__ __forceinline__ void flag_pivots(const Common& c, int sh, int bad, int neg) {
+  if (bad) {
+    unsigned long long* q = (unsigned long long*)&c.info[sh];
+    unsigned long long old = atomicCAS(q, 0ull, (unsigned long long)bad);
+    while (old != 0ull && old > (unsigned long long)bad) {
+      const unsigned long long seen = atomicCAS(q, old, (unsigned long long)bad);
+      if (seen == old) break;
+      old = seen;
+    }
+  }
+  if (neg) atomicAdd((unsigned long long*)&c.negc[sh], (unsigned long long)neg);
+}
+
+// Dense LDL^T of the panel's wp x wp diagonal block in LDS with L_pp^{-1}.
+//
+// What bounds it is the chain of wp dependent column steps on one workgroup
+// per shift.  With a barrier and a read-modify-write of the whole trailing
+// block in LDS per column (512 threads) a step took 0.97 us: 62 us per launch
+// of 64 columns x 60 shifts.  Here the block is cut into 16-column block
+// columns:
+//   panel(b)   wave 0, one row per lane, the 16 columns in registers: per
+//              column the pivot and the multipliers of the 15 rows below are
+//              broadcast by lane reads, no LDS and no barrier;
+//   next(b)    block column b + 1 of the trailing matrix on the matrix cores
+//              (waves 0-2), so panel(b + 1) can start;
+//   rest(b)    beside panel(b + 1), waves 1-3: the other trailing blocks and
+//              the inverse: X_bm = X_bb Y_bm for the columns m < b, Y_im -= L_ib
+//              X_bm for the rows below (X = L^{-1}, Y its partial sums).  X_bb
+//              comes from lanes of panel(b) that have no row (b > 0).
+// 26 us per launch of 64 complex columns x 60 shifts (real: 25), 14 for 16
+// columns; of the 64-column time about 11 us are panels (one wave's issue of
+// lane reads and fused multiply-adds), 4 the trailing products, the rest
+// loads, stores and launch.  a[col][row] holds A, then L, in its
+// lower triangle (block columns in place) and X transposed in the strict upper
+// one, a[row][col] = X[row][col]: one array (66.5 KB of LDS), so a workgroup
+// fits on a CU beside two of the matrix kernels.  Rows and columns from wp on
+// are those of the identity.
+constexpr int NTD = 256;
+constexpr int LDD = 65;   // row stride of a[][]: 16-byte elements rotate over the banks
+
+template <bool CPLX>
+using elem_t = std::conditional_t<CPLX, dbl2, double>;
+__device__ __forceinline__ cplx to_cplx(dbl2 v) { return {v.x, v.y}; }
+__device__ __forceinline__ cplx to_cplx(double v) { return {v, 0.0}; }
+template <bool CPLX>
+__device__ __forceinline__ elem_t<CPLX> to_elem(cplx v) {
+  if constexpr (CPLX) return dbl2{v.re, v.im};
+  else return v.re;
+}
+// products that drop the imaginary part of real elements
+template <bool CPLX>
+__device__ __forceinline__ cplx mul(cplx a, cplx b) {
+  if constexpr (CPLX) return cmul(a, b);
+  else return {a.re * b.re, 0.0};
+}
+// x -= a b, one fused operation per product
+template <bool CPLX>
+__device__ __forceinline__ void sub_mul(cplx& x, cplx a, cplx b) {
+  x.re = fma(-a.re, b.re, x.re);
+  if constexpr (CPLX) {
+    x.im = fma(-a.re, b.im, x.im);
+    x.re = fma(a.im, b.im, x.re);
+    x.im = fma(-a.im, b.re, x.im);
+  }
+}
+template <bool CPLX>
+__device__ __forceinline__ cplx inv_of(cplx d) {
+  if constexpr (CPLX) return cinv(d);
+  else return {1.0 / d.re, 0.0};
+}
+__device__ __forceinline__ double lane_read(double v, int lane) {
+  const uint64_t u = __double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+  return __longlong_as_double(((uint64_t)hi << 32) | lo);
+}
+
+// Orders the wave's LDS accesses before and after it (no instruction: a wave's
+// LDS operations execute in order; it keeps the compiler from reusing values
+// that other lanes have replaced).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// One 16 x 16 x 16 block product on the calling wave: fa(m, k) and fb(k, n)
+// give the operands, out(m, n, value) takes P[m][n] (lanes run along n).
+template <bool CPLX, class FA, class FB, class FO>
+__device__ __forceinline__ void block_product(FA fa, FB fb, FO out) {
+  const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+  dbl4 re{0.0, 0.0, 0.0, 0.0}, im{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) {
+    const int k = ks * 4 + lk;
+    const cplx x = fa(li, k), y = fb(k, li);
+    re = __builtin_amdgcn_mfma_f64_16x16x4f64(x.re, y.re, re, 0, 0, 0);
+    if constexpr (CPLX) {
+      im = __builtin_amdgcn_mfma_f64_16x16x4f64(x.re, y.im, im, 0, 0, 0);
+      re = __builtin_amdgcn_mfma_f64_16x16x4f64(x.im, y.im, re, 0, 0, 1);
+      im = __builtin_amdgcn_mfma_f64_16x16x4f64(x.im, y.re, im, 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) out(lk + 4 * r, li, cplx{re[r], im[r]});
+  __builtin_amdgcn_sched_barrier(0);
+}
 
 template <bool CPLX, class Src>
-__global__ void __launch_bounds__(NTD) k_diag(Src src) {
-  // a[col][row], row > col: the working matrix, then L^{-1}; L is kept in
-  // the other strict triangle, a[row][col] = L[row][col] (one array, 68 KB
-  // of LDS, so a workgroup fits on a CU beside one of the matrix kernels)
-  __shared__ double a_re[64][LDP];
-  __shared__ double a_im[CPLX ? 64 : 1][LDP];
-  __shared__ double dd_re[2][64];    // running diagonal, double-buffered by step parity
-  __shared__ double dd_im[2][CPLX ? 64 : 1];
-  __shared__ double pv_re[64];       // pivots d_k
-  __shared__ double pv_im[CPLX ? 64 : 1];
+__global__ void __launch_bounds__(NTD, 2) k_diag(Src src) {
+  using T = elem_t<CPLX>;
+  __shared__ T a[64][LDD];
+  __shared__ T pv[64];   // pivots d_k
   Common c;
   PanelK p;
   int bx, sh;
@@ -1135,100 +1224,148 @@ __global__ void __launch_bounds__(NTD) k_diag(Src src) {
   double* Ls = shift_base<CPLX>(c, sh);
   const int wp = p.wp;
   const int t = threadIdx.x;
+  const int lane = t & 63, li = lane & 15, lk = lane >> 4;
+  const int w = wave_id();
+  const int nblk = (wp + 15) / 16;
   const int64_t dbase = p.off + (int64_t)p.p0 * p.ld + p.p0;
-  for (int idx = t; idx < wp * wp; idx += NTD) {
-    const int cc = idx / wp, r = idx % wp;
-    cplx v{0.0, 0.0};
-    if (r >= cc) v = ld_elem<CPLX>(Ls, dbase + (int64_t)cc * p.ld + r);
-    a_re[cc][r] = v.re;
-    if (CPLX) a_im[cc][r] = v.im;
-    if (r == cc) {
-      dd_re[0][r] = v.re;
-      if (CPLX) dd_im[0][r] = v.im;
+  {
+    cplx v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int cc = w + 4 * u;
+      v[u] = cplx{lane == cc ? 1.0 : 0.0, 0.0};
+      if (lane >= cc && lane < wp) v[u] = ld_elem<CPLX>(Ls, dbase + (int64_t)cc * p.ld + lane);
+    }
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int cc = w + 4 * u;
+      if (lane >= cc) a[cc][lane] = to_elem<CPLX>(v[u]);
     }
   }
-  __syncthreads();
-  auto inv = [](cplx d) -> cplx { return CPLX ? cinv(d) : cplx{1.0 / d.re, 0.0}; };
-  // column 0 of L
-  if (t > 0 && t < wp) {
-    const cplx d0{dd_re[0][0], CPLX ? dd_im[0][0] : 0.0};
-    const cplx v = cmul(cplx{a_re[0][t], CPLX ? a_im[0][t] : 0.0}, inv(d0));
-    a_re[t][0] = v.re;
-    if (CPLX) a_im[t][0] = v.im;
-  }
-  __syncthreads();
-  const double wabs = sqrt(c.shifts[2 * sh] * c.shifts[2 * sh] + c.shifts[2 * sh + 1] * c.shifts[2 * sh + 1]);
-  const double thr = c.pivtol * (c.absmax[0] + (CPLX ? wabs : fabs(c.shifts[2 * sh])) * c.absmax[1]);
-  int bad = 0;
-  int neg = 0;
-  const int r = t & 63, cg = t >> 6;   // eight threads per row
-  for (int k = 0; k < wp; ++k) {
-    const int cur = k & 1, nxt = cur ^ 1;
-    const cplx dk{dd_re[cur][k], CPLX ? dd_im[cur][k] : 0.0};
-    if (t == 0) {
-      const double ad = CPLX ? sqrt(dk.re * dk.re + dk.im * dk.im) : fabs(dk.re);
-      if (!(ad >= thr) && bad == 0) bad = p.col0 + k + 1;
-      if (!CPLX && dk.re < 0.0) ++neg;
-      pv_re[k] = dk.re;
-      if (CPLX) pv_im[k] = dk.im;
+  auto L = [&](int r, int k) { return to_cplx(a[k][r]); };
+  auto X = [&](int r, int k) { return to_cplx(a[r][k]); };
+  // X_bb as an operand: unit diagonal, zero above it
+  auto Xd = [&](int c0, int r, int k) {
+    const cplx v = X(c0 + r, c0 + k);
+    return r > k ? v : cplx{r == k ? 1.0 : 0.0, 0.0};
+  };
+  // A_ij -= L_ib D_b L_jb^T (block row i, block column j)
+  auto trailing = [&](int b, int i, int j) {
+    const int kb = 16 * b;
+    block_product<CPLX>([&](int m, int k) { return mul<CPLX>(to_cplx(pv[kb + k]), L(16 * j + m, kb + k)); },
+                        [&](int k, int n) { return L(16 * i + n, kb + k); },
+                        [&](int m, int n, cplx v) {
+                          if (i == j && n < m) return;
+                          T& e = a[16 * j + m][16 * i + n];
+                          const cplx o = to_cplx(e);
+                          e = to_elem<CPLX>(cplx{o.re - v.re, o.im - v.im});
+                        });
+  };
+  // X_00 by substitution (the panels of the later blocks have lanes to spare
+  // for theirs): column li, rows lk, lk + 4, ... per lane; every wave computes
+  // and stores the same values
+  auto inverse_of_first = [&]() {
+    cplx x[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) x[u] = cplx{lk + 4 * u == li ? 1.0 : 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < 15; ++k) {
+      const int from = (k & 3) * 16 + li;   // the lane that holds X[k][li]
+      const cplx xk{__shfl(x[k >> 2].re, from), CPLX ? __shfl(x[k >> 2].im, from) : 0.0};
+#pragma unroll
+      for (int u = k >> 2; u < 4; ++u) {
+        const int r = lk + 4 * u;
+        sub_mul<CPLX>(x[u], r > k ? L(r, k) : cplx{0.0, 0.0}, xk);
+      }
     }
-    if (r > k && r < wp) {
-      const cplx lrk{a_re[r][k], CPLX ? a_im[r][k] : 0.0};
-      const cplx dl = cmul(dk, lrk);                 // d_k L[r][k]
-      // trailing columns j in (k+1, r): off-diagonal entries of A
-      for (int j = k + 2 + cg; j < r; j += NTD / 64) {
-        const cplx f = cmul(dl, cplx{a_re[j][k], CPLX ? a_im[j][k] : 0.0});
-        a_re[j][r] -= f.re;
-        if (CPLX) a_im[j][r] -= f.im;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (li < lk + 4 * u) a[lk + 4 * u][li] = to_elem<CPLX>(x[u]);
+  };
+  // the inverse's share of step b, column blocks m = q, q + nq, ...
+  auto inverse = [&](int b, int q, int nq) {
+    const int c0 = 16 * b;
+    if (b == 0) inverse_of_first();
+    wave_sync();
+    for (int m = q; m <= b; m += nq) {
+      if (m < b)
+        block_product<CPLX>([&](int r, int k) { return Xd(c0, r, k); }, [&](int k, int n) { return X(c0 + k, 16 * m + n); },
+                            [&](int r, int n, cplx v) { a[c0 + r][16 * m + n] = to_elem<CPLX>(v); });
+      wave_sync();
+      for (int i = b + 1; i < nblk; ++i)
+        block_product<CPLX>([&](int r, int k) { return L(16 * i + r, c0 + k); },
+                            [&](int k, int n) { return m < b ? X(c0 + k, 16 * m + n) : Xd(c0, k, n); },
+                            [&](int r, int n, cplx v) {
+                              T& e = a[16 * i + r][16 * m + n];
+                              const cplx o = m < b ? to_cplx(e) : cplx{0.0, 0.0};
+                              e = to_elem<CPLX>(cplx{o.re - v.re, o.im - v.im});
+                            });
+    }
+  };
+  __syncthreads();
+  for (int b = 0; b < nblk; ++b) {
+    const int c0 = 16 * b;
+    if (w == 0) {
+      const int row = c0 + lane;
+      const bool in = row < 64;
+      // lanes without a row of A (b > 0: LE and up have none) carry the rows
+      // of an identity below it: their entries before the division are
+      // (I L_bb^{-T})[i][j] = X_bb[j][i]
+      const int LE = b > 0 ? 48 : 64;
+      cplx x[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) x[k] = in ? to_cplx(a[c0 + k][row]) : cplx{lane - LE == k ? 1.0 : 0.0, 0.0};
+      // one basic block: the next column is updated first and its pivot's
+      // reciprocal runs beside the updates of the others
+      cplx id = inv_of<CPLX>(cplx{lane_read(x[0].re, 0), CPLX ? lane_read(x[0].im, 0) : 0.0});
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const cplx aj = x[j];   // A[row][j] before the division
+        const cplx l = mul<CPLX>(aj, id);
+#pragma unroll
+        for (int k = j + 1; k < 16; ++k) {
+          sub_mul<CPLX>(x[k], l, cplx{lane_read(aj.re, k), CPLX ? lane_read(aj.im, k) : 0.0});
+          if (k == j + 1) id = inv_of<CPLX>(cplx{lane_read(x[k].re, k), CPLX ? lane_read(x[k].im, k) : 0.0});
+        }
+        const bool keep = lane == j || lane >= LE;
+        x[j].re = keep ? aj.re : l.re;
+        x[j].im = keep ? aj.im : l.im;
       }
-      if (cg == 0) {
-        // running diagonal of row r
-        const cplx f = cmul(dl, lrk);
-        dd_re[nxt][r] = dd_re[cur][r] - f.re;
-        if (CPLX) dd_im[nxt][r] = dd_im[cur][r] - f.im;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        if (in && lane > k) a[c0 + k][row] = to_elem<CPLX>(x[k]);
+        if (lane == k) pv[c0 + k] = to_elem<CPLX>(x[k]);
+        // X_bb[k][i] from the identity row i
+        if (b > 0 && lane >= LE && lane - LE < k) a[c0 + k][c0 + lane - LE] = to_elem<CPLX>(x[k]);
       }
-      if (cg == 1 && r > k + 1) {
-        // look-ahead: L[r][k+1] with d_{k+1} formed from the previous values
-        const cplx lk1{a_re[k + 1][k], CPLX ? a_im[k + 1][k] : 0.0};
-        const cplx dk1n = cmul(cmul(dk, lk1), lk1);
-        const cplx dk1{dd_re[cur][k + 1] - dk1n.re, CPLX ? dd_im[cur][k + 1] - dk1n.im : 0.0};
-        const cplx f = cmul(dl, lk1);
-        const cplx arn{a_re[k + 1][r] - f.re, CPLX ? a_im[k + 1][r] - f.im : 0.0};
-        const cplx v = cmul(arn, inv(dk1));
-        a_re[r][k + 1] = v.re;
-        if (CPLX) a_im[r][k + 1] = v.im;
-      }
-      // inverse: columns t < k of X get the elimination of column k
-      for (int tc = cg; tc < k; tc += NTD / 64) {
-        const cplx f = cmul(lrk, cplx{a_re[tc][k], CPLX ? a_im[tc][k] : 0.0});
-        a_re[tc][r] -= f.re;
-        if (CPLX) a_im[tc][r] -= f.im;
-      }
-      if (cg == 2) {
-        a_re[k][r] = -lrk.re;
-        if (CPLX) a_im[k][r] = -lrk.im;
-      }
+    } else if (b > 0) {
+      // the trailing blocks right of column b by step b - 1, then its inverse
+      int q = 0;
+      for (int j = b + 1; j < nblk; ++j)
+        for (int i = j; i < nblk; ++i)
+          if (q++ % 3 == w - 1) trailing(b - 1, i, j);
+      inverse(b - 1, w - 1, 3);
     }
     __syncthreads();
+    if (b + 1 < nblk && b + 1 + w < nblk) trailing(b, b + 1 + w, b + 1);
+    __syncthreads();
   }
-  if (t == 0) {
-    // the smallest flagged column wins (0 = none yet), whatever the order in
-    // which independent subtrees run
-    if (bad) {
-      unsigned long long* q = (unsigned long long*)&c.info[sh];
-      unsigned long long old = atomicCAS(q, 0ull, (unsigned long long)bad);
-      while (old != 0ull && old > (unsigned long long)bad) {
-        const unsigned long long seen = atomicCAS(q, old, (unsigned long long)bad);
-        if (seen == old) break;
-        old = seen;
-      }
-    }
-    if (!CPLX && neg) atomicAdd((unsigned long long*)&c.negc[sh], (unsigned long long)neg);
+  inverse(nblk - 1, w, 4);
+  if (w == 0) {
+    const double wabs = sqrt(c.shifts[2 * sh] * c.shifts[2 * sh] + c.shifts[2 * sh + 1] * c.shifts[2 * sh + 1]);
+    const double thr = c.pivtol * (c.absmax[0] + (CPLX ? wabs : fabs(c.shifts[2 * sh])) * c.absmax[1]);
+    const cplx d = to_cplx(pv[lane]);
+    const double ad = CPLX ? sqrt(d.re * d.re + d.im * d.im) : fabs(d.re);
+    const uint64_t tiny = __ballot(lane < wp && !(ad >= thr));
+    const int neg = CPLX ? 0 : __popcll(__ballot(lane < wp && d.re < 0.0));
+    if (lane == 0) flag_pivots(c, sh, tiny ? p.col0 + __ffsll((unsigned long long)tiny) : 0, neg);
   }
-  for (int idx = t; idx < wp * wp; idx += NTD) {
-    const int cc = idx / wp, rr = idx % wp;
-    if (rr > cc) st_elem<CPLX>(Ls, dbase + (int64_t)cc * p.ld + rr, cplx{a_re[cc][rr], CPLX ? a_im[cc][rr] : 0.0});
-    if (rr == cc) st_elem<CPLX>(Ls, dbase + (int64_t)cc * p.ld + rr, cplx{pv_re[cc], CPLX ? pv_im[cc] : 0.0});
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    const int cc = w + 4 * u;
+    if (lane < wp && lane >= cc)
+      st_elem<CPLX>(Ls, dbase + (int64_t)cc * p.ld + lane, to_cplx(lane > cc ? a[lane][cc] : pv[cc]));
   }
 }
 
@@ -1534,15 +1671,17 @@ __global__ void PXS_LB(true, 64) k_selinv_diag_partial(Src src) {
 
 // Z_pp = Linv^T D^{-1} Linv - sum of the partials, written over the diagonal block.
 // One workgroup per shift (the block is overwritten in place, so it is read
-// by the same workgroup that writes it) with 1024 threads: a wave holds one
-// column cc and its 64 rows, so the work per wave follows the triangle.
-constexpr int NTF = 1024;
+// by the same workgroup that writes it).  Latency bound: the 16 x 16 blocks
+// on and below the diagonal run on the matrix cores, one or two per wave, as
+// Z_RC = sum over the block rows k >= R of X_kR^T D_k^{-1} X_kC (X = Linv), and
+// the partials of a wave's blocks are summed while the block is on its way.
+// Scalar dot products over the 64 rows in LDS took 22.7 us per launch at 60
+// shifts.
+constexpr int NTF = 512;
 template <class Src>
-__global__ void __launch_bounds__(NTF) k_selinv_diag_final(Src src) {
-  __shared__ double l_re[64][LDP];   // l[col][row] = Linv[row][col]
-  __shared__ double l_im[64][LDP];
+__global__ void __launch_bounds__(NTF, 2) k_selinv_diag_final(Src src) {
+  __shared__ dbl2 x[64][LDD];   // x[col][row] = Linv[row][col]
   __shared__ cplx dinv[64];
-  constexpr int NE = 64 * 64 / NTF;
   Common c;
   PanelK p;
   int bx, by;
@@ -1552,53 +1691,69 @@ __global__ void __launch_bounds__(NTF) k_selinv_diag_final(Src src) {
   const double* W = wbase(c, sh);
   const double* part = W + 2 * (int64_t)p.nb * p.wp;
   const int wp = p.wp;
-  const int t = threadIdx.x;
+  const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+  const int w = wave_id();
   const int64_t dbase = p.off + (int64_t)p.p0 * p.ld + p.p0;
-  // element (r, cc) of the block at slot u: cc = t / 64 + 16 u, r = t % 64;
-  // every load is issued before the first LDS store
-  const int r = t & 63, c0 = t >> 6;
-  cplx v[NE];
+  cplx v[8];
 #pragma unroll
-  for (int u = 0; u < NE; ++u) {
-    const int cc = c0 + u * (NTF / 64);
+  for (int u = 0; u < 8; ++u) {
+    const int cc = w + 8 * u;
     v[u] = cplx{0.0, 0.0};
-    if (cc < wp && r < wp && r >= cc) v[u] = ld_elem<true>(Ls, dbase + (int64_t)cc * p.ld + r);
+    if (lane >= cc && lane < wp) v[u] = ld_elem<true>(Ls, dbase + (int64_t)cc * p.ld + lane);
+  }
+  // the wave's blocks (R >= C) in the order of tri_index, the longest first;
+  // the two last ones go to waves 6 and 7
+  const int nsplit = (p.nb > 0) ? p.split : 0;
+  cplx q[2][4];
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    int R, C;
+    tri_index(w + 2 * b, R, C);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) q[b][r] = cplx{0.0, 0.0};
+    if (16 * R >= wp || (b == 1 && w < 6)) continue;
+    for (int sp = 0; sp < nsplit; ++sp)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        // partial[m = cc][n = r] holds (W^T Z_Bp)[r][cc] for r >= cc
+        const cplx e = ld_elem<true>(part + 2 * (int64_t)sp * 64 * 64, (int64_t)(16 * C + lk + 4 * r) * 64 + 16 * R + li);
+        q[b][r].re += e.re;
+        q[b][r].im += e.im;
+      }
   }
 #pragma unroll
-  for (int u = 0; u < NE; ++u) {
-    const int cc = c0 + u * (NTF / 64);
-    cplx x = (r > cc) ? v[u] : cplx{0.0, 0.0};
-    if (r == cc && r < wp) {
-      x = cplx{1.0, 0.0};
-      dinv[r] = cinv(v[u]);
+  for (int u = 0; u < 8; ++u) {
+    const int cc = w + 8 * u;
+    if (lane == cc) {
+      dinv[lane] = lane < wp ? cinv(v[u]) : cplx{0.0, 0.0};
+      v[u] = cplx{lane < wp ? 1.0 : 0.0, 0.0};
     }
-    l_re[cc][r] = x.re;
-    l_im[cc][r] = x.im;
+    x[cc][lane] = dbl2{v[u].re, v[u].im};
   }
   __syncthreads();
-  const int nsplit = (p.nb > 0) ? p.split : 0;
 #pragma unroll
-  for (int u = 0; u < NE; ++u) {
-    const int cc = c0 + u * (NTF / 64);
-    if (cc >= wp || r >= wp || r < cc) continue;   // the stored (lower) triangle
-    // sum_{k >= r} Linv[k][r] dinv[k] Linv[k][cc]
-    cplx s{0.0, 0.0};
-    for (int k = r; k < wp; ++k) {
-      const cplx a{l_re[r][k], l_im[r][k]};
-      const cplx b{l_re[cc][k], l_im[cc][k]};
-      const cplx q = cmul(cmul(a, dinv[k]), b);
-      s.re += q.re;
-      s.im += q.im;
+  for (int b = 0; b < 2; ++b) {
+    int R, C;
+    tri_index(w + 2 * b, R, C);
+    if (16 * R >= wp || (b == 1 && w < 6)) continue;
+    dbl4 re{0.0, 0.0, 0.0, 0.0}, im{0.0, 0.0, 0.0, 0.0};
+    for (int kb = R; 16 * kb < wp; ++kb)
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        const int k = 16 * kb + ks * 4 + lk;
+        const cplx f = cmul(to_cplx(x[16 * C + li][k]), dinv[k]), y = to_cplx(x[16 * R + li][k]);
+        re = __builtin_amdgcn_mfma_f64_16x16x4f64(f.re, y.re, re, 0, 0, 0);
+        im = __builtin_amdgcn_mfma_f64_16x16x4f64(f.re, y.im, im, 0, 0, 0);
+        re = __builtin_amdgcn_mfma_f64_16x16x4f64(f.im, y.im, re, 0, 0, 1);
+        im = __builtin_amdgcn_mfma_f64_16x16x4f64(f.im, y.re, im, 0, 0, 0);
+      }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int cc = 16 * C + lk + 4 * r, row = 16 * R + li;
+      // the diagonal block in global memory is no longer read (Linv and D sit in LDS)
+      if (row >= cc && row < wp)
+        st_elem<true>(Ls, dbase + (int64_t)cc * p.ld + row, cplx{re[r] - q[b][r].re, im[r] - q[b][r].im});
     }
-    // partial[m = cc][n = r] holds (W^T Z_Bp)[r][cc]
-    for (int sp = 0; sp < nsplit; ++sp) {
-      const cplx q = ld_elem<true>(part + 2 * (int64_t)sp * 64 * 64, (int64_t)cc * 64 + r);
-      s.re -= q.re;
-      s.im -= q.im;
-    }
-    // each (r, cc) is computed by exactly one thread, and the diagonal block
-    // in global memory is no longer read (Linv and D sit in LDS)
-    st_elem<true>(Ls, dbase + (int64_t)cc * p.ld + r, s);
   }
 }
 
@@ -1644,13 +1799,14 @@ __global__ void __launch_bounds__(NT) k_pole_sum(const double* __restrict__ L, i
   if (threadIdx.x < 8) partial[8 * blockIdx.x + threadIdx.x] = red[threadIdx.x][0];
 }
 
+// The 8 sums over nb blocks' partials, one wave each: 64 strided sums, then
+// halves in a fixed order.  (One thread per sum over 1024 partials took 153 us.)
 __global__ void k_sum_partials(const double* partial, int nb, double* out) {
-  const int q = threadIdx.x;
-  if (q < 8) {
-    double s = 0.0;
-    for (int b = 0; b < nb; ++b) s += partial[8 * b + q];
-    out[q] = s;
-  }
+  const int q = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  double s = 0.0;
+  for (int b = lane; b < nb; b += 64) s += partial[8 * b + q];
+  for (int h = 32; h > 0; h >>= 1) s += __shfl_down(s, h);
+  if (lane == 0) out[q] = s;
 }
 
 __global__ void k_gather(const double* __restrict__ L, const int64_t* __restrict__ eoff,
@@ -1948,7 +2104,7 @@ int factor_prologue(const Symbolic& S, const double* H, const double* Sv, int ns
   const int nbm = blocks_for(S.nnz_lower, ABSMAX_BLOCKS);
   hipLaunchKernelGGL(k_absmax_partial, dim3(nbm), dim3(NT), 0, st, H, Sv, S.nnz_lower,
                      (double*)(w + WK_ABSMAX_PART));
-  hipLaunchKernelGGL(k_absmax_final, dim3(1), dim3(64), 0, st, (const double*)(w + WK_ABSMAX_PART),
+  hipLaunchKernelGGL(k_absmax_final, dim3(1), dim3(128), 0, st, (const double*)(w + WK_ABSMAX_PART),
                      nbm, (double*)(w + WK_ABSMAX));
   PXS_CHECK_LAUNCH();
   const int64_t total_d = (CPLX ? 2 : 1) * S.nnzL_store * (int64_t)nshift;   // doubles
@@ -2615,7 +2771,7 @@ int run_pole_sum_kernels(const Symbolic& S, int nshift, const void* L, void* wor
                      (const double*)(w + WK_WEIGHTS), nsets, (const int64_t*)(m + S.o_entry_off),
                      (const int32_t*)(m + S.o_entry_diag), S.nnz_lower, H, Sv, out,
                      (double*)(w + WK_POLESUM_PART), accumulate);
-  hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(64), 0, st, (const double*)(w + WK_POLESUM_PART), nb,
+  hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(512), 0, st, (const double*)(w + WK_POLESUM_PART), nb,
                      (double*)(w + WK_TRACES));
   PXS_CHECK_LAUNCH();
   return 0;
