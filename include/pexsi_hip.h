@@ -302,6 +302,22 @@ pxs_status pxs_inertia_hermitian(pxs_symbolic sym, const pxs_c64* Hval, const px
                                  int32_t nshift, const double* eps, void* Lbuf, void* work,
                                  int64_t* neg_count, int64_t* info, void* stream);
 
+/* Lower triangle of pattern(H) U pattern(S) U diagonal in CSC, for matrices
+ * given by the positions of their entries, with the source of every value.
+ * layout (per matrix): 0 coordinates (rows and cols: nnz indices each), 1
+ * compressed rows (rows: n + 1 offsets, cols: nnz indices), 2 compressed
+ * columns (cols: offsets, rows: indices).  Outputs (host): colptr (n + 1),
+ * rowind, hsrc and ssrc (room for nnz of H plus nnz of S plus n), *nnz their
+ * length.  hsrc[k] is the index of H's entry, -2 - index where the entry of H
+ * lies above the diagonal only (its mirror image), -1 where H has none; ssrc
+ * likewise.  *duplicates: 1 if a matrix names a position twice (the first is
+ * used).  PXS_EINVAL: null argument, n < 0, an index or offset out of range. */
+pxs_status pxs_lower_union(int32_t n, int32_t hlayout, int64_t hnnz, const int64_t* hrows,
+                           const int64_t* hcols, int32_t slayout, int64_t snnz,
+                           const int64_t* srows, const int64_t* scols, int64_t* colptr,
+                           int32_t* rowind, int64_t* hsrc, int64_t* ssrc, int64_t* nnz,
+                           int32_t* duplicates);
+
 /* The density matrix of Sec. II.B in one call: the pole table of eq.
  * polerho for (beta, dE, mu, P) and nsets weight sets (eq. gammaF), the
  * factorization and selected inversion of every shift, and the pole sums

@@ -54,48 +54,135 @@ def _as_coo(M):
     return int(a.shape[0]), r.astype(np.int64), c.astype(np.int64), a[r, c], a.shape
 
 
+def _entries(M):
+    """(shape, layout, rows, cols, values) of a square matrix: host index
+    arrays as pxs_lower_union takes them and the values (a numpy array, or a
+    torch tensor on M's device) they point into.  A position may occur twice;
+    _as_coo sums such entries."""
+    import scipy.sparse as sp
+    try:
+        import torch
+    except ImportError:          # pragma: no cover
+        torch = None
+    if torch is not None and isinstance(M, torch.Tensor):
+        if M.layout == torch.sparse_csr:
+            return tuple(M.shape), 1, M.crow_indices().cpu().numpy(), M.col_indices().cpu().numpy(), M.values()
+        if M.layout == torch.sparse_csc:
+            return tuple(M.shape), 2, M.row_indices().cpu().numpy(), M.ccol_indices().cpu().numpy(), M.values()
+        if M.layout == torch.sparse_coo:
+            M = M.coalesce()
+            idx = M.indices().cpu().numpy()
+            return tuple(M.shape), 0, idx[0], idx[1], M.values()
+    elif sp.issparse(M) and M.format in ("csr", "csc"):
+        if M.format == "csr":
+            return tuple(M.shape), 1, M.indptr, M.indices, M.data
+        return tuple(M.shape), 2, M.indices, M.indptr, M.data
+    n, r, c, v, shape = _as_coo(M)
+    return tuple(shape), 0, r, c, v
+
+
+def _union(H, S):
+    """(n, colptr, rowind, (hsrc, values of H), (ssrc, values of S)): the
+    pattern of lower_csc with the sources of its values (binding.lower_union)."""
+    h, s = _entries(H), _entries(S)
+    for again in (False, True):
+        if len(h[0]) != 2 or h[0][0] != h[0][1] or h[0] != s[0]:
+            raise ValueError(f"H and S must be square of one size, got {h[0]} and {s[0]}")
+        n = int(h[0][0])
+        colptr, rowind, hsrc, ssrc, dup = B.lower_union(n, h[1:4], s[1:4])
+        if not dup or again:
+            break
+        h, s = ((x[4], 0, x[1], x[2], x[3]) for x in (_as_coo(H), _as_coo(S)))   # sums the entries of one position
+    return n, colptr, rowind, (hsrc, h[4]), (ssrc, s[4])
+
+
+def _take(src, vals, dt):
+    """The values at their sources: zero where there is none (-1), conjugated
+    where the entry is mirrored (-2 - index) and complex."""
+    if not isinstance(vals, np.ndarray):
+        vals = vals.cpu().numpy()
+    out = np.zeros(src.shape[0], dtype=dt)
+    low, mir = src >= 0, src < -1
+    if low.all():
+        out[:] = vals[src]
+        return out
+    out[low] = vals[src[low]]
+    up = vals[-2 - src[mir]]
+    out[mir] = np.conj(up) if np.iscomplexobj(out) else up
+    return out
+
+
 def lower_csc(H, S):
     """(n, colptr int64, rowind int32, hval, sval): the lower triangle of
     pattern(H) U pattern(S) in CSC (rows sorted, diagonal included), values
     aligned with it (zero where a matrix has no entry).  Lower entries win;
     an entry present only above the diagonal is mirrored, conjugated when the
     values are complex."""
-    nh, rh, ch, vh, shape_h = _as_coo(H)
-    ns, rs, cs, vs, shape_s = _as_coo(S)
-    if shape_h[0] != shape_h[1] or tuple(shape_h) != tuple(shape_s):
-        raise ValueError(f"H and S must be square of one size, got {shape_h} and {shape_s}")
-    n = nh
-    cplx = np.iscomplexobj(vh) or np.iscomplexobj(vs)
-    dt = np.complex128 if cplx else np.float64
+    n, colptr, rowind, h, s = _union(H, S)
+    dt = np.complex128 if _is_complex(h[1]) or _is_complex(s[1]) else np.float64
+    return n, colptr, rowind, _take(*h, dt), _take(*s, dt)
 
-    def lower_keyed(r, c, v):
-        v = np.asarray(v, dtype=dt)
-        lo = r >= c
-        key_lo = c[lo] * n + r[lo]                       # column-major key of (r, c), r >= c
-        up = ~lo
-        key_up = r[up] * n + c[up]                       # (c, r) mirrored below
-        v_up = np.conj(v[up]) if cplx else v[up]
-        # lower entries first: np.unique keeps the first occurrence
-        keys = np.concatenate([key_lo, key_up])
-        vals = np.concatenate([v[lo], v_up])
-        k, first = np.unique(keys, return_index=True)
-        return k, vals[first]
 
-    kh, vh2 = lower_keyed(rh, ch, vh)
-    ks, vs2 = lower_keyed(rs, cs, vs)
-    keys = np.union1d(kh, ks)
-    diag = np.arange(n, dtype=np.int64) * (n + 1)
-    keys = np.union1d(keys, diag)                        # the diagonal is always stored
-    hval = np.zeros(keys.shape[0], dtype=dt)
-    sval = np.zeros(keys.shape[0], dtype=dt)
-    hval[np.searchsorted(keys, kh)] = vh2
-    sval[np.searchsorted(keys, ks)] = vs2
-    cols = keys // n
-    rows = keys % n
-    colptr = np.zeros(n + 1, dtype=np.int64)
-    np.add.at(colptr, cols + 1, 1)
-    colptr = np.cumsum(colptr)
-    return n, colptr, rows.astype(np.int32), hval, sval
+def _is_complex(v):
+    return np.iscomplexobj(v) if isinstance(v, np.ndarray) else v.is_complex()
+
+
+def _index_arrays(M):
+    """The index tensors of a torch sparse matrix on the device (coalesced
+    coordinates, compressed rows or columns) and its values; None for any
+    other input, and for values the host path refuses (with gradients, or
+    lazily conjugated)."""
+    try:
+        import torch
+    except ImportError:          # pragma: no cover
+        return None
+    if not isinstance(M, torch.Tensor) or not M.is_cuda:
+        return None
+    if M.layout == torch.sparse_csr:
+        out = M.crow_indices(), M.col_indices(), M.values()
+    elif M.layout == torch.sparse_csc:
+        out = M.ccol_indices(), M.row_indices(), M.values()
+    elif M.layout == torch.sparse_coo:
+        M = M.coalesce()
+        out = M.indices(), M.values()
+    else:
+        return None
+    v = out[-1]
+    return None if v.requires_grad or v.is_conj() or v.is_neg() or v.dim() != 1 else out
+
+
+class _ValueMap:
+    """The device-side part of lower_csc for one pair of input patterns:
+    copies of their index arrays, compared in full with those of a later
+    input, and for every stored entry the source of its value."""
+
+    def __init__(self, key, index, h, s, device):
+        import torch
+        self.key = key
+        self.index = [t.clone() for t in index]
+        self.maps = []
+        for src, _ in (h, s):
+            low = torch.from_numpy(np.where(src >= 0, src, np.where(src < -1, -2 - src, 0))).to(device)
+            none = torch.from_numpy(src == -1).to(device) if np.any(src == -1) else None
+            mir = torch.from_numpy(src < -1).to(device) if np.any(src < -1) else None
+            self.maps.append((low, none, mir))
+
+    def matches(self, key, index):
+        import torch
+        return key == self.key and all(a.shape == b.shape and torch.equal(a, b) for a, b in zip(self.index, index))
+
+    def values(self, which, vals, cplx):
+        import torch
+        low, none, mir = self.maps[which]
+        dt = torch.complex128 if cplx else torch.float64
+        if vals.numel() == 0:
+            return torch.zeros(low.shape[0], dtype=dt, device=low.device)
+        out = vals.to(dt).index_select(0, low)
+        if mir is not None and cplx:
+            out = torch.where(mir, out.conj(), out)
+        if none is not None:
+            out = out.masked_fill(none, 0.0)
+        return out
 
 
 def spectrum_bound(colptr, rowind, hval, sval):
@@ -160,9 +247,35 @@ class Solver:
             import torch
             e = {"analysis": a, "buffers": {},
                  "colptr": torch.from_numpy(colptr).to(self.device),
-                 "rowind": torch.from_numpy(rowind.astype(np.int64)).to(self.device)}
+                 "rowind": torch.from_numpy(rowind.astype(np.int64)).to(self.device),
+                 "colptr_host": colptr, "rowind_host": rowind, "maps": []}
             self._cache[key] = e
         return e
+
+    def _pencil(self, H, S, blocks, coords):
+        """(cache entry, H values, S values on the device).  Sparse tensors on
+        the device whose index arrays equal those of an earlier call (compared
+        in full there) have their values gathered on the device; everything
+        else goes through the host."""
+        import torch
+        hi, si = _index_arrays(H), _index_arrays(S)
+        index = key = None
+        if hi is not None and si is not None and H.shape == S.shape and H.device == S.device:
+            index = [*hi[:-1], *si[:-1]]
+            key = (H.layout, S.layout, tuple(H.shape), H.device, *(t.dtype for t in index))
+            cplx = hi[-1].is_complex() or si[-1].is_complex()
+            for e in list(self._cache.values()):
+                for m in e["maps"]:
+                    if m.matches(key, index):
+                        return e, m.values(0, hi[-1], cplx), m.values(1, si[-1], cplx)
+        n, colptr, rowind, h, s = _union(H, S)
+        dt = np.complex128 if _is_complex(h[1]) or _is_complex(s[1]) else np.float64
+        e = self._entry(n, colptr, rowind, blocks, coords)
+        Hd, Sd = (torch.from_numpy(_take(*x, dt)).to(self.device) for x in (h, s))
+        # (entries summed into one position have other values than the input's)
+        if index is not None and Hd.device == H.device and h[1].shape == hi[-1].shape and s[1].shape == si[-1].shape:
+            e["maps"] = [*e["maps"][-1:], _ValueMap(key, index, h, s, Hd.device)]   # the last two input patterns
+        return e, Hd, Sd
 
     def _buffers(self, e, kind, P):
         import torch
@@ -229,14 +342,12 @@ class Solver:
             if not ok:
                 raise ValueError(f"S is not positive definite: {bad} non-positive pivots, tiny pivot at {info}")
         nsets = 1 + max(SETS.index(o) for o in outputs)
-        n, colptr, rowind, hval, sval = lower_csc(H, S)
-        herm = np.iscomplexobj(hval)
-        if dE is None:
-            dE = pencil_dE(colptr, rowind, hval, sval, mu)
-        e = self._entry(n, colptr, rowind, blocks, coords)
+        e, Hd, Sd = self._pencil(H, S, blocks, coords)
         a = e["analysis"]
-        Hd = torch.from_numpy(hval).to(self.device)
-        Sd = torch.from_numpy(sval).to(self.device)
+        n = a.n
+        herm = Hd.is_complex()
+        if dE is None:
+            dE = pencil_dE(e["colptr_host"], e["rowind_host"], Hd.cpu().numpy(), Sd.cpu().numpy(), mu)
         if herm:
             L, W = self._buffers(e, "herm", P)
             sh, wt = B.poles(beta, dE, mu, P, nsets)

@@ -66,6 +66,8 @@ def load():
         "pxs_poles": (C.c_int, [C.c_double, C.c_double, C.c_double, C.c_int32, C.c_int32, _P, _P]),
         "pxs_analyze": (C.c_int, [C.c_int32, _P, _P, C.c_int32, _P, _P, _P, _P]),
         "pxs_symbolic_info": (C.c_int, [_P, _P]),
+        "pxs_lower_union": (C.c_int, [C.c_int32, C.c_int32, C.c_int64, _P, _P, C.c_int32, C.c_int64, _P, _P,
+                                      _P, _P, _P, _P, _P, _P]),
         "pxs_workspace_size": (C.c_int, [_P, C.c_int32, C.c_int32, _P]),
         "pxs_symbolic_export": (C.c_int, [_P, _P, _P, _P, _P, _P]),
         "pxs_symbolic_bind": (C.c_int, [_P, _P, _P]),
@@ -172,6 +174,32 @@ def poles(beta: float, dE: float, mu: float, P: int, nsets: int = 2):
     wt = np.zeros(nsets * P, dtype=np.complex128)
     _check("pxs_poles", lib.pxs_poles(beta, dE, mu, P, nsets, _ptr(sh), _ptr(wt)))
     return sh, wt.reshape(nsets, P)
+
+
+def lower_union(n, h, s):
+    """Lower triangle of the union of two patterns.  h, s: (layout, rows,
+    cols) as for pxs_lower_union, int64 host arrays.  Returns (colptr, rowind,
+    hsrc, ssrc, duplicates)."""
+    lib = load()
+    args, cap = [], n
+    for layout, rows, cols in (h, s):
+        rows = np.ascontiguousarray(rows, dtype=np.int64)
+        cols = np.ascontiguousarray(cols, dtype=np.int64)
+        nnz = rows.shape[0] if layout == 2 else cols.shape[0]
+        if (layout == 0 and rows.shape != cols.shape) or (layout == 1 and rows.shape[0] != n + 1) \
+                or (layout == 2 and cols.shape[0] != n + 1):
+            raise ValueError("index arrays of the wrong length")
+        args.append((layout, nnz, rows, cols))
+        cap += nnz
+    colptr = np.empty(n + 1, dtype=np.int64)
+    rowind = np.empty(cap, dtype=np.int32)
+    src = np.empty((2, cap), dtype=np.int64)
+    nnz, dup = C.c_int64(), C.c_int32()
+    flat = [x for layout, m, rows, cols in args for x in (layout, m, _ptr(rows), _ptr(cols))]
+    _check("pxs_lower_union", lib.pxs_lower_union(n, *flat, _ptr(colptr), _ptr(rowind), _ptr(src[0]), _ptr(src[1]),
+                                                  C.byref(nnz), C.byref(dup)))
+    k = nnz.value
+    return colptr, rowind[:k].copy(), src[0, :k].copy(), src[1, :k].copy(), bool(dup.value)
 
 
 class Analysis:

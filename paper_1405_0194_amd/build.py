@@ -14,7 +14,7 @@ CSRC = os.path.join(HERE, "csrc")
 ROOT = os.path.dirname(HERE)
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libpexsi_hip.so")
-SOURCES = ["poles.cpp", "symbolic.cpp", "capi.cpp", "numeric.hip"]
+SOURCES = ["poles.cpp", "symbolic.cpp", "marshal.cpp", "capi.cpp", "numeric.hip"]
 ARCH = "gfx950"
 
 

@@ -435,6 +435,25 @@ pxs_status pxs_inertia_hermitian(pxs_symbolic sym, const pxs_c64* Hval, const px
   return tiny ? PXS_TINY_PIVOT : PXS_OK;
 }
 
+pxs_status pxs_lower_union(int32_t n, int32_t hlayout, int64_t hnnz, const int64_t* hrows, const int64_t* hcols,
+                           int32_t slayout, int64_t snnz, const int64_t* srows, const int64_t* scols,
+                           int64_t* colptr, int32_t* rowind, int64_t* hsrc, int64_t* ssrc, int64_t* nnz,
+                           int32_t* duplicates) {
+  if (n < 0 || hlayout < 0 || hlayout > 2 || slayout < 0 || slayout > 2 || hnnz < 0 || snnz < 0) return PXS_EINVAL;
+  if (!hrows || !hcols || !srows || !scols || !colptr || !rowind || !hsrc || !ssrc || !nnz || !duplicates)
+    return PXS_EINVAL;
+  try {
+    if (pxs::lower_union(n, pxs::EntryList{hlayout, hnnz, hrows, hcols}, pxs::EntryList{slayout, snnz, srows, scols},
+                         colptr, rowind, hsrc, ssrc, nnz, duplicates) != 0) {
+      g_last_error = "pxs_lower_union: an index or offset is out of range";
+      return PXS_EINVAL;
+    }
+  } catch (const std::bad_alloc&) {
+    return PXS_ENOMEM;
+  }
+  return PXS_OK;
+}
+
 pxs_status pxs_density_matrix(pxs_symbolic sym, const double* Hval, const double* Sval, double beta,
                               double dE, double mu, int32_t P, int32_t nsets, void* Lbuf, void* work,
                               double* out, double* traces, int64_t* info, pxs_c64* shifts,

@@ -11,6 +11,23 @@ namespace pxs {
 int pole_table(double beta, double dE, double mu, int P, int nsets, double* shifts_ri,
                double* weights_ri);
 
+// The entries of a sparse n x n matrix by position (marshal.cpp).  layout 0:
+// rows and cols hold nnz indices; 1 (2): rows (cols) holds the n + 1 offsets of
+// compressed rows (columns), the other nnz indices.
+struct EntryList {
+  int32_t layout;
+  int64_t nnz;
+  const int64_t* rows;
+  const int64_t* cols;
+};
+// Lower triangle of the union pattern in CSC (colptr n + 1; rowind, hsrc, ssrc
+// at most nnz(H) + nnz(S) + n) with the source of each value: the entry's index,
+// -2 - index where the entry above the diagonal is mirrored, -1 for none.
+// *duplicates is 1 if a matrix names a position twice.  -1: an index is out of
+// range.
+int lower_union(int32_t n, const EntryList& h, const EntryList& s, int64_t* colptr, int32_t* rowind, int64_t* hsrc,
+                int64_t* ssrc, int64_t* nnz, int32_t* duplicates);
+
 struct Panel {
   int32_t J;   // supernode
   int32_t p0;  // first column, as a position in the supernode's row list
