@@ -107,19 +107,23 @@ __device__ __forceinline__ cplx ld_or_zero(const double* base, int64_t e, bool o
 // im += ar bi + ai br.  The last argument of the f64 MFMA builtin holds the
 // operand negation bits (bit 0 negates A), so -ai costs no instruction.
 // --------------------------------------------------------------------------
-template <int NTILE>
+// TALL (complex products of panels of at most 48 columns): 64 and 32 columns
+// with the waves along n first, so that a panel's dead 16-row blocks are left
+// out of every wave alike; the row blocks alternate between the two wave rows
+// of a 32-column tile.
+template <int NTILE, bool TALL = false>
 struct Geo {
-  static constexpr int WN = NTILE < 32 ? 1 : NTILE / 32;   // waves along n
+  static constexpr int WN = TALL ? (NTILE + 15) / 16 : NTILE < 32 ? 1 : NTILE / 32;   // waves along n
   static constexpr int WM = 4 / WN;            // waves along m
-  static constexpr int BM = 64 / WM / 16;      // 16-blocks per wave along m
-  static constexpr int BN = NTILE < 32 ? 1 : 2;            // 16-blocks per wave along n
+  static constexpr int BM = TALL ? (NTILE == 64 ? 3 : NTILE == 32 ? 2 : 1) : 64 / WM / 16;   // 16-blocks per wave along m
+  static constexpr int BN = TALL || NTILE < 32 ? 1 : 2;    // 16-blocks per wave along n
   static constexpr int XA = 64 * KC / NT;      // A transfers per thread and chunk
   static constexpr int XB = NTILE * KC / NT;   // B transfers per thread and chunk
 };
 
-template <bool CPLX, int NTILE>
+template <bool CPLX, int NTILE, bool TALL = false>
 struct Acc {
-  static constexpr int BM = Geo<NTILE>::BM, BN = Geo<NTILE>::BN;
+  static constexpr int BM = Geo<NTILE, TALL>::BM, BN = Geo<NTILE, TALL>::BN;
   dbl4 re[BM][BN];
   dbl4 im[CPLX ? BM : 1][CPLX ? BN : 1];
   __device__ void zero() {
@@ -153,10 +157,12 @@ struct NoScale {};
 // first wave row (column) taking blocks {0, 3} and the second {1, 2}, so that
 // both skip equally many blocks of a triangle (products with a triangular
 // operand or a symmetric result).
-template <int NTILE, int SWZ>
+template <int NTILE, int SWZ, bool TALL = false>
 __device__ __forceinline__ int block_row(int w, int a) {
-  using G = Geo<NTILE>;
-  if constexpr ((SWZ & 1) != 0) {
+  using G = Geo<NTILE, TALL>;
+  if constexpr (TALL) {
+    return 16 * (a * G::WM + w / G::WN);
+  } else if constexpr ((SWZ & 1) != 0) {
     static_assert(G::BM == 2 && G::WM == 2, "block swizzle needs 2 x 2 waves of 2 blocks");
     const int wr = w / G::WN;
     return 16 * (a == 0 ? wr : 3 - wr);
@@ -164,15 +170,15 @@ __device__ __forceinline__ int block_row(int w, int a) {
     return (w / G::WN) * (G::BM * 16) + a * 16;
   }
 }
-template <int NTILE, int SWZ>
+template <int NTILE, int SWZ, bool TALL = false>
 __device__ __forceinline__ int block_col(int w, int b) {
-  using G = Geo<NTILE>;
+  using G = Geo<NTILE, TALL>;
   if constexpr ((SWZ & 2) != 0) {
     static_assert(G::BN == 2 && G::WN == 2, "block swizzle needs 2 x 2 waves of 2 blocks");
     const int wc = w % G::WN;
     return 16 * (b == 0 ? wc : 3 - wc);
   } else {
-    return (w % G::WN) * 32 + b * 16;
+    return (w % G::WN) * (G::BN * 16) + b * 16;
   }
 }
 
@@ -241,9 +247,9 @@ __device__ __forceinline__ void mfma_chunk(Acc<CPLX, NTILE>& acc, const Stage<CP
 }
 
 // Visits every accumulator element as (m, n, value).
-template <bool CPLX, int NTILE, int SWZ = 0, class F>
-__device__ __forceinline__ void acc_foreach(const Acc<CPLX, NTILE>& acc, F f) {
-  using G = Geo<NTILE>;
+template <bool CPLX, int NTILE, int SWZ = 0, bool TALL = false, class F>
+__device__ __forceinline__ void acc_foreach(const Acc<CPLX, NTILE, TALL>& acc, F f) {
+  using G = Geo<NTILE, TALL>;
   const int lane = threadIdx.x & 63;
   const int w = threadIdx.x >> 6;
 #pragma unroll
@@ -252,8 +258,8 @@ __device__ __forceinline__ void acc_foreach(const Acc<CPLX, NTILE>& acc, F f) {
     for (int b = 0; b < G::BN; ++b)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int m = block_row<NTILE, SWZ>(w, a) + (lane >> 4) + 4 * r;
-        const int n = block_col<NTILE, SWZ>(w, b) + (lane & 15);
+        const int m = block_row<NTILE, SWZ, TALL>(w, a) + (lane >> 4) + 4 * r;
+        const int n = block_col<NTILE, SWZ, TALL>(w, b) + (lane & 15);
         cplx v{acc.re[a][b][r], CPLX ? acc.im[a][b][r] : 0.0};
         f(m, n, v);
       }
@@ -261,18 +267,17 @@ __device__ __forceinline__ void acc_foreach(const Acc<CPLX, NTILE>& acc, F f) {
 
 // The idx-th accumulator element of the calling thread (the order in which
 // acc_foreach visits them) and its tile coordinates.
-template <int NTILE>
-constexpr int acc_elems() { return Geo<NTILE>::BM * Geo<NTILE>::BN * 4; }
+template <int NTILE, bool TALL = false>
+constexpr int acc_elems() { return Geo<NTILE, TALL>::BM * Geo<NTILE, TALL>::BN * 4; }
 
-template <bool CPLX, int NTILE>
-__device__ __forceinline__ void acc_at(const Acc<CPLX, NTILE>& acc, int idx, int& m, int& n, cplx& v) {
-  using G = Geo<NTILE>;
+template <bool CPLX, int NTILE, bool TALL>
+__device__ __forceinline__ void acc_at(const Acc<CPLX, NTILE, TALL>& acc, int idx, int& m, int& n, cplx& v) {
+  using G = Geo<NTILE, TALL>;
   const int lane = threadIdx.x & 63;
   const int w = threadIdx.x >> 6;
-  const int wm = (w / G::WN) * (G::BM * 16), wn = (w % G::WN) * 32;
   const int r = idx & 3, b = (idx >> 2) % G::BN, a = (idx >> 2) / G::BN;
-  m = wm + a * 16 + (lane >> 4) + 4 * r;
-  n = wn + b * 16 + (lane & 15);
+  m = block_row<NTILE, 0, TALL>(w, a) + (lane >> 4) + 4 * r;
+  n = block_col<NTILE, 0, TALL>(w, b) + (lane & 15);
   v = cplx{acc.re[a][b][r], CPLX ? acc.im[a][b][r] : 0.0};
 }
 
@@ -283,12 +288,12 @@ __device__ __forceinline__ void acc_at(const Acc<CPLX, NTILE>& acc, int idx, int
 // target), then all old values, then all stores.  Every target
 // belongs to one element of one workgroup, so reordering the stores changes
 // no result.
-template <bool CPLX, int NTILE, class AF>
-__device__ __forceinline__ void acc_sub_into(const Acc<CPLX, NTILE>& acc, double* target, AF addr) {
-  constexpr int NE = acc_elems<NTILE>();
+template <bool CPLX, int NTILE, bool TALL, class AF>
+__device__ __forceinline__ void acc_sub_into(const Acc<CPLX, NTILE, TALL>& acc, double* target, AF addr) {
+  constexpr int NE = acc_elems<NTILE, TALL>();
   // complex: at most 8 elements at a time, so positions and old values fit
   // beside the accumulators in the 128 registers of four waves per SIMD
-  constexpr int NH = CPLX && NE > 8 ? 8 : NE;
+  constexpr int NH = CPLX && NE > 8 ? (NE % 8 ? 4 : 8) : NE;
 #pragma unroll
   for (int h = 0; h < NE; h += NH) {
     int64_t e[NH];
@@ -297,7 +302,7 @@ __device__ __forceinline__ void acc_sub_into(const Acc<CPLX, NTILE>& acc, double
     for (int i = 0; i < NH; ++i) {
       int m, n;
       cplx v;
-      acc_at<CPLX, NTILE>(acc, h + i, m, n, v);
+      acc_at(acc, h + i, m, n, v);
       ok[i] = addr(m, n, e[i]);
     }
     // addr returns an in-bounds position also for skipped elements, so the
@@ -309,7 +314,7 @@ __device__ __forceinline__ void acc_sub_into(const Acc<CPLX, NTILE>& acc, double
     for (int i = 0; i < NH; ++i) {
       int m, n;
       cplx v;
-      acc_at<CPLX, NTILE>(acc, h + i, m, n, v);
+      acc_at(acc, h + i, m, n, v);
       if (ok[i]) st_elem<CPLX>(target, e[i], cplx{o[i].re - v.re, o[i].im - v.im});
     }
   }
@@ -428,52 +433,33 @@ struct Stage2 {
 // column k of A on its way to the matrix cores (one load per k and chunk
 // instead of one per element); it must accept any k of the last chunk.
 // Which block pairs (a, b) of the wave take part in a chunk, as a mask of
-// bits 2a + b (evaluated per chunk, uniform over the wave): all (AllLive);
-// for a triangular A operand on a 64-row tile (TriLive, swizzled block rows),
+// bits 2a + b (evaluated per chunk, uniform over the wave): all (AllLive), or
+// for a triangular A operand on a 64-row tile (TriLive, swizzled block rows)
 // both pairs of each row block whose rows meet the chunk's k range in the
-// nonzero triangle; for a symmetric 64 x 64 result of which one triangle is
-// used (UpperLive), the pairs on or above the block diagonal.
+// nonzero triangle.
 struct AllLive {
   static constexpr bool kAll = true;
   static constexpr int kSwz = 0;
   __device__ int operator()(int) const { return 15; }
 };
-template <bool LOWER, int NTILE = 64>   // LOWER: A[m][k] = 0 for k > m; else A[m][k] = 0 for k < m
+template <bool LOWER>   // LOWER: A[m][k] = 0 for k > m; else A[m][k] = 0 for k < m
 struct TriLive {
   static constexpr bool kAll = false;
-  static constexpr int kSwz = NTILE == 64 ? 1 : 0;
+  static constexpr int kSwz = 1;
   __device__ int operator()(int k0) const {
-    // a chunk lies in one 16-column block
-    const int wr = (threadIdx.x >> 6) / Geo<NTILE>::WN;
-    const int c = k0 / 16;
+    static_assert(KC == 16, "a chunk spans one 16-row block");
+    const int wr = (threadIdx.x >> 6) / Geo<64>::WN;
+    const int c = k0 / KC;
     const int mb0 = wr, mb1 = 3 - wr;
-    if constexpr (NTILE != 64)   // one block row per wave
-      return __builtin_amdgcn_readfirstlane((LOWER ? c <= wr : c >= wr) ? 15 : 0);
     const bool l0 = LOWER ? c <= mb0 : c >= mb0;
     const bool l1 = LOWER ? c <= mb1 : c >= mb1;
     return __builtin_amdgcn_readfirstlane((l0 ? 3 : 0) | (l1 ? 12 : 0));   // both column blocks of a live row block
   }
 };
-// A symmetric 64 x 64 result of which only the entries n >= m are needed:
-// the block pairs with column block >= row block (rows and columns swizzled,
-// so no wave has more than 3 of its 4 pairs).
-struct UpperLive {
-  static constexpr bool kAll = false;
-  static constexpr int kSwz = 3;
-  __device__ int operator()(int) const {
-    const int w = threadIdx.x >> 6;
-    const int wr = w / Geo<64>::WN, wc = w % Geo<64>::WN;
-    int mask = 0;
-    for (int a = 0; a < 2; ++a)
-      for (int b = 0; b < 2; ++b)
-        if ((b == 0 ? wc : 3 - wc) >= (a == 0 ? wr : 3 - wr)) mask |= 1 << (2 * a + b);
-    return __builtin_amdgcn_readfirstlane(mask);
-  }
-};
 
-// The masks these functors return (15, 12, 3, 11, 10; 0 when no pair is
-// live) each have an instance below; a functor returning another mask would
-// skip its chunk, so a new one adds its masks here.
+// The masks these functors return (15, 12, 3; 0 when no pair is live) each
+// have an instance below; a functor returning another mask would skip its
+// chunk, so a new one adds its masks here.
 template <bool CPLX, int NTILE, bool SC, class LV>
 __device__ __forceinline__ void run_chunk(Acc<CPLX, NTILE>& acc, const Stage<CPLX, NTILE>& st, LV lv, int k0) {
   if constexpr (LV::kAll) {
@@ -483,8 +469,6 @@ __device__ __forceinline__ void run_chunk(Acc<CPLX, NTILE>& acc, const Stage<CPL
     if (m == 15) mfma_chunk<CPLX, NTILE, SC, 15, LV::kSwz>(acc, st);
     else if (m == 12) mfma_chunk<CPLX, NTILE, SC, 12, LV::kSwz>(acc, st);
     else if (m == 3) mfma_chunk<CPLX, NTILE, SC, 3, LV::kSwz>(acc, st);
-    else if (m == 11) mfma_chunk<CPLX, NTILE, SC, 11, LV::kSwz>(acc, st);
-    else if (m == 10) mfma_chunk<CPLX, NTILE, SC, 10, LV::kSwz>(acc, st);
   }
 }
 
@@ -555,6 +539,29 @@ struct RowsFast {
 };
 struct KFast {
   __device__ bool operator()(int) const { return true; }
+};
+
+// Which 16 x 16 blocks of a complex tile take part in the 16 columns c of the
+// product: all, those of a triangular A operand that meet the columns in its
+// nonzero triangle (LOWER: A[m][k] = 0 for k > m, else for k < m), or those on
+// or above the diagonal of a symmetric result (cb: block column of the whole
+// result).
+struct AllBlocks {
+  static constexpr bool kAll = true;
+  static constexpr int kSwz = 0;
+  __device__ bool operator()(int, int, int) const { return true; }
+};
+template <bool LOWER>
+struct TriBlocks {
+  static constexpr bool kAll = false;
+  static constexpr int kSwz = 1;   // on 64 x 64 tiles the wave rows take blocks {0, 3} and {1, 2}
+  __device__ bool operator()(int rb, int, int c) const { return LOWER ? c <= rb : c >= rb; }
+};
+struct UpperBlocks {
+  static constexpr bool kAll = false;
+  static constexpr int kSwz = 3;   // rows and columns
+  int cb0;                         // the tile's first block column
+  __device__ bool operator()(int rb, int cb, int) const { return cb0 + cb >= rb; }
 };
 
 // --------------------------------------------------------------------------
@@ -678,10 +685,11 @@ struct RowsOp : LoadCount<ROWS> {
   using LoadCount<ROWS>::J;
   const double* base;
   int K, w;
+  int rows16;   // rows rounded up to blocks of 16: the slots behind them are never read
   unsigned v[J];
   int kk[J];
   __device__ __forceinline__ RowsOp(const double* b, int ld, int nrows, int K_)
-      : base(uniform(b)), K(K_), w(wave_id()) {
+      : base(uniform(b)), K(K_), w(wave_id()), rows16((nrows + 15) & ~15) {
 #pragma unroll
     for (int j = 0; j < J; ++j) {
       int m;
@@ -692,7 +700,7 @@ struct RowsOp : LoadCount<ROWS> {
   __device__ __forceinline__ void issue(int k0, dbl2* lds) const {
 #pragma unroll
     for (int j = 0; j < J; ++j) {
-      if (N < 4 && w >= N) continue;
+      if ((N < 4 && w >= N) || (w + 4 * j) * 8 >= rows16) continue;
       load_lds(base + 2 * (int64_t)k0, k0 + kk[j] < K ? v[j] : LANE_OUT, lds + (w + 4 * j) * 64);
     }
   }
@@ -814,13 +822,13 @@ struct NoDiag {
   __device__ __forceinline__ void issue(int, dbl2*) const {}
 };
 
-// One stage on the matrix cores.  MASKED: only the block pairs (a, b) with
-// bit 2a + b of mask set (uniform over the wave; a branch per pair, one copy of
+// One stage on the matrix cores.  MASKED: only the block pairs (a, b) with bit
+// BN a + b of mask set (uniform over the wave; a branch per pair, one copy of
 // the code: a copy per mask spilled registers at four waves per SIMD).
-template <int NTILE, bool SCALE, bool MASKED, int SWZ>
-__device__ __forceinline__ void mfma_stage(Acc<true, NTILE>& acc, const dbl2* as, bool afast, const dbl2* bs, bool bfast,
-                                           const dbl2* ds, int mask) {
-  using G = Geo<NTILE>;
+template <int NTILE, bool TALL, bool SCALE, bool MASKED, int SWZ>
+__device__ __forceinline__ void mfma_stage(Acc<true, NTILE, TALL>& acc, const dbl2* as, bool afast, const dbl2* bs,
+                                           bool bfast, const dbl2* ds, int mask) {
+  using G = Geo<NTILE, TALL>;
   const int lane = threadIdx.x & 63;
   const int w = threadIdx.x >> 6;
   const int li = lane & 15, lk = lane >> 4;
@@ -830,12 +838,12 @@ __device__ __forceinline__ void mfma_stage(Acc<true, NTILE>& acc, const dbl2* as
     dbl2 av[G::BM], bv[G::BN];
 #pragma unroll
     for (int t = 0; t < G::BM; ++t) {
-      const int m = block_row<NTILE, SWZ>(w, t) + li;
+      const int m = block_row<NTILE, SWZ, TALL>(w, t) + li;
       av[t] = as[afast ? m * 8 + (k ^ (li >> 1)) : k * 64 + m];
     }
 #pragma unroll
     for (int t = 0; t < G::BN; ++t) {
-      const int n = block_col<NTILE, SWZ>(w, t) + li;
+      const int n = block_col<NTILE, SWZ, TALL>(w, t) + li;
       bv[t] = bs[bfast ? n * 8 + (k ^ (li >> 1)) : k * NTILE + n];
     }
     if constexpr (SCALE) {
@@ -859,7 +867,7 @@ __device__ __forceinline__ void mfma_stage(Acc<true, NTILE>& acc, const dbl2* as
       for (int a = 0; a < G::BM; ++a)
 #pragma unroll
         for (int b = 0; b < G::BN; ++b)
-          if ((mask >> (2 * a + b)) & 1) {
+          if ((mask >> (G::BN * a + b)) & 1) {
             first(a, b);
             second(a, b);
           }
@@ -883,34 +891,73 @@ __device__ __forceinline__ void stage_barrier() { asm volatile("s_waitcnt vmcnt(
 // P += A[:, k] B[k, :] over k in [0, K): two stages, one barrier per stage.
 // A stage's loads start right after the barrier that ends the reads of its
 // buffer and have the other stage's MFMAs (and three other workgroups') to
-// land.
-template <int NTILE, class LV = AllLive, class OA, class OB, class OD>
-__device__ __forceinline__ void gemm_lds(Acc<true, NTILE>& acc, CStage<NTILE, !std::is_same<OD, NoDiag>::value>& s, int K,
-                                         const OA& oa, const OB& ob, const OD& od, LV lv = LV()) {
+// land.  The result has mrows rows (64, or fewer: the blocks behind them are
+// not multiplied).
+template <class LV, int NTILE, bool TALL, class OA, class OB, class OD>
+__device__ __forceinline__ void gemm_lds(Acc<true, NTILE, TALL>& acc,
+                                         CStage<NTILE, !std::is_same<OD, NoDiag>::value>& s, int mrows, int K, const OA& oa,
+                                         const OB& ob, const OD& od, LV lv) {
   constexpr bool SC = !std::is_same<OD, NoDiag>::value;
+  using G = Geo<NTILE, TALL>;
+  constexpr int SWZ = NTILE == 64 && !TALL ? LV::kSwz : 0;
+  constexpr bool MASKED = TALL || NTILE == 16 || !LV::kAll;
   if (K <= 0) return;
   const int nc = (K + KD - 1) / KD;
+  const int w = wave_id();
   auto issue = [&](int c, int q) {
     oa.issue(c * KD, s.a[q]);
     ob.issue(c * KD, s.b[q]);
     od.issue(c * KD, s.d[SC ? q : 0]);
   };
+  auto blocks = [&](int c) {   // the wave's live blocks in the 16 columns c
+    int m = 0;
+#pragma unroll
+    for (int a = 0; a < G::BM; ++a)
+#pragma unroll
+      for (int b = 0; b < G::BN; ++b) {
+        const int row = block_row<NTILE, SWZ, TALL>(w, a);
+        if (row < mrows && lv(row / 16, block_col<NTILE, SWZ, TALL>(w, b) / 16, c)) m |= 1 << (G::BN * a + b);
+      }
+    return m;
+  };
   issue(0, 0);
   int q = 0;
+  int mask = LV::kAll && MASKED ? blocks(0) : 0;
   for (int c = 0; c < nc; ++c) {
     stage_barrier();
     if (c + 1 < nc) issue(c + 1, q ^ 1);
     const int k0 = c * KD;
-    const bool fa = oa.fast(k0), fb = ob.fast(k0);
-    if constexpr (LV::kAll) {
-      mfma_stage<NTILE, SC, false, 0>(acc, s.a[q], fa, s.b[q], fb, s.d[SC ? q : 0], 15);
-    } else {
-      const int m = lv(k0);
-      if (m) mfma_stage<NTILE, SC, NTILE == 64, LV::kSwz>(acc, s.a[q], fa, s.b[q], fb, s.d[SC ? q : 0], m);
-    }
+    if (!LV::kAll) mask = blocks(k0 / 16);
+    if (!MASKED || mask)
+      mfma_stage<NTILE, TALL, SC, MASKED, SWZ>(acc, s.a[q], oa.fast(k0), s.b[q], ob.fast(k0), s.d[SC ? q : 0], mask);
     q ^= 1;
   }
 }
+
+// f(acc) with the accumulators of a tile of mrows rows: the square wave layout,
+// or the tall one where at most three of the four 16-row blocks are live.  (16
+// columns have one block per wave: one layout.)
+template <int NTILE, class F>
+__device__ __forceinline__ void with_layout(int mrows, F f) {
+  if (NTILE == 16 || mrows > 48) {
+    Acc<true, NTILE, false> acc;
+    acc.zero();
+    f(acc);
+  } else if constexpr (NTILE != 16) {
+    Acc<true, NTILE, true> acc;
+    acc.zero();
+    f(acc);
+  }
+}
+// the block swizzle gemm_lds uses for an accumulator type
+template <class A>
+struct AccLayout;
+template <bool CPLX, int NTILE, bool TALL>
+struct AccLayout<Acc<CPLX, NTILE, TALL>> {
+  static constexpr bool kSquare64 = NTILE == 64 && !TALL;
+};
+template <class A, class LV>
+constexpr int swz_of = AccLayout<std::decay_t<A>>::kSquare64 ? LV::kSwz : 0;
 
 // --------------------------------------------------------------------------
 // small kernels
@@ -1391,17 +1438,25 @@ __global__ void PXS_LB(CPLX, TN) k_trsm(Src src) {
     const cplx d = ld_elem<CPLX>(Ls, dbase + (int64_t)threadIdx.x * p.ld + threadIdx.x);
     dinv[threadIdx.x] = CPLX ? cinv(d) : cplx{1.0 / d.re, 0.0};
   }
-  Acc<CPLX, TN> acc;
-  acc.zero();
+  // P[m][n] / d_m into row n of the panel
+  auto store = [&](int m, int n, cplx v) {
+    const int ig = i0 + n;
+    if (m < p.wp && ig < p.nb) st_elem<CPLX>(Ls, rbase + (int64_t)m * p.ld + ig, cmul(v, dinv[m]));
+  };
   // L^{-1} is lower triangular: the all-zero blocks of a chunk are not
-  // multiplied (for the real 128-row tiles they are)
-  using LV = std::conditional_t<CPLX || TN == 64, TriLive<true, CPLX ? TN : 64>, AllLive>;
+  // multiplied (on the real 128-row tiles they are)
   if constexpr (CPLX) {
     __shared__ CStage<TN, false> s;
-    gemm_lds<TN, LV>(acc, s, p.wp, TriOp<false>(Ls + 2 * dbase, p.ld, p.wp),
-                     ColsOp<TN>(Ls + 2 * (rbase + i0), p.ld, p.nb - i0, p.wp), NoDiag());
+    with_layout<TN>(p.wp, [&](auto& acc) {
+      gemm_lds(acc, s, p.wp, p.wp, TriOp<false>(Ls + 2 * dbase, p.ld, p.wp),
+               ColsOp<TN>(Ls + 2 * (rbase + i0), p.ld, p.nb - i0, p.wp), NoDiag(), TriBlocks<true>());
+      acc_foreach<true, TN, swz_of<decltype(acc), TriBlocks<true>>>(acc, store);
+    });
   } else {
     __shared__ Stage2<false, TN> s;
+    using LV = std::conditional_t<TN == 64, TriLive<true>, AllLive>;
+    Acc<false, TN> acc;
+    acc.zero();
     gemm_pipe<false, TN, false>(
         acc, s, 0, p.wp,
         [&](int m, int kg) -> cplx {   // Linv[c][k]: column k of the diagonal block
@@ -1413,11 +1468,8 @@ __global__ void PXS_LB(CPLX, TN) k_trsm(Src src) {
           return ld_or_zero<false>(Ls, rbase + (int64_t)kg * p.ld + ig, kg < p.wp && ig < p.nb);
         },
         RowsFast(), NoScale(), LV());
+    acc_foreach<false, TN, LV::kSwz>(acc, store);
   }
-  acc_foreach<CPLX, TN, LV::kSwz>(acc, [&](int m, int n, cplx v) {
-    const int ig = i0 + n;
-    if (m < p.wp && ig < p.nb) st_elem<CPLX>(Ls, rbase + (int64_t)m * p.ld + ig, cmul(v, dinv[m]));
-  });
 }
 
 // Left-looking update of panel p from the earlier columns of its own
@@ -1434,16 +1486,25 @@ __global__ void PXS_LB(CPLX, TN) k_int_update(Src src) {
   const int r0 = bx * TN;            // rows p0 + r0 .. of the row list
   const int nrows = p.ld - p.p0;
   const int64_t cbase = p.off + p.p0;        // element (row p0, column 0)
-  Acc<CPLX, TN> acc;
-  acc.zero();
+  auto at = [&](int m, int n, int64_t& e) {
+    const int rg = r0 + n;
+    // clamped into the panel (in bounds for skipped elements)
+    e = cbase + (int64_t)(p.p0 + min(m, p.wp - 1)) * p.ld + min(rg, nrows - 1);
+    return m < p.wp && rg < nrows && rg >= m;
+  };
   if constexpr (CPLX) {
     // A: L[p0 + c][k], scaled by d_k on the way to the MFMAs; B: L[p0 + r][k]
     __shared__ CStage<TN, true> s;
-    gemm_lds<TN>(acc, s, p.p0, ColsOp<64>(Ls + 2 * cbase, p.ld, p.wp, p.p0),
-                 ColsOp<TN>(Ls + 2 * (cbase + r0), p.ld, nrows - r0, p.p0),
-                 DiagOp(Ls + 2 * p.off, (int64_t)p.ld + 1, p.p0));
+    with_layout<TN>(p.wp, [&](auto& acc) {
+      gemm_lds(acc, s, p.wp, p.p0, ColsOp<64>(Ls + 2 * cbase, p.ld, p.wp, p.p0),
+               ColsOp<TN>(Ls + 2 * (cbase + r0), p.ld, nrows - r0, p.p0),
+               DiagOp(Ls + 2 * p.off, (int64_t)p.ld + 1, p.p0), AllBlocks());
+      acc_sub_into(acc, Ls, at);
+    });
   } else {
     __shared__ Stage2<false, TN> s;
+    Acc<false, TN> acc;
+    acc.zero();
     gemm_pipe<false, TN, false>(
         acc, s, 0, p.p0,
         [&](int m, int kg) -> cplx {   // L[p0 + c][k] (times d_k on the way to the MFMAs)
@@ -1457,13 +1518,8 @@ __global__ void PXS_LB(CPLX, TN) k_int_update(Src src) {
         [&](int kg) -> cplx {          // d_k
           return ld_or_zero<false>(Ls, p.off + (int64_t)kg * p.ld + kg, kg < p.p0);
         });
+    acc_sub_into(acc, Ls, at);
   }
-  acc_sub_into<CPLX, TN>(acc, Ls, [&](int m, int n, int64_t& e) {
-    const int rg = r0 + n;
-    // clamped into the panel (in bounds for skipped elements)
-    e = cbase + (int64_t)(p.p0 + min(m, p.wp - 1)) * p.ld + min(rg, nrows - 1);
-    return m < p.wp && rg < nrows && rg >= m;
-  });
 }
 
 __device__ __forceinline__ void tri_index(int b, int& ti, int& tj) {
@@ -1497,16 +1553,31 @@ __global__ void PXS_LB(CPLX, TN) k_update(Src src) {
   const int base = p.p0 + p.wp;   // row-list position of the first row below
   const int64_t rbase = p.off + base;   // element (row base, column 0)
   const int kb = p.p0, ke = p.p0 + p.wp;
-  Acc<CPLX, TN> acc;
-  acc.zero();
+  const int64_t* cmap = c.colmap + p.cm;
+  const int64_t* cseg = c.colseg + p.cm;
+  auto at = [&](int m, int n, int64_t& e) {
+    const int jg = j0 + m, ig = i0 + n;
+    // branch-free, so the map loads of all elements are in flight together:
+    // indices clamped into the supernode's row list with row >= column
+    // (where relpos is defined); a skipped element reads a valid position
+    // and is not stored
+    const int jc = min(jg, p.nb - 1), ic = min(max(ig, jc), p.nb - 1);
+    e = cmap[base + jc] + c.relpos[cseg[base + jc] + base + ic];
+    return jg < p.nb && ig < p.nb && ig >= jg;
+  };
   if constexpr (CPLX) {
     __shared__ CStage<TN, true> s;
     const int64_t k0 = rbase + (int64_t)kb * p.ld;
-    gemm_lds<TN>(acc, s, ke - kb, ColsOp<64>(Ls + 2 * (k0 + j0), p.ld, p.nb - j0, ke - kb),
-                 ColsOp<TN>(Ls + 2 * (k0 + i0), p.ld, p.nb - i0, ke - kb),
-                 DiagOp(Ls + 2 * (p.off + (int64_t)kb * (p.ld + 1)), (int64_t)p.ld + 1, ke - kb));
+    with_layout<TN>(min(64, p.nb - j0), [&](auto& acc) {
+      gemm_lds(acc, s, p.nb - j0, ke - kb, ColsOp<64>(Ls + 2 * (k0 + j0), p.ld, p.nb - j0, ke - kb),
+               ColsOp<TN>(Ls + 2 * (k0 + i0), p.ld, p.nb - i0, ke - kb),
+               DiagOp(Ls + 2 * (p.off + (int64_t)kb * (p.ld + 1)), (int64_t)p.ld + 1, ke - kb), AllBlocks());
+      acc_sub_into(acc, Ls, at);
+    });
   } else {
     __shared__ Stage2<false, TN> s;
+    Acc<false, TN> acc;
+    acc.zero();
     gemm_pipe<false, TN, false>(
         acc, s, kb, ke,
         [&](int m, int kg) -> cplx {   // L[j][k] (times d_k on the way to the MFMAs)
@@ -1521,19 +1592,8 @@ __global__ void PXS_LB(CPLX, TN) k_update(Src src) {
         [&](int kg) -> cplx {          // d_k
           return ld_or_zero<false>(Ls, p.off + (int64_t)kg * p.ld + kg, kg < ke);
         });
+    acc_sub_into(acc, Ls, at);
   }
-  const int64_t* cmap = c.colmap + p.cm;
-  const int64_t* cseg = c.colseg + p.cm;
-  acc_sub_into<CPLX, TN>(acc, Ls, [&](int m, int n, int64_t& e) {
-    const int jg = j0 + m, ig = i0 + n;
-    // branch-free, so the map loads of all elements are in flight together:
-    // indices clamped into the supernode's row list with row >= column
-    // (where relpos is defined); a skipped element reads a valid position
-    // and is not stored
-    const int jc = min(jg, p.nb - 1), ic = min(max(ig, jc), p.nb - 1);
-    e = cmap[base + jc] + c.relpos[cseg[base + jc] + base + ic];
-    return jg < p.nb && ig < p.nb && ig >= jg;
-  });
 }
 
 // --------------------------------------------------------------------------
@@ -1557,15 +1617,14 @@ __global__ void PXS_LB(true, TN) k_lhat(Src src) {
   const int i0 = bx * TN;
   const int64_t dbase = p.off + (int64_t)p.p0 * p.ld + p.p0;
   const int64_t rbase = dbase + p.wp;
-  Acc<true, TN> acc;
-  acc.zero();
   // A[m][k] = L^{-1}[k][m] vanishes for k < m (see k_trsm)
-  using LV = TriLive<false, TN>;
-  gemm_lds<TN, LV>(acc, s, p.wp, TriOp<true>(Ls + 2 * dbase, p.ld, p.wp),
-                   ColsOp<TN>(Ls + 2 * (rbase + i0), p.ld, p.nb - i0, p.wp), NoDiag());
-  acc_foreach<true, TN, LV::kSwz>(acc, [&](int m, int n, cplx v) {
-    const int ig = i0 + n;
-    if (m < p.wp && ig < p.nb) st_elem<true>(W, (int64_t)m * p.nb + ig, v);
+  with_layout<TN>(p.wp, [&](auto& acc) {
+    gemm_lds(acc, s, p.wp, p.wp, TriOp<true>(Ls + 2 * dbase, p.ld, p.wp),
+             ColsOp<TN>(Ls + 2 * (rbase + i0), p.ld, p.nb - i0, p.wp), NoDiag(), TriBlocks<false>());
+    acc_foreach<true, TN, swz_of<decltype(acc), TriBlocks<false>>>(acc, [&](int m, int n, cplx v) {
+      const int ig = i0 + n;
+      if (m < p.wp && ig < p.nb) st_elem<true>(W, (int64_t)m * p.nb + ig, v);
+    });
   });
 }
 
@@ -1587,16 +1646,16 @@ __global__ void PXS_LB(true, TN) k_selinv_off(Src src) {
   const int i0 = bx * TN;
   const int base = p.p0 + p.wp;
   const int gw = p.w - base;   // rows of B inside the supernode
-  Acc<true, TN> acc;
-  acc.zero();
-  gemm_lds<TN>(acc, s, p.nb, RowsOp<64>(W, p.nb, p.wp, p.nb),
-               SymOp<TN, false>(Ls + 2 * (p.off + (int64_t)base * (p.ld + 1)), p.ld, G - 2 * (int64_t)gw * (p.c + 1), p.c,
-                                gw, i0, p.nb),
-               NoDiag());
   const int64_t rbase = p.off + (int64_t)p.p0 * p.ld + base;
-  acc_foreach<true, TN>(acc, [&](int m, int n, cplx v) {
-    const int ig = i0 + n;
-    if (m < p.wp && ig < p.nb) st_elem<true>(Ls, rbase + (int64_t)m * p.ld + ig, cplx{-v.re, -v.im});
+  with_layout<TN>(p.wp, [&](auto& acc) {
+    gemm_lds(acc, s, p.wp, p.nb, RowsOp<64>(W, p.nb, p.wp, p.nb),
+             SymOp<TN, false>(Ls + 2 * (p.off + (int64_t)base * (p.ld + 1)), p.ld, G - 2 * (int64_t)gw * (p.c + 1), p.c, gw,
+                              i0, p.nb),
+             NoDiag(), AllBlocks());
+    acc_foreach<true, TN>(acc, [&](int m, int n, cplx v) {
+      const int ig = i0 + n;
+      if (m < p.wp && ig < p.nb) st_elem<true>(Ls, rbase + (int64_t)m * p.ld + ig, cplx{-v.re, -v.im});
+    });
   });
 }
 
@@ -1643,30 +1702,34 @@ __global__ void __launch_bounds__(NT) k_gather_cc(Src src) {
   }
 }
 
-// Partial W^T Z_Bp over k in [split * SPLIT_ROWS, ...): P[c][r] = sum_k Z[k][c] W[k][r].
-template <class Src>
-__global__ void PXS_LB(true, 64) k_selinv_diag_partial(Src src) {
-  __shared__ CStage<TM, false> s;
+// Partial W^T Z_Bp over k in [split * SPLIT_ROWS, ...): P[c][r] = sum_k Z[k][c] W[k][r],
+// in tiles of TN of its columns r (tile bx = split x columns).
+template <int TN, class Src>
+__global__ void PXS_LB(true, TN) k_selinv_diag_partial(Src src) {
+  __shared__ CStage<TN, false> s;
   Common c;
   PanelK p;
   int bx, by;
   locate(src, c, p, bx, by, true);
   const int sh = p.sh0 + by;
-  const int sp = bx;
+  const int nt = (p.wp + TN - 1) / TN;
+  const int sp = bx / nt, n0 = (bx - sp * nt) * TN;
   double* Ls = shift_base<true>(c, sh);
   double* W = wbase(c, sh);
   double* part = W + 2 * (int64_t)p.nb * p.wp;   // after W: split x 64 x 64 complex
   const int base = p.p0 + p.wp;
   const int64_t rbase = p.off + (int64_t)p.p0 * p.ld + base;
   const int kb = sp * (int)SPLIT_ROWS, ke = min(p.nb, kb + (int)SPLIT_ROWS);
-  Acc<true, TM> acc;
-  acc.zero();
+  double* out = part + 2 * (int64_t)sp * 64 * 64;
   // Z_pp is symmetric and stored by its lower triangle: only P[c][r], r >= c,
   // is summed by k_selinv_diag_final, so the blocks below that are skipped
-  gemm_lds<TM, UpperLive>(acc, s, ke - kb, RowsOp<64>(Ls + 2 * (rbase + kb), p.ld, p.wp, ke - kb),
-                          RowsOp<TM>(W + 2 * (int64_t)kb, p.nb, p.wp, ke - kb), NoDiag());
-  double* out = part + 2 * (int64_t)sp * 64 * 64;
-  acc_foreach<true, TM, UpperLive::kSwz>(acc, [&](int m, int n, cplx v) { st_elem<true>(out, (int64_t)m * 64 + n, v); });
+  with_layout<TN>(p.wp, [&](auto& acc) {
+    const UpperBlocks lv{n0 / 16};
+    gemm_lds(acc, s, p.wp, ke - kb, RowsOp<64>(Ls + 2 * (rbase + kb), p.ld, p.wp, ke - kb),
+             RowsOp<TN>(W + 2 * ((int64_t)n0 * p.nb + kb), p.nb, p.wp - n0, ke - kb), NoDiag(), lv);
+    acc_foreach<true, TN, swz_of<decltype(acc), UpperBlocks>>(
+        acc, [&](int m, int n, cplx v) { st_elem<true>(out, (int64_t)m * 64 + n0 + n, v); });
+  });
 }
 
 // Z_pp = Linv^T D^{-1} Linv - sum of the partials, written over the diagonal block.
@@ -1937,16 +2000,22 @@ Common make_common(const Symbolic& S, void* L, void* work) {
 // on a full launch (4096 rows x 32 shifts), hence the rates.  At 884 rows x
 // 60 shifts (4, 7 and 14 rounds) 54.4, 59.9 and 53.6 TFLOP/s, at 452 x 40 (2,
 // 3, 5 rounds) 33.3, 43.4 and 47.8, at 130 x 40 (1, 1, 2) 13.7, 22.6 and 22.2.
+//
+// m: rows of the product (the panel's width): with b of its four 16-row blocks
+// live a wave multiplies b blocks per 16 columns on 64-column tiles, (b + 1) / 2
+// on 32- and one on 16-column ones (with_layout).
 constexpr int NCU = 256;
 template <class F>
-int pick_tile(F tiles) {
+int pick_tile(int m, F tiles) {
+  const int b = std::min(4, (m + 15) / 16);
   const int width[3] = {64, 32, 16};
+  const int work[3] = {b, (b + 1) / 2, 1};
   const double rate[3] = {1.0, 0.985, 0.88};
   int best = 64;
   double cost = 0.0;
   for (int q = 0; q < 3; ++q) {
     const int64_t rounds = ((int64_t)tiles(width[q]) + NCU - 1) / NCU;
-    const double t = (double)rounds * width[q] / rate[q];
+    const double t = (double)rounds * work[q] / rate[q];
     if (q == 0 || t < cost) {
       best = width[q];
       cost = t;
@@ -2136,7 +2205,9 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
   const double fm = CPLX ? 8.0 : 2.0;   // flops per multiply-add
   const double eb = CPLX ? 16.0 : 8.0;  // bytes per element
   // tile width of a product over `rows` rows
-  auto tile = [&](int rows) { return CPLX ? pick_tile([&](int tn) { return (int64_t)tiles_of(rows, tn) * nshift; }) : TR; };
+  auto tile = [&](int rows, int m) {
+    return CPLX ? pick_tile(m, [&](int tn) { return (int64_t)tiles_of(rows, tn) * nshift; }) : TR;
+  };
   // the panel work of one panel: left-looking update from the earlier
   // columns of its supernode, LDL^T of the diagonal block, the rows below
   auto panel_work = [&](const Panel& P, hipStream_t s) -> int {
@@ -2146,7 +2217,7 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
       const int nrows = k.ld - k.p0;
       ProfScope ps(KC_UPDATE, s, fm * nshift * xm.intu, eb * nshift * ((double)nrows * k.p0 + 2.0 * nrows * k.wp),
                    fm * nshift * ((double)nrows * k.wp - 0.5 * k.wp * (k.wp - 1)) * k.p0);
-      with_tile_of<CPLX>(tile(nrows), [&](auto t) {
+      with_tile_of<CPLX>(tile(nrows, k.wp), [&](auto t) {
         constexpr int TN = decltype(t)::value;
         hipLaunchKernelGGL((k_int_update<CPLX, TN, OnePanel>), dim3(tiles_of(nrows, TN), nshift), dim3(NT), 0, s, OnePanel{c, k});
       });
@@ -2159,7 +2230,7 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
     if (k.nb > 0) {
       ProfScope ps(KC_TRSM, s, fm * nshift * xm.trsm, eb * nshift * (2.0 * k.nb * k.wp + 0.5 * k.wp * (k.wp + 1)),
                    fm * nshift * (double)k.nb * k.wp * (k.wp + 1) / 2.0);
-      with_tile_of<CPLX>(tile(k.nb), [&](auto t) {
+      with_tile_of<CPLX>(tile(k.nb, k.wp), [&](auto t) {
         constexpr int TN = decltype(t)::value;
         hipLaunchKernelGGL((k_trsm<CPLX, TN, OnePanel>), dim3(tiles_of(k.nb, TN), nshift), dim3(NT), 0, s, OnePanel{c, k});
       });
@@ -2177,7 +2248,7 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
     u.p0 = 0;
     u.wp = w;
     u.nb = below;
-    const int tn = CPLX ? pick_tile([&](int q) { return update_tiles(below, q) * nshift; }) : TR;
+    const int tn = CPLX ? pick_tile(below, [&](int q) { return update_tiles(below, q) * nshift; }) : TR;
     ProfScope ps(KC_UPDATE, s, fm * nshift * S.xm_update[P.J],
                  eb * nshift * ((double)below * w + (double)below * (below + 1)),
                  fm * nshift * (double)below * (below + 1) / 2.0 * w);
@@ -2298,7 +2369,10 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
       grp.n = 0;
       int64_t start = 0;
       double w = 0.0, b = 0.0, s = 0.0;
-      const int tn = !CPLX ? TR : pick_tile([&](int tq) {
+      int m = 0;
+      for (int q = 0; q < NS; ++q)
+        if (ready(q) && lane[q][pos[q]].kind == kind) m = std::max(m, lane[q][pos[q]].it.p.wp);
+      const int tn = !CPLX ? TR : pick_tile(m, [&](int tq) {
         int64_t n = 0;
         for (int q = 0; q < NS; ++q)
           if (ready(q) && lane[q][pos[q]].kind == kind) n += (int64_t)tiles_of(lane[q][pos[q]].rows, tq) * nshift;
@@ -2483,7 +2557,11 @@ int lane_launch(int32_t kind, int tn, const LaneGroup& g, int64_t blocks, hipStr
         hipLaunchKernelGGL((k_selinv_off<decltype(t)::value, LaneGroup>), grid, dim3(NT), 0, st, g);
       });
       break;
-    case LK_DPART: hipLaunchKernelGGL(k_selinv_diag_partial<LaneGroup>, grid, dim3(NT), 0, st, g); break;
+    case LK_DPART:
+      with_tile(tn, [&](auto t) {
+        hipLaunchKernelGGL((k_selinv_diag_partial<decltype(t)::value, LaneGroup>), grid, dim3(NT), 0, st, g);
+      });
+      break;
     case LK_DFIN: hipLaunchKernelGGL(k_selinv_diag_final<LaneGroup>, grid, dim3(NTF), 0, st, g); break;
     default: return (int)hipErrorInvalidValue;
   }
@@ -2588,10 +2666,16 @@ int run_selinv_lanes(const Symbolic& S, int nshift, void* L, void* work, hipStre
       grp.n = 0;
       int64_t start = 0;
       double w = 0.0, b = 0.0, s = 0.0;
-      const int tn = pick_tile([&](int tq) {
+      int m = 0;
+      for (int q = 0; q < NL; ++q)
+        if (ready(q) && lane[q][pos[q]].kind == kind) m = std::max(m, lane[q][pos[q]].it.p.wp);
+      const int tn = pick_tile(m, [&](int tq) {
         int64_t n = 0;
-        for (int q = 0; q < NL; ++q)
-          if (ready(q) && lane[q][pos[q]].kind == kind) n += (int64_t)tiles_of(lane[q][pos[q]].rows, tq) * nsh;
+        for (int q = 0; q < NL; ++q) {
+          if (!ready(q) || lane[q][pos[q]].kind != kind) continue;
+          const LaneOp& o = lane[q][pos[q]];
+          n += (int64_t)(kind == LK_DPART ? o.it.p.split * tiles_of(o.it.p.wp, tq) : tiles_of(o.rows, tq)) * nsh;
+        }
         return n;
       });
       for (int q = 0; q < NL; ++q) {
@@ -2599,6 +2683,7 @@ int run_selinv_lanes(const Symbolic& S, int nshift, void* L, void* work, hipStre
         const LaneOp& o = lane[q][pos[q]];
         GroupItem it = o.it;
         if (o.rows > 0) it.tiles = tiles_of(o.rows, tn);
+        if (kind == LK_DPART) it.tiles = it.p.split * tiles_of(it.p.wp, tn);
         it.start = start;
         start += (int64_t)it.tiles * it.nsh;
         grp.it[grp.n++] = it;
@@ -2696,7 +2781,7 @@ int run_selinv(const Symbolic& S, int nshift, void* L, void* work, hipStream_t s
         k.sh0 = sh0;
         const PanelMacs& xm = S.xm_panel[ip];
         if (k.nb > 0) {
-          const int tn = pick_tile([&](int q2) { return (int64_t)tiles_of(k.nb, q2) * nsh; });
+          const int tn = pick_tile(k.wp, [&](int q2) { return (int64_t)tiles_of(k.nb, q2) * nsh; });
           {
             // L-hat is a by-product of the blocked algorithm: no exact flops
             ProfScope ps(KC_LHAT, sj, 0.0, 16.0 * nsh * (2.0 * k.nb * k.wp + 0.5 * k.wp * (k.wp + 1)),
@@ -2720,7 +2805,11 @@ int run_selinv(const Symbolic& S, int nshift, void* L, void* work, hipStream_t s
             ProfScope ps(KC_SELINV_DIAG, sj, 8.0 * nsh * xm.sdiag,
                          16.0 * nsh * (2.0 * k.nb * k.wp + (double)k.wp * k.wp),
                          8.0 * nsh * (double)k.nb * k.wp * k.wp);
-            hipLaunchKernelGGL(k_selinv_diag_partial<OnePanel>, dim3(k.split, nsh), dim3(NT), 0, sj, OnePanel{c, k});
+            with_tile(pick_tile(k.wp, [&](int q2) { return (int64_t)k.split * tiles_of(k.wp, q2) * nsh; }), [&](auto t) {
+              constexpr int TN = decltype(t)::value;
+              hipLaunchKernelGGL((k_selinv_diag_partial<TN, OnePanel>), dim3(k.split * tiles_of(k.wp, TN), nsh), dim3(NT), 0,
+                                 sj, OnePanel{c, k});
+            });
           }
         }
         hipLaunchKernelGGL(k_selinv_diag_final<OnePanel>, dim3(1, nsh), dim3(NTF), 0, sj, OnePanel{c, k});
