@@ -1095,15 +1095,28 @@ struct PanelGroup {
   int32_t n;
 };
 
-// LaneGroup: the same as PanelGroup for at most MAX_LANES panels whose items
-// travel in the kernel arguments (no device table, so a stream capture
-// records them like any other launch): the fused selected inversion of the
-// subtree lanes of one system.
-constexpr int MAX_LANES = 8;
-struct LaneGroup {
-  GroupItem it[MAX_LANES];
-  int32_t n;
+// LaneGroup: the same as PanelGroup for at most N panels of one system whose
+// items travel in the kernel arguments (no device table, so a stream capture
+// records them like any other launch): the fused launches of a tree of small
+// supernodes.  Everything but the panel and the workspace views is common;
+// starts sit in one array, which a workgroup reads as a whole.  A launch of one
+// panel goes as OnePanel and one of up to FEW_ITEMS in the short form: reading
+// 3.6 KB of arguments adds 2 us to every launch.
+constexpr int MAX_ITEMS = 32, FEW_ITEMS = 8;
+struct LaneItem {
+  PanelK p;
+  int64_t wfix;      // workspace views of the item (Common's fields)
+  double* G;
+  int64_t gstride;
+  int32_t tiles;     // workgroups per shift
 };
+template <int N>
+struct LaneGroup {
+  Common c;
+  int32_t start[N];   // first logical workgroup of the item (INT32_MAX behind the last)
+  LaneItem it[N];
+};
+static_assert(sizeof(LaneGroup<MAX_ITEMS>) <= 4096, "kernel arguments");
 
 // remap: XCD-aware order (else the plain one); bx = tile, by = shift
 __device__ __forceinline__ void locate(const OnePanel& src, Common& c, PanelK& p, int& bx, int& by, bool remap) {
@@ -1135,16 +1148,20 @@ __device__ __forceinline__ void locate(const PanelGroup& src, Common& c, PanelK&
   by = (int)(local / it.tiles);
 }
 
-__device__ __forceinline__ void locate(const LaneGroup& src, Common& c, PanelK& p, int& bx, int& by, bool remap) {
+template <int N>
+__device__ __forceinline__ void locate(const LaneGroup<N>& src, Common& c, PanelK& p, int& bx, int& by, bool remap) {
   int lx = (int)blockIdx.x, ly = 0;
   if (remap) xcd_remap(lx, ly);   // grid (total, 1)
-  int i = 0;                      // the last item starting at or before lx
-  for (int q = 1; q < src.n; ++q)
-    if (src.it[q].start <= lx) i = q;
-  const GroupItem& it = src.it[i];
-  c = it.c;
+  int i = -1;                     // the last item starting at or before lx
+#pragma unroll
+  for (int q = 0; q < N; ++q) i += src.start[q] <= lx ? 1 : 0;
+  const LaneItem& it = src.it[i];
+  c = src.c;
+  c.wfix = it.wfix;
+  c.G = it.G;
+  c.gstride = it.gstride;
   p = it.p;
-  const int local = lx - (int)it.start;
+  const int local = lx - src.start[i];
   bx = local % it.tiles;
   by = local / it.tiles;
 }
@@ -1180,7 +1197,10 @@ __device__ __forceinline__ void flag_pivots(const Common& c, int sh, int bad, in
 //   rest(b)    beside panel(b + 1), waves 1-3: the other trailing blocks and
 //              the inverse: X_bm = X_bb Y_bm for the columns m < b, Y_im -= L_ib
 //              X_bm for the rows below (X = L^{-1}, Y its partial sums).  X_bb
-//              comes from lanes of panel(b) that have no row (b > 0).
+//              comes from lanes of panel(b) that have no row.
+// With at most SMALL_ROWS rows below the block it also computes them (L_Bp =
+// A_Bp L_pp^{-T} D^{-1}, k_trsm's work): a launch less where a launch is what
+// counts (a chain's k_trsm took 8 us beside 16 of this kernel).
 // 26 us per launch of 64 complex columns x 60 shifts (real: 25), 14 for 16
 // columns; of the 64-column time about 11 us are panels (one wave's issue of
 // lane reads and fused multiply-adds), 4 the trailing products, the rest
@@ -1190,6 +1210,7 @@ __device__ __forceinline__ void flag_pivots(const Common& c, int sh, int bad, in
 // fits on a CU beside two of the matrix kernels.  Rows and columns from wp on
 // are those of the identity.
 constexpr int NTD = 256;
+constexpr int SMALL_ROWS = 80;   // rows below a panel that k_diag and k_selinv_small take along
 constexpr int LDD = 65;   // row stride of a[][]: 16-byte elements rotate over the banks
 
 template <bool CPLX>
@@ -1332,7 +1353,7 @@ __global__ void __launch_bounds__(NTD, 2) k_diag(Src src) {
   // the inverse's share of step b, column blocks m = q, q + nq, ...
   auto inverse = [&](int b, int q, int nq) {
     const int c0 = 16 * b;
-    if (b == 0) inverse_of_first();
+    if (b == 0 && wp > 48) inverse_of_first();
     wave_sync();
     for (int m = q; m <= b; m += nq) {
       if (m < b)
@@ -1354,19 +1375,18 @@ __global__ void __launch_bounds__(NTD, 2) k_diag(Src src) {
     const int c0 = 16 * b;
     if (w == 0) {
       const int row = c0 + lane;
-      const bool in = row < 64;
-      // lanes without a row of A (b > 0: LE and up have none) carry the rows
-      // of an identity below it: their entries before the division are
-      // (I L_bb^{-T})[i][j] = X_bb[j][i]
-      const int LE = b > 0 ? 48 : 64;
+      // lanes without a row of A (LE and up, unless the first block column has
+      // 64 rows) carry the rows of an identity below it: their entries before
+      // the division are (I L_bb^{-T})[i][j] = X_bb[j][i]
+      const int LE = b > 0 || wp <= 48 ? 48 : 64;
+      const bool in = lane < LE && row < 64;
       cplx x[16];
 #pragma unroll
       for (int k = 0; k < 16; ++k) x[k] = in ? to_cplx(a[c0 + k][row]) : cplx{lane - LE == k ? 1.0 : 0.0, 0.0};
       // one basic block: the next column is updated first and its pivot's
       // reciprocal runs beside the updates of the others
       cplx id = inv_of<CPLX>(cplx{lane_read(x[0].re, 0), CPLX ? lane_read(x[0].im, 0) : 0.0});
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
+      auto column = [&](int j) {
         const cplx aj = x[j];   // A[row][j] before the division
         const cplx l = mul<CPLX>(aj, id);
 #pragma unroll
@@ -1377,13 +1397,19 @@ __global__ void __launch_bounds__(NTD, 2) k_diag(Src src) {
         const bool keep = lane == j || lane >= LE;
         x[j].re = keep ? aj.re : l.re;
         x[j].im = keep ? aj.im : l.im;
+      };
+#pragma unroll
+      for (int j = 0; j < 8; ++j) column(j);
+      if (c0 + 8 < wp) {   // else only identity columns follow, which stay as they are
+#pragma unroll
+        for (int j = 8; j < 16; ++j) column(j);
       }
 #pragma unroll
       for (int k = 0; k < 16; ++k) {
         if (in && lane > k) a[c0 + k][row] = to_elem<CPLX>(x[k]);
         if (lane == k) pv[c0 + k] = to_elem<CPLX>(x[k]);
         // X_bb[k][i] from the identity row i
-        if (b > 0 && lane >= LE && lane - LE < k) a[c0 + k][c0 + lane - LE] = to_elem<CPLX>(x[k]);
+        if (lane >= LE && lane - LE < k) a[c0 + k][c0 + lane - LE] = to_elem<CPLX>(x[k]);
       }
     } else if (b > 0) {
       // the trailing blocks right of column b by step b - 1, then its inverse
@@ -1397,6 +1423,20 @@ __global__ void __launch_bounds__(NTD, 2) k_diag(Src src) {
     if (b + 1 < nblk && b + 1 + w < nblk) trailing(b, b + 1 + w, b + 1);
     __syncthreads();
   }
+  // the rows below, block column w of 16 rows at a time
+  const bool rows_too = p.nb > 0 && p.nb <= SMALL_ROWS;
+  const int64_t rbase = dbase + wp;
+  cplx f[16];
+  auto load_rows = [&](int n) {
+    const int i = 16 * n + li;
+#pragma unroll
+    for (int ks = 0; ks < 16; ++ks) {
+      const int k = 4 * ks + lk;
+      f[ks] = cplx{0.0, 0.0};
+      if (i < p.nb && k < wp) f[ks] = ld_elem<CPLX>(Ls, rbase + (int64_t)k * p.ld + i);
+    }
+  };
+  if (rows_too) load_rows(0);
   inverse(nblk - 1, w, 4);
   if (w == 0) {
     const double wabs = sqrt(c.shifts[2 * sh] * c.shifts[2 * sh] + c.shifts[2 * sh + 1] * c.shifts[2 * sh + 1]);
@@ -1413,6 +1453,31 @@ __global__ void __launch_bounds__(NTD, 2) k_diag(Src src) {
     const int cc = w + 4 * u;
     if (lane < wp && lane >= cc)
       st_elem<CPLX>(Ls, dbase + (int64_t)cc * p.ld + lane, to_cplx(lane > cc ? a[lane][cc] : pv[cc]));
+  }
+  if (!rows_too) return;
+  for (int n = 0; 16 * n < p.nb; ++n) {
+    if (n > 0) load_rows(n);
+    stage_barrier();   // every wave has read the rows that the others overwrite
+    if (w >= nblk) continue;
+    dbl4 re{0.0, 0.0, 0.0, 0.0}, im{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int ks = 0; ks < 16; ++ks) {
+      if (ks / 4 > w) continue;   // X[c][k] = 0 for k > c
+      const int r = 16 * w + li, k = 4 * ks + lk;
+      const cplx x = r > k ? X(r, k) : cplx{r == k ? 1.0 : 0.0, 0.0};
+      re = __builtin_amdgcn_mfma_f64_16x16x4f64(x.re, f[ks].re, re, 0, 0, 0);
+      if constexpr (CPLX) {
+        im = __builtin_amdgcn_mfma_f64_16x16x4f64(x.re, f[ks].im, im, 0, 0, 0);
+        re = __builtin_amdgcn_mfma_f64_16x16x4f64(x.im, f[ks].im, re, 0, 0, 1);
+        im = __builtin_amdgcn_mfma_f64_16x16x4f64(x.im, f[ks].re, im, 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int cc = 16 * w + lk + 4 * r, i = 16 * n + li;
+      if (cc < wp && i < p.nb)
+        st_elem<CPLX>(Ls, rbase + (int64_t)cc * p.ld + i, mul<CPLX>(cplx{re[r], im[r]}, inv_of<CPLX>(to_cplx(pv[cc]))));
+    }
   }
 }
 
@@ -1820,6 +1885,157 @@ __global__ void __launch_bounds__(NTF, 2) k_selinv_diag_final(Src src) {
   }
 }
 
+// The whole selected inversion of one panel with at most SMALL_ROWS rows below
+// its diagonal block: W = L_Bp Linv, Z_Bp = -Z_BB W and Z_pp in one workgroup
+// per shift, Z_BB read through the maps.  A tree of small supernodes (a 1D chain: 64 columns, 16
+// rows below) is bound by the latency of its launches; as five launches per
+// level (Z_CC gather, W, Z_Bp, partials, final) it took 5.5 + 7.4 + 11.4 + 7.4 +
+// 6.2 us with 8 lanes x 60 shifts.  Per panel: all loads first (Linv, the first
+// blocks of L_Bp and Z_BB), W in LDS, the diagonal product, Z_Bp over Linv's
+// place in LDS, the second diagonal product.
+
+//
+// ROWS = 16 for panels of at most that many rows: 80 KB of LDS, two workgroups
+// per CU.
+template <int ROWS, class Src>
+__global__ void __launch_bounds__(NT, ROWS <= 16 ? 2 : 1) k_selinv_small(Src src) {
+  // all 160 KB of LDS (ROWS = 80): Linv (column, row) with D^{-1} on its diagonal, then
+  // Z_Bp (row, column), and W (row, column); 64 slots a line, permuted by the
+  // line so that 16 lines are read or written without bank conflicts
+  __shared__ dbl2 xs[(ROWS > 64 ? ROWS : 64) * 64], wl[ROWS * 64];
+  auto at = [](int line, int q) { return line * 64 + (q ^ (line & 15)); };
+  Common c;
+  PanelK p;
+  int bx, by;
+  locate(src, c, p, bx, by, false);
+  const int sh = p.sh0 + by;
+  double* Ls = shift_base<true>(c, sh);
+  const int wp = p.wp, nb = p.nb;
+  const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+  const int w = wave_id();
+  const int64_t dbase = p.off + (int64_t)p.p0 * p.ld + p.p0;
+  const int64_t rbase = dbase + wp;
+  const int base = p.p0 + wp;
+  const int64_t* cmap = c.colmap + p.cm;
+  const int64_t* cseg = c.colseg + p.cm;
+  const int mbs = (wp + 15) / 16, nbs = (nb + 15) / 16;
+  cplx v[16];
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    const int cc = w + 4 * u;
+    v[u] = cplx{0.0, 0.0};
+    if (lane >= cc && lane < wp) v[u] = ld_elem<true>(Ls, dbase + (int64_t)cc * p.ld + lane);
+  }
+  // operand blocks of the rows 16 n..: L_Bp[i][k] (k < wp) and Z(k, i) (k < nb)
+  auto load_l = [&](int n, cplx (&f)[16]) {
+    const int i = 16 * n + li;
+#pragma unroll
+    for (int ks = 0; ks < 16; ++ks) {
+      const int k = 4 * ks + lk;
+      f[ks] = cplx{0.0, 0.0};
+      if (i < nb && k < wp) f[ks] = ld_elem<true>(Ls, rbase + (int64_t)k * p.ld + i);
+    }
+  };
+  constexpr int ZK = ROWS / 4;
+  auto load_z = [&](int n, cplx (&f)[ZK]) {
+    const int i = 16 * n + li;
+    int64_t e[ZK];
+#pragma unroll
+    for (int ks = 0; ks < ZK; ++ks) {
+      // branch-free over the maps: indices clamped into the row list
+      const int k = 4 * ks + lk;
+      const int q0 = base + min(i, nb - 1), q1 = base + min(k, nb - 1);
+      const int lo = min(q0, q1), hi = max(q0, q1);
+      e[ks] = lo < p.w ? p.off + (int64_t)lo * p.ld + hi : cmap[lo] + c.relpos[cseg[lo] + hi];
+    }
+#pragma unroll
+    for (int ks = 0; ks < ZK; ++ks) {
+      f[ks] = cplx{0.0, 0.0};
+      if (i < nb && 4 * ks + lk < nb) f[ks] = ld_elem<true>(Ls, e[ks]);
+    }
+  };
+  auto mac = [&](dbl4& re, dbl4& im, cplx a, cplx b) {
+    re = __builtin_amdgcn_mfma_f64_16x16x4f64(a.re, b.re, re, 0, 0, 0);
+    im = __builtin_amdgcn_mfma_f64_16x16x4f64(a.re, b.im, im, 0, 0, 0);
+    re = __builtin_amdgcn_mfma_f64_16x16x4f64(a.im, b.im, re, 0, 0, 1);
+    im = __builtin_amdgcn_mfma_f64_16x16x4f64(a.im, b.re, im, 0, 0, 0);
+  };
+  // the wave's block pairs (row block n, column block m): w, w + 4, ... of n mbs + m
+  cplx f[16], z[ZK];
+  if (w < mbs * nbs) {
+    load_l(w / mbs, f);
+    load_z(w / mbs, z);
+  }
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    const int cc = w + 4 * u;
+    if (lane == cc && lane < wp) v[u] = cinv(v[u]);
+    xs[at(cc, lane)] = dbl2{v[u].re, v[u].im};
+  }
+  __syncthreads();
+  auto X = [&](int col, int row) {   // Linv[row][col] for row >= col - 15
+    const cplx e = to_cplx(xs[at(col, row)]);
+    return row == col ? cplx{col < wp ? 1.0 : 0.0, 0.0} : e;
+  };
+  // W[i][c] = sum_{k >= c} Linv[k][c] L[i][k]
+  for (int q = w; q < mbs * nbs; q += 4) {
+    const int n = q / mbs, m = q - n * mbs;
+    if (q != w) load_l(n, f);
+    dbl4 re{0.0, 0.0, 0.0, 0.0}, im{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int ks = 0; ks < 16; ++ks)
+      if (ks / 4 >= m && ks / 4 < mbs) mac(re, im, X(16 * m + li, 4 * ks + lk), f[ks]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) wl[at(16 * n + li, 16 * m + lk + 4 * r)] = dbl2{re[r], im[r]};
+  }
+  // Z_pp's first term, the wave's blocks R >= C
+  dbl4 re[3], im[3];
+#pragma unroll
+  for (int b = 0; b < 3; ++b) {
+    int R, C;
+    tri_index(w + 4 * b, R, C);
+    re[b] = im[b] = dbl4{0.0, 0.0, 0.0, 0.0};
+    for (int kb = R; kb < mbs && R < 4; ++kb)
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        const int k = 16 * kb + ks * 4 + lk;
+        mac(re[b], im[b], cmul(X(16 * C + li, k), to_cplx(xs[at(k, k)])), X(16 * R + li, k));
+      }
+  }
+  __syncthreads();
+  // Z_Bp[i][c] = -sum_k W[k][c] Z(k, i)
+  for (int q = w; q < mbs * nbs; q += 4) {
+    const int n = q / mbs, m = q - n * mbs;
+    if (q != w) load_z(n, z);
+    dbl4 zr{0.0, 0.0, 0.0, 0.0}, zi{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int ks = 0; ks < ZK; ++ks)
+      if (ks / 4 < nbs) mac(zr, zi, to_cplx(wl[at(4 * ks + lk, 16 * m + li)]), z[ks]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int cc = 16 * m + lk + 4 * r, i = 16 * n + li;
+      xs[at(i, cc)] = dbl2{-zr[r], -zi[r]};
+      if (cc < wp && i < nb) st_elem<true>(Ls, rbase + (int64_t)cc * p.ld + i, cplx{-zr[r], -zi[r]});
+    }
+  }
+  __syncthreads();
+  // Z_pp[r][c] -= sum_k W[k][r] Z_Bp[k][c]
+#pragma unroll
+  for (int b = 0; b < 3; ++b) {
+    int R, C;
+    tri_index(w + 4 * b, R, C);
+    if (R >= mbs) continue;
+    dbl4 sr{0.0, 0.0, 0.0, 0.0}, si{0.0, 0.0, 0.0, 0.0};
+    for (int k = lk; k < 16 * nbs; k += 4) mac(sr, si, to_cplx(xs[at(k, 16 * C + li)]), to_cplx(wl[at(k, 16 * R + li)]));
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int cc = 16 * C + lk + 4 * r, row = 16 * R + li;
+      if (row >= cc && row < wp)
+        st_elem<true>(Ls, dbase + (int64_t)cc * p.ld + row, cplx{re[b][r] - sr[r], im[b][r] - si[r]});
+    }
+  }
+}
+
 // --------------------------------------------------------------------------
 // pole sums, extraction
 // --------------------------------------------------------------------------
@@ -2193,6 +2409,43 @@ int factor_prologue(const Symbolic& S, const double* H, const double* Sv, int ns
   return 0;
 }
 
+// launch(group, grid) with a fused launch's items (nsh shifts each) in the
+// shortest form that holds them; false when they pass the grid's range.
+template <class F>
+static bool with_group(const Common& c, const std::vector<LaneItem>& items, int nsh, F launch) {
+  int64_t total = 0;
+  for (const LaneItem& it : items) total += (int64_t)it.tiles * nsh;
+  if (items.empty() || total > (int64_t)INT32_MAX - 1) return false;
+  auto fill = [&](auto& g) {
+    constexpr int N = sizeof(g.start) / sizeof(g.start[0]);
+    g.c = c;
+    int64_t at = 0;
+    for (int q = 0; q < N; ++q) {
+      g.start[q] = INT32_MAX;
+      if (q >= (int)items.size()) continue;
+      g.start[q] = (int32_t)at;
+      g.it[q] = items[q];
+      at += (int64_t)items[q].tiles * nsh;
+    }
+  };
+  if (items.size() == 1) {
+    OnePanel o{c, items[0].p};
+    o.c.wfix = items[0].wfix;
+    o.c.G = items[0].G;
+    o.c.gstride = items[0].gstride;
+    launch(o, dim3((unsigned)items[0].tiles, (unsigned)nsh));
+  } else if (items.size() <= FEW_ITEMS) {
+    LaneGroup<FEW_ITEMS> g;
+    fill(g);
+    launch(g, dim3((unsigned)total));
+  } else {
+    LaneGroup<MAX_ITEMS> g;
+    fill(g);
+    launch(g, dim3((unsigned)total));
+  }
+  return true;
+}
+
 template <bool CPLX>
 int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int nshift, void* L,
                        void* work, hipStream_t st, bool inorder) {
@@ -2223,11 +2476,13 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
       });
     }
     {
-      ProfScope ps(KC_DIAG, s, fm * nshift * xm.diag, eb * nshift * (double)k.wp * (k.wp + 1),
-                   fm * nshift * (double)k.wp * k.wp * k.wp / 3.0);
+      const double rows = k.nb <= SMALL_ROWS ? k.nb : 0.0;   // rows below done along
+      ProfScope ps(KC_DIAG, s, fm * nshift * (xm.diag + (rows > 0.0 ? xm.trsm : 0.0)),
+                   eb * nshift * ((double)k.wp * (k.wp + 1) + 2.0 * rows * k.wp),
+                   fm * nshift * ((double)k.wp * k.wp * k.wp / 3.0 + rows * k.wp * (k.wp + 1) / 2.0));
       hipLaunchKernelGGL((k_diag<CPLX, OnePanel>), dim3(1, nshift), dim3(NTD), 0, s, OnePanel{c, k});
     }
-    if (k.nb > 0) {
+    if (k.nb > SMALL_ROWS) {
       ProfScope ps(KC_TRSM, s, fm * nshift * xm.trsm, eb * nshift * (2.0 * k.nb * k.wp + 0.5 * k.wp * (k.wp + 1)),
                    fm * nshift * (double)k.nb * k.wp * (k.wp + 1) / 2.0);
       with_tile_of<CPLX>(tile(k.nb, k.wp), [&](auto t) {
@@ -2276,143 +2531,162 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
   // one subtree stream, everything runs on the caller's stream.
   int err = 0;
   if (S.fused_lanes && NS > 1) {
-    // fused lanes (see run_selinv_lanes; no library streams or events, so
-    // also on the in-order paths): the panel operations of each lane
-    // (the sel_stream subtrees, supernodes in fac_order) and one more lane of
-    // the ancestor scatters in fac_order, all on the caller's stream; a
-    // launch takes the next operation of every ready lane of one kind.  The
-    // first panel operation of J waits for the scatter of fac_child[J] (and
-    // so for every scatter before it), a scatter for the last panel
-    // operation of its supernode; scatters are never fused with each other.
-    enum : int32_t { FK_INT, FK_DIAG, FK_TRSM, FK_UPD };
+    // Fused launches (no library streams or events, so also on the in-order
+    // paths): a launch takes the next panel operation of up to MAX_ITEMS
+    // supernodes, of the kind that most of them wait for; a supernode is ready
+    // once every scatter into it was in an earlier launch.  When no panel
+    // operation is ready, one launch takes the scatters of finished supernodes
+    // that share no target supernode with each other or with an earlier one
+    // (in fac_order) that has not been scattered, so every entry receives its
+    // scatters in the same order as on the other paths.  (One launch per
+    // scatter and one lane per subtree stream took 52 launches of panel work
+    // and scatters for a chain of 31 supernodes.)
+    enum : int32_t { FK_INT, FK_DIAG, FK_TRSM, FK_UPD, FK_KINDS };
     struct FOp {
-      int32_t kind, J;
-      bool first, last;
+      int32_t kind;
       int32_t rows;   // rows of the product (its tiles follow from the launch's tile width)
-      GroupItem it;
+      PanelK p;
       double work, bytes, stored;
     };
-    if (NS > MAX_LANES) return (int)hipErrorInvalidValue;
-    std::vector<std::vector<FOp>> lane(NS + 1);   // lane NS: the scatters
+    if ((int)S.tgt_ptr.size() != ns + 1) return (int)hipErrorInvalidValue;
+    std::vector<std::vector<FOp>> ops(ns);
+    std::vector<int32_t> order;   // supernodes with panels, in fac_order
+    std::vector<int32_t> need(ns, 0);   // scatters into J still to come
     for (int J : S.fac_order) {
       if (pfirst[J] < 0) continue;
-      std::vector<FOp>& ops = lane[S.sel_stream[J]];
-      const size_t n0 = ops.size();
-      auto add = [&](std::vector<FOp>& v, int32_t kind, const PanelK& k, int32_t rows, double w, double b, double s) {
-        FOp o;
-        o.kind = kind;
-        o.J = J;
-        o.first = &v == &ops && v.size() == n0;
-        o.last = false;
-        o.it.c = c;
-        o.it.p = k;
-        o.it.start = 0;
-        o.it.tiles = 0;
-        o.it.nsh = nshift;
-        o.rows = rows;
-        o.work = w;
-        o.bytes = b;
-        o.stored = s;
-        v.push_back(o);
-      };
+      order.push_back(J);
+      for (int64_t t = S.tgt_ptr[J]; t < S.tgt_ptr[J + 1]; ++t) ++need[S.tgt[t]];
       for (int ip = pfirst[J]; ip <= plast[J]; ++ip) {
         const PanelK k = panel_args(S, S.panels[ip]);
         const PanelMacs& xm = S.xm_panel[ip];
         if (k.p0 > 0) {
           const int nrows = k.ld - k.p0;
-          add(ops, FK_INT, k, nrows, fm * nshift * xm.intu,
-              eb * nshift * ((double)nrows * k.p0 + 2.0 * nrows * k.wp),
-              fm * nshift * ((double)nrows * k.wp - 0.5 * k.wp * (k.wp - 1)) * k.p0);
+          ops[J].push_back(FOp{FK_INT, nrows, k, fm * nshift * xm.intu,
+                               eb * nshift * ((double)nrows * k.p0 + 2.0 * nrows * k.wp),
+                               fm * nshift * ((double)nrows * k.wp - 0.5 * k.wp * (k.wp - 1)) * k.p0});
         }
-        add(ops, FK_DIAG, k, 1, fm * nshift * xm.diag, eb * nshift * (double)k.wp * (k.wp + 1),
-            fm * nshift * (double)k.wp * k.wp * k.wp / 3.0);
-        if (k.nb > 0)
-          add(ops, FK_TRSM, k, k.nb, fm * nshift * xm.trsm,
-              eb * nshift * (2.0 * k.nb * k.wp + 0.5 * k.wp * (k.wp + 1)),
-              fm * nshift * (double)k.nb * k.wp * (k.wp + 1) / 2.0);
+        const double rows = k.nb <= SMALL_ROWS ? k.nb : 0.0;   // rows below done along
+        ops[J].push_back(FOp{FK_DIAG, 0, k, fm * nshift * (xm.diag + (rows > 0.0 ? xm.trsm : 0.0)),
+                             eb * nshift * ((double)k.wp * (k.wp + 1) + 2.0 * rows * k.wp),
+                             fm * nshift * ((double)k.wp * k.wp * k.wp / 3.0 + rows * k.wp * (k.wp + 1) / 2.0)});
+        if (k.nb > SMALL_ROWS)
+          ops[J].push_back(FOp{FK_TRSM, k.nb, k, fm * nshift * xm.trsm,
+                               eb * nshift * (2.0 * k.nb * k.wp + 0.5 * k.wp * (k.wp + 1)),
+                               fm * nshift * (double)k.nb * k.wp * (k.wp + 1) / 2.0});
       }
-      ops.back().last = true;
-      if (S.sparent[J] >= 0) add(lane[NS], FK_UPD, panel_args(S, S.panels[plast[J]]), 0, 0.0, 0.0, 0.0);
     }
-    std::vector<int64_t> pdone(ns, -1), sdone(ns, -1);   // launch of J's last panel op / scatter
-    std::vector<size_t> pos(NS + 1, 0);
+    std::vector<size_t> pos(ns, 0);
+    std::vector<uint8_t> scattered(ns, 0);
+    std::vector<int64_t> mark(ns, -1);   // the launch whose scatters already claim this target
+    size_t first = 0;                    // order[0 .. first) is finished
     int64_t nl = 0;
-    auto ready = [&](int q) {
-      if (pos[q] >= lane[q].size()) return false;
-      const FOp& o = lane[q][pos[q]];
-      if (q == NS) return pdone[o.J] >= 0 && pdone[o.J] < nl;
-      if (!o.first) return true;
-      const int ch = S.fac_child[o.J];
-      return ch < 0 || (sdone[ch] >= 0 && sdone[ch] < nl);
-    };
-    for (;;) {
-      int lead = -1;
-      size_t most = 0;
-      for (int q = 0; q <= NS; ++q) {
-        if (!ready(q)) continue;
-        const size_t left = lane[q].size() - pos[q];
-        if (left > most) {
-          most = left;
-          lead = q;
-        }
+    std::vector<int32_t> take;
+    std::vector<LaneItem> items;
+    bool ok = true;
+    for (;; ++nl) {
+      while (first < order.size() && scattered[order[first]]) ++first;
+      if (first == order.size()) break;
+      int cnt[FK_KINDS] = {0, 0, 0, 0};
+      for (size_t i = first; i < order.size(); ++i) {
+        const int J = order[i];
+        if (need[J] == 0 && pos[J] < ops[J].size()) ++cnt[ops[J][pos[J]].kind];
       }
-      if (lead < 0) break;
-      const int32_t kind = lane[lead][pos[lead]].kind;
-      if (kind == FK_UPD) {
-        const FOp& o = lane[NS][pos[NS]];
-        if ((err = scatter(S.panels[plast[o.J]], st))) return err;
-        sdone[o.J] = nl++;
-        ++pos[NS];
-        continue;
-      }
-      LaneGroup grp;
-      grp.n = 0;
-      int64_t start = 0;
-      double w = 0.0, b = 0.0, s = 0.0;
+      const int kind = (int)(std::max_element(cnt, cnt + FK_UPD) - cnt);
+      take.clear();
+      items.clear();
       int m = 0;
-      for (int q = 0; q < NS; ++q)
-        if (ready(q) && lane[q][pos[q]].kind == kind) m = std::max(m, lane[q][pos[q]].it.p.wp);
-      const int tn = !CPLX ? TR : pick_tile(m, [&](int tq) {
-        int64_t n = 0;
-        for (int q = 0; q < NS; ++q)
-          if (ready(q) && lane[q][pos[q]].kind == kind) n += (int64_t)tiles_of(lane[q][pos[q]].rows, tq) * nshift;
-        return n;
-      });
-      for (int q = 0; q < NS; ++q) {
-        if (!ready(q) || lane[q][pos[q]].kind != kind) continue;
-        const FOp& o = lane[q][pos[q]];
-        GroupItem it = o.it;
-        it.tiles = kind == FK_DIAG ? 1 : tiles_of(o.rows, tn);
-        it.start = start;
-        start += (int64_t)it.tiles * it.nsh;
-        grp.it[grp.n++] = it;
-        w += o.work;
-        b += o.bytes;
-        s += o.stored;
-        if (o.last) pdone[o.J] = nl;
-        ++pos[q];
-      }
-      if (start > (int64_t)INT32_MAX) return (int)hipErrorInvalidConfiguration;
-      const dim3 grid((unsigned)start);
-      if (kind == FK_INT) {
+      double w = 0.0, b = 0.0, s = 0.0;
+      if (cnt[kind] > 0) {
+        for (size_t i = first; i < order.size() && (int)take.size() < MAX_ITEMS; ++i) {
+          const int J = order[i];
+          if (need[J] != 0 || pos[J] >= ops[J].size() || ops[J][pos[J]].kind != kind) continue;
+          take.push_back(J);
+          m = std::max(m, ops[J][pos[J]].p.wp);
+        }
+        auto rows = [&](int J) { return ops[J][pos[J]].rows; };
+        const int tn = !CPLX ? TR : pick_tile(m, [&](int tq) {
+          int64_t n = 0;
+          for (int J : take) n += (int64_t)tiles_of(rows(J), tq) * nshift;
+          return n;
+        });
+        for (size_t q = 0; q < take.size(); ++q) {
+          const int J = take[q];
+          const FOp& o = ops[J][pos[J]];
+          items.push_back(LaneItem{o.p, c.wfix, c.G, c.gstride, kind == FK_DIAG ? 1 : tiles_of(o.rows, tn)});
+          w += o.work;
+          b += o.bytes;
+          s += o.stored;
+          // a root has no scatter: it is finished with its last operation
+          if (++pos[J] == ops[J].size() && S.tgt_ptr[J] == S.tgt_ptr[J + 1]) scattered[J] = 1;
+        }
+        if (kind == FK_INT) {
+          ProfScope ps(KC_UPDATE, st, w, b, s);
+          with_tile_of<CPLX>(tn, [&](auto t) {
+            constexpr int TN = decltype(t)::value;
+            ok = with_group(c, items, nshift, [&](const auto& g, dim3 grid) {
+              hipLaunchKernelGGL((k_int_update<CPLX, TN, std::decay_t<decltype(g)>>), grid, dim3(NT), 0, st, g);
+            });
+          });
+        } else if (kind == FK_DIAG) {
+          ProfScope ps(KC_DIAG, st, w, b, s);
+          ok = with_group(c, items, nshift, [&](const auto& g, dim3 grid) {
+            hipLaunchKernelGGL((k_diag<CPLX, std::decay_t<decltype(g)>>), grid, dim3(NTD), 0, st, g);
+          });
+        } else {
+          ProfScope ps(KC_TRSM, st, w, b, s);
+          with_tile_of<CPLX>(tn, [&](auto t) {
+            constexpr int TN = decltype(t)::value;
+            ok = with_group(c, items, nshift, [&](const auto& g, dim3 grid) {
+              hipLaunchKernelGGL((k_trsm<CPLX, TN, std::decay_t<decltype(g)>>), grid, dim3(NT), 0, st, g);
+            });
+          });
+        }
+      } else {
+        for (size_t i = first; i < order.size() && (int)take.size() < MAX_ITEMS; ++i) {
+          const int J = order[i];
+          if (scattered[J]) continue;
+          bool may = need[J] == 0 && pos[J] == ops[J].size();
+          for (int64_t t = S.tgt_ptr[J]; t < S.tgt_ptr[J + 1]; ++t) {
+            may = may && mark[S.tgt[t]] != nl;
+            mark[S.tgt[t]] = nl;
+          }
+          if (may) take.push_back(J);
+        }
+        if (take.empty()) return (int)hipErrorUnknown;   // unreachable: the first unscattered supernode is ready
+        auto below = [&](int J) { return S.ld[J] - (S.sfirst[J + 1] - S.sfirst[J]); };
+        for (int J : take) m = std::max(m, below(J));
+        const int tn = !CPLX ? TR : pick_tile(m, [&](int tq) {
+          int64_t n = 0;
+          for (int J : take) n += update_tiles(below(J), tq) * nshift;
+          return n;
+        });
+        for (size_t q = 0; q < take.size(); ++q) {
+          const int J = take[q];
+          items.push_back(LaneItem{panel_args(S, S.panels[plast[J]]), c.wfix, c.G, c.gstride, 0});
+          LaneItem& it = items.back();
+          PanelK& u = it.p;
+          const int32_t wj = S.sfirst[J + 1] - S.sfirst[J], bl = below(J);
+          u.p0 = 0;
+          u.wp = wj;
+          u.nb = bl;
+          it.tiles = tiles_of(bl, TM) * tiles_of(bl, tn);
+          w += fm * nshift * S.xm_update[J];
+          b += eb * nshift * ((double)bl * wj + (double)bl * (bl + 1));
+          s += fm * nshift * (double)bl * (bl + 1) / 2.0 * wj;
+          scattered[J] = 1;
+          for (int64_t t = S.tgt_ptr[J]; t < S.tgt_ptr[J + 1]; ++t) --need[S.tgt[t]];
+        }
         ProfScope ps(KC_UPDATE, st, w, b, s);
         with_tile_of<CPLX>(tn, [&](auto t) {
-          hipLaunchKernelGGL((k_int_update<CPLX, decltype(t)::value, LaneGroup>), grid, dim3(NT), 0, st, grp);
-        });
-      } else if (kind == FK_DIAG) {
-        ProfScope ps(KC_DIAG, st, w, b, s);
-        hipLaunchKernelGGL((k_diag<CPLX, LaneGroup>), grid, dim3(NTD), 0, st, grp);
-      } else {
-        ProfScope ps(KC_TRSM, st, w, b, s);
-        with_tile_of<CPLX>(tn, [&](auto t) {
-          hipLaunchKernelGGL((k_trsm<CPLX, decltype(t)::value, LaneGroup>), grid, dim3(NT), 0, st, grp);
+          constexpr int TN = decltype(t)::value;
+          ok = with_group(c, items, nshift, [&](const auto& g, dim3 grid) {
+            hipLaunchKernelGGL((k_update<CPLX, TN, std::decay_t<decltype(g)>>), grid, dim3(NT), 0, st, g);
+          });
         });
       }
+      if (!ok) return (int)hipErrorInvalidConfiguration;
       PXS_CHECK_LAUNCH();
-      ++nl;
     }
-    for (int q = 0; q <= NS; ++q)
-      if (pos[q] != lane[q].size()) return (int)hipErrorUnknown;   // unreachable: some lane is always ready
     return 0;
   }
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -2519,65 +2793,65 @@ int selinv_event_count(const Symbolic& S) { return S.nsuper + S.sel_nstreams + 1
 
 namespace {
 
-// Selected inversion with the subtree lanes fused (fused_lanes).  The
-// supernodes keep the lanes of the stream assignment (sel_stream) and each
-// lane its own workspace regions, as on separate streams; the operations of
-// a lane (per supernode from the root down: the Z_CC gather, then per panel
-// from the last: L-hat, off-diagonal product, diagonal partials, diagonal
-// final) run in their order.  Every launch on the caller's stream takes the
-// next operation of each lane whose next operation is of one kind and ready
-// -- the first operation of a supernode whose parent is on another lane
-// waits until the parent's last operation was in an earlier launch -- and
-// runs them as one grid (LaneGroup); the kind is that of the ready lane with
-// the most operations left.  Some lane is always ready: the one whose next
-// supernode is the highest-numbered, since its parent (a higher number) is
-// already done.  Each panel operation computes what it computes on a stream
-// of its own, so the results are the bits of the other paths.
-enum LaneKind : int32_t { LK_GATHER, LK_LHAT, LK_OFF, LK_DPART, LK_DFIN };
+// Selected inversion in fused launches (fused_lanes).  The operations of a
+// supernode run in their order (per panel from the last: one operation for a
+// panel of at most SMALL_ROWS rows below; for the others, after the Z_CC gather
+// of the supernode, L-hat, off-diagonal product, diagonal partials, diagonal
+// final); a launch on the caller's stream takes the next operation of up to
+// MAX_ITEMS supernodes whose parent was finished by an earlier launch, of the
+// kind that most of them wait for.  Operations that use the workspace take the
+// region of the supernode's stream (sel_stream), which one supernode holds at a
+// time.  Each panel operation computes what it computes on a stream of its own,
+// so the results are the bits of the other paths.
+enum LaneKind : int32_t { LK_GATHER, LK_LHAT, LK_OFF, LK_DPART, LK_DFIN, LK_SMALL, LK_SMALL16, LK_KINDS };
 
 struct LaneOp {
   int32_t kind;
-  int32_t J;
-  bool first;   // first operation of supernode J
-  bool last;    // last operation of J
-  int32_t rows; // rows of an L-hat or off-diagonal product (its tiles follow from the launch's tile width), else 0
-  GroupItem it;
+  int32_t rows;    // rows of an L-hat or off-diagonal product (its tiles follow from the launch's tile width), else 0
+  int32_t tiles;   // workgroups per shift of the other kinds
+  PanelK p;
   double work, bytes, stored;   // profile figures (ProfScope)
 };
 
-int lane_launch(int32_t kind, int tn, const LaneGroup& g, int64_t blocks, hipStream_t st) {
-  const dim3 grid((unsigned)blocks);
+int lane_launch(int32_t kind, int tn, const Common& c, const std::vector<LaneItem>& items, int nsh, hipStream_t st) {
+  bool ok = false;
+  auto tiled = [&](auto launch) {   // launch(tile width, group, grid)
+    with_tile(tn, [&](auto t) { ok = with_group(c, items, nsh, [&](const auto& g, dim3 grid) { launch(t, g, grid); }); });
+  };
+#define PXS_LANE_TILED(kernel)                                                                                  \
+  tiled([&](auto t, const auto& g, dim3 grid) {                                                                 \
+    hipLaunchKernelGGL((kernel<decltype(t)::value, std::decay_t<decltype(g)>>), grid, dim3(NT), 0, st, g);      \
+  })
+#define PXS_LANE(threads, ...)                                                                                  \
+  ok = with_group(c, items, nsh, [&](const auto& g, dim3 grid) {                                                \
+    hipLaunchKernelGGL((__VA_ARGS__ std::decay_t<decltype(g)>>), grid, dim3(threads), 0, st, g);                \
+  })
   switch (kind) {
-    case LK_GATHER: hipLaunchKernelGGL(k_gather_cc<LaneGroup>, grid, dim3(NT), 0, st, g); break;
-    case LK_LHAT:
-      with_tile(tn, [&](auto t) { hipLaunchKernelGGL((k_lhat<decltype(t)::value, LaneGroup>), grid, dim3(NT), 0, st, g); });
-      break;
-    case LK_OFF:
-      with_tile(tn, [&](auto t) {
-        hipLaunchKernelGGL((k_selinv_off<decltype(t)::value, LaneGroup>), grid, dim3(NT), 0, st, g);
-      });
-      break;
-    case LK_DPART:
-      with_tile(tn, [&](auto t) {
-        hipLaunchKernelGGL((k_selinv_diag_partial<decltype(t)::value, LaneGroup>), grid, dim3(NT), 0, st, g);
-      });
-      break;
-    case LK_DFIN: hipLaunchKernelGGL(k_selinv_diag_final<LaneGroup>, grid, dim3(NTF), 0, st, g); break;
+    case LK_GATHER: PXS_LANE(NT, k_gather_cc<); break;
+    case LK_LHAT: PXS_LANE_TILED(k_lhat); break;
+    case LK_OFF: PXS_LANE_TILED(k_selinv_off); break;
+    case LK_DPART: PXS_LANE_TILED(k_selinv_diag_partial); break;
+    case LK_DFIN: PXS_LANE(NTF, k_selinv_diag_final<); break;
+    case LK_SMALL: PXS_LANE(NT, k_selinv_small<SMALL_ROWS,); break;
+    case LK_SMALL16: PXS_LANE(NT, k_selinv_small<16,); break;
     default: return (int)hipErrorInvalidValue;
   }
+#undef PXS_LANE
+#undef PXS_LANE_TILED
   PXS_CHECK_LAUNCH();
-  return 0;
+  return ok ? 0 : (int)hipErrorInvalidConfiguration;
 }
 
-const int kLaneClass[5] = {KC_GATHER, KC_LHAT, KC_SELINV_OFF, KC_SELINV_DIAG, KC_NONE};
+const int kLaneClass[LK_KINDS] = {KC_GATHER, KC_LHAT, KC_SELINV_OFF, KC_SELINV_DIAG, KC_NONE, KC_SELINV_OFF,
+                                  KC_SELINV_OFF};
 
 int run_selinv_lanes(const Symbolic& S, int nshift, void* L, void* work, hipStream_t st) {
   const int NL = S.sel_nstreams;
-  if (NL < 1 || NL > MAX_LANES) return (int)hipErrorInvalidValue;
   const int ns = S.nsuper;
   const int chunk = (S.selinv_chunk > 0 && S.selinv_chunk < nshift) ? S.selinv_chunk : nshift;
   // workspace views as on NL streams (selinv_work_bytes)
-  std::vector<Common> cs(NL, make_common(S, L, work));
+  const Common c0 = make_common(S, L, work);
+  std::vector<Common> cs(NL, c0);
   int64_t gofs = S.work_fixed + (int64_t)nshift * NL * S.work_per_shift;
   for (int q = 0; q < NL; ++q) {
     cs[q].wfix = S.work_fixed + (int64_t)q * nshift * S.work_per_shift;
@@ -2587,122 +2861,113 @@ int run_selinv_lanes(const Symbolic& S, int nshift, void* L, void* work, hipStre
   }
   std::vector<int> pfirst(ns, 0);
   for (int ip = (int)S.panels.size() - 1; ip >= 0; --ip) pfirst[S.panels[ip].J] = ip;
-  std::vector<std::vector<LaneOp>> lane(NL);
-  std::vector<int64_t> done(ns);   // launch of J's last operation, -1 before it
+  std::vector<std::vector<LaneOp>> ops(ns);
+  std::vector<size_t> pos(ns);
+  std::vector<int32_t> holder(NL), ready, next, take;
+  std::vector<LaneItem> items;
+  std::vector<std::vector<int32_t>> kids(ns);
+  for (int J = ns - 1; J >= 0; --J)
+    if (S.sparent[J] >= 0) kids[S.sparent[J]].push_back(J);
   for (int sh0 = 0; sh0 < nshift; sh0 += chunk) {
     const int nsh = std::min(chunk, nshift - sh0);
-    for (auto& v : lane) v.clear();
-    for (int J = ns - 1; J >= 0; --J) {
-      const int q = S.sel_stream[J];
-      std::vector<LaneOp>& ops = lane[q];
-      const size_t n0 = ops.size();
+    for (int J = 0; J < ns; ++J) {
+      ops[J].clear();
+      pos[J] = 0;
       auto add = [&](int32_t kind, const PanelK& k, int64_t tiles, double w, double b, double s) {
-        LaneOp o;
-        o.kind = kind;
-        o.J = J;
-        o.first = ops.size() == n0;
-        o.last = false;
-        o.it.c = cs[q];
-        o.it.p = k;
-        o.it.start = 0;
-        o.it.tiles = (int32_t)tiles;
-        o.it.nsh = nsh;
-        o.rows = (kind == LK_LHAT || kind == LK_OFF) ? k.nb : 0;
-        o.work = w;
-        o.bytes = b;
-        o.stored = s;
-        ops.push_back(o);
+        ops[J].push_back(LaneOp{kind, (kind == LK_LHAT || kind == LK_OFF) ? k.nb : 0, (int32_t)tiles, k, w, b, s});
       };
       const int first = pfirst[J];
       int last = first;
       while (last + 1 < (int)S.panels.size() && S.panels[last + 1].J == J) ++last;
-      PanelK g = panel_args(S, S.panels[last]);
-      g.sh0 = sh0;
-      if (g.c > 0) {
-        const int64_t nt = (g.c + TM - 1) / TM;
-        const double gb = (32.0 * nsh + 4.0) * 0.5 * g.c * (g.c + 1);
-        add(LK_GATHER, g, nt * (nt + 1) / 2, gb, gb, gb);
-      }
+      bool gathered = false;
       for (int ip = last; ip >= first; --ip) {
         PanelK k = panel_args(S, S.panels[ip]);
         k.sh0 = sh0;
         const PanelMacs& xm = S.xm_panel[ip];
-        if (k.nb > 0) {
-          add(LK_LHAT, k, 0, 0.0, 16.0 * nsh * (2.0 * k.nb * k.wp + 0.5 * k.wp * (k.wp + 1)),
-              8.0 * nsh * (double)k.nb * k.wp * (k.wp + 1) / 2.0);
-          add(LK_OFF, k, 0, 8.0 * nsh * xm.off, 16.0 * nsh * (0.5 * k.nb * (k.nb + 1) + 2.0 * k.nb * k.wp),
-              8.0 * nsh * (double)k.nb * k.nb * k.wp);
-          add(LK_DPART, k, k.split, 8.0 * nsh * xm.sdiag, 16.0 * nsh * (2.0 * k.nb * k.wp + (double)k.wp * k.wp),
-              8.0 * nsh * (double)k.nb * k.wp * k.wp);
+        if (k.nb <= SMALL_ROWS) {
+          add(k.nb <= 16 ? LK_SMALL16 : LK_SMALL, k, 1, 8.0 * nsh * (xm.off + xm.sdiag),
+              16.0 * nsh * (0.5 * k.nb * (k.nb + 1) + 2.0 * k.nb * k.wp + (double)k.wp * k.wp),
+              8.0 * nsh * ((double)k.nb * k.nb * k.wp + (double)k.nb * k.wp * k.wp));
+          continue;
         }
+        if (k.c > 0 && !gathered) {
+          gathered = true;
+          const int64_t nt = (k.c + TM - 1) / TM;
+          const double gb = (32.0 * nsh + 4.0) * 0.5 * k.c * (k.c + 1);
+          add(LK_GATHER, k, nt * (nt + 1) / 2, gb, gb, gb);
+        }
+        add(LK_LHAT, k, 0, 0.0, 16.0 * nsh * (2.0 * k.nb * k.wp + 0.5 * k.wp * (k.wp + 1)),
+            8.0 * nsh * (double)k.nb * k.wp * (k.wp + 1) / 2.0);
+        add(LK_OFF, k, 0, 8.0 * nsh * xm.off, 16.0 * nsh * (0.5 * k.nb * (k.nb + 1) + 2.0 * k.nb * k.wp),
+            8.0 * nsh * (double)k.nb * k.nb * k.wp);
+        add(LK_DPART, k, k.split, 8.0 * nsh * xm.sdiag, 16.0 * nsh * (2.0 * k.nb * k.wp + (double)k.wp * k.wp),
+            8.0 * nsh * (double)k.nb * k.wp * k.wp);
         add(LK_DFIN, k, 1, 0.0, 0.0, 0.0);
       }
-      ops.back().last = true;
     }
-    std::fill(done.begin(), done.end(), (int64_t)-1);
-    std::vector<size_t> pos(NL, 0);
-    int64_t nl = 0;   // launches of this chunk so far
-    auto ready = [&](int q) {
-      if (pos[q] >= lane[q].size()) return false;
-      const LaneOp& o = lane[q][pos[q]];
-      if (!o.first) return true;
-      const int P = S.sparent[o.J];
-      return P < 0 || S.sel_stream[P] == q || (done[P] >= 0 && done[P] < nl);
-    };
-    for (;;) {
-      int lead = -1;
-      size_t most = 0;
-      for (int q = 0; q < NL; ++q) {
-        if (!ready(q)) continue;
-        const size_t left = lane[q].size() - pos[q];
-        if (left > most) {
-          most = left;
-          lead = q;
+    std::fill(holder.begin(), holder.end(), -1);
+    ready.clear();   // supernodes whose parent is finished, themselves not
+    for (int J = ns - 1; J >= 0; --J)
+      if (S.sparent[J] < 0) ready.push_back(J);
+    while (!ready.empty()) {
+      // may J's next operation run (one that uses the workspace needs the
+      // region of its stream, or holds it already)
+      auto runs = [&](int J) {
+        const int h = holder[S.sel_stream[J]];
+        return ops[J][pos[J]].kind >= LK_SMALL || h < 0 || h == J;
+      };
+      int cnt[LK_KINDS] = {};
+      for (int J : ready)
+        if (runs(J)) ++cnt[ops[J][pos[J]].kind];
+      const int kind = (int)(std::max_element(cnt, cnt + LK_KINDS) - cnt);
+      if (cnt[kind] == 0) return (int)hipErrorUnknown;   // unreachable: a region's holder can always go on
+      take.clear();
+      next.clear();
+      int m = 0;
+      for (int J : ready) {
+        if ((int)take.size() < MAX_ITEMS && ops[J][pos[J]].kind == kind && runs(J)) {
+          take.push_back(J);
+          m = std::max(m, ops[J][pos[J]].p.wp);
+          if (kind < LK_SMALL) holder[S.sel_stream[J]] = J;
+        } else {
+          next.push_back(J);
         }
       }
-      if (lead < 0) break;
-      const int32_t kind = lane[lead][pos[lead]].kind;
-      LaneGroup grp;
-      grp.n = 0;
-      int64_t start = 0;
-      double w = 0.0, b = 0.0, s = 0.0;
-      int m = 0;
-      for (int q = 0; q < NL; ++q)
-        if (ready(q) && lane[q][pos[q]].kind == kind) m = std::max(m, lane[q][pos[q]].it.p.wp);
+      auto tiles = [&](int J, int tn) {
+        const LaneOp& o = ops[J][pos[J]];
+        return o.rows > 0 ? tiles_of(o.rows, tn) : kind == LK_DPART ? o.tiles * tiles_of(o.p.wp, tn) : o.tiles;
+      };
       const int tn = pick_tile(m, [&](int tq) {
         int64_t n = 0;
-        for (int q = 0; q < NL; ++q) {
-          if (!ready(q) || lane[q][pos[q]].kind != kind) continue;
-          const LaneOp& o = lane[q][pos[q]];
-          n += (int64_t)(kind == LK_DPART ? o.it.p.split * tiles_of(o.it.p.wp, tq) : tiles_of(o.rows, tq)) * nsh;
-        }
+        for (int J : take) n += (int64_t)tiles(J, tq) * nsh;
         return n;
       });
-      for (int q = 0; q < NL; ++q) {
-        if (!ready(q) || lane[q][pos[q]].kind != kind) continue;
-        const LaneOp& o = lane[q][pos[q]];
-        GroupItem it = o.it;
-        if (o.rows > 0) it.tiles = tiles_of(o.rows, tn);
-        if (kind == LK_DPART) it.tiles = it.p.split * tiles_of(it.p.wp, tn);
-        it.start = start;
-        start += (int64_t)it.tiles * it.nsh;
-        grp.it[grp.n++] = it;
+      items.clear();
+      double w = 0.0, b = 0.0, s = 0.0;
+      for (size_t q = 0; q < take.size(); ++q) {
+        const int J = take[q];
+        const LaneOp& o = ops[J][pos[J]];
+        const Common& cq = cs[S.sel_stream[J]];
+        items.push_back(LaneItem{o.p, cq.wfix, cq.G, cq.gstride, tiles(J, tn)});
         w += o.work;
         b += o.bytes;
         s += o.stored;
-        if (o.last) done[o.J] = nl;
-        ++pos[q];
       }
-      if (start > (int64_t)INT32_MAX) return (int)hipErrorInvalidConfiguration;
+      for (int J : take) {
+        ++pos[J];
+        bool ws = false;   // workspace operations left
+        for (size_t i = pos[J]; i < ops[J].size(); ++i) ws = ws || ops[J][i].kind < LK_SMALL;
+        if (!ws && holder[S.sel_stream[J]] == J) holder[S.sel_stream[J]] = -1;
+        if (pos[J] < ops[J].size()) next.push_back(J);
+        else next.insert(next.end(), kids[J].begin(), kids[J].end());
+      }
       {
         ProfScope ps(kLaneClass[kind], st, w, b, s);
-        const int e = lane_launch(kind, tn, grp, start, st);
+        const int e = lane_launch(kind, tn, c0, items, nsh, st);
         if (e) return e;
       }
-      ++nl;
+      ready.swap(next);
     }
-    for (int q = 0; q < NL; ++q)
-      if (pos[q] != lane[q].size()) return (int)hipErrorUnknown;   // unreachable: some lane is always ready
   }
   return 0;
 }
@@ -2769,7 +3034,8 @@ int run_selinv(const Symbolic& S, int nshift, void* L, void* work, hipStream_t s
       while (last + 1 < (int)S.panels.size() && S.panels[last + 1].J == J) ++last;
       PanelK g = panel_args(S, S.panels[last]);
       g.sh0 = sh0;
-      if (g.c > 0) {
+      // (the first panel has the most rows below: Z_CC is gathered if any has too many)
+      if (g.c > 0 && S.panels[first].nb_rows > SMALL_ROWS) {
         const int nt = (g.c + TM - 1) / TM;
         // bytes: the lower triangle of Z_CC read from the ancestors and written to G, relative positions
         const double gb = (32.0 * nsh + 4.0) * 0.5 * g.c * (g.c + 1);
@@ -2780,6 +3046,15 @@ int run_selinv(const Symbolic& S, int nshift, void* L, void* work, hipStream_t s
         PanelK k = panel_args(S, S.panels[ip]);
         k.sh0 = sh0;
         const PanelMacs& xm = S.xm_panel[ip];
+        if (k.nb <= SMALL_ROWS) {
+          ProfScope ps(KC_SELINV_OFF, sj, 8.0 * nsh * (xm.off + xm.sdiag),
+                       16.0 * nsh * (0.5 * k.nb * (k.nb + 1) + 2.0 * k.nb * k.wp + (double)k.wp * k.wp),
+                       8.0 * nsh * ((double)k.nb * k.nb * k.wp + (double)k.nb * k.wp * k.wp));
+          if (k.nb <= 16) hipLaunchKernelGGL((k_selinv_small<16, OnePanel>), dim3(1, nsh), dim3(NT), 0, sj, OnePanel{c, k});
+          else hipLaunchKernelGGL((k_selinv_small<SMALL_ROWS, OnePanel>), dim3(1, nsh), dim3(NT), 0, sj, OnePanel{c, k});
+          PXS_CHECK_LAUNCH();
+          continue;
+        }
         if (k.nb > 0) {
           const int tn = pick_tile(k.wp, [&](int q2) { return (int64_t)tiles_of(k.nb, q2) * nsh; });
           {

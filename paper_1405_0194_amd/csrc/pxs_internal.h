@@ -115,12 +115,17 @@ struct Symbolic {
   int32_t max_below_super = 0;      // max over supernodes of ld - w
 
   // Factorization with the same subtree streams: supernodes are issued by
-  // height in the supernodal tree (leaves first, column order within a
-  // height), the panel work of J on stream sel_stream[J], every ancestor
+  // height in the supernodal tree (leaves first; within a height by the
+  // color that keeps scatters with a common target apart, then column
+  // order), the panel work of J on stream sel_stream[J], every ancestor
   // scatter on the caller's stream in that order.  fac_child[J] is the child
   // of J issued last (-1 for a leaf): its scatter ends the scatters into J.
   std::vector<int32_t> fac_order;
   std::vector<int32_t> fac_child;
+  // The supernodes that own J's rows below it, tgt[tgt_ptr[J] .. tgt_ptr[J + 1]):
+  // those its scatter writes to.
+  std::vector<int64_t> tgt_ptr;
+  std::vector<int32_t> tgt;
 };
 
 struct AnalyzeOptions {

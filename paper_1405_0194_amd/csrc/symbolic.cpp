@@ -698,15 +698,48 @@ int analyze(int32_t n, const int64_t* colptr, const int32_t* rowind, int32_t nbl
       g = std::max(g, (16 * c * c + 255) / 256 * 256);
     }
   }
+  // targets of every ancestor scatter (rows below are sorted, so owners are too)
+  S.tgt_ptr.assign((size_t)ns + 1, 0);
+  S.tgt.clear();
+  for (int32_t J = 0; J < ns; ++J) {
+    for (int64_t i = S.rowptr[J] + (S.sfirst[J + 1] - S.sfirst[J]); i < S.rowptr[J + 1]; ++i) {
+      const int32_t o = S.snode_of_col[S.rows[i]];
+      if ((int64_t)S.tgt.size() == S.tgt_ptr[J] || S.tgt.back() != o) S.tgt.push_back(o);
+    }
+    S.tgt_ptr[J + 1] = (int64_t)S.tgt.size();
+  }
   {
     // factorization issue order (children are numbered before parents)
     std::vector<int32_t> height(ns, 0);
     for (int32_t J = 0; J < ns; ++J)
       if (S.sparent[J] >= 0) height[S.sparent[J]] = std::max(height[S.sparent[J]], height[J] + 1);
+    // within a height by color, so that scatters next to each other share no
+    // target (fused launches then take many at once: neighbouring leaves of a
+    // chain share a separator, every other one does not)
+    std::vector<int32_t> color(ns, 0);
+    std::vector<uint64_t> used(ns, 0);
+    std::vector<int32_t> used_at(ns, -1);   // the height whose colors used[] holds
     S.fac_order.resize(ns);
     std::iota(S.fac_order.begin(), S.fac_order.end(), 0);
     std::stable_sort(S.fac_order.begin(), S.fac_order.end(),
                      [&](int32_t a, int32_t b) { return height[a] < height[b]; });
+    for (int32_t J : S.fac_order) {
+      uint64_t taken = 0;
+      for (int64_t t = S.tgt_ptr[J]; t < S.tgt_ptr[J + 1]; ++t)
+        if (used_at[S.tgt[t]] == height[J]) taken |= used[S.tgt[t]];
+      int32_t c = 0;
+      while (c < 63 && ((taken >> c) & 1)) ++c;
+      color[J] = c;
+      for (int64_t t = S.tgt_ptr[J]; t < S.tgt_ptr[J + 1]; ++t) {
+        uint64_t& u = used[S.tgt[t]];
+        if (used_at[S.tgt[t]] != height[J]) u = 0;
+        used_at[S.tgt[t]] = height[J];
+        u |= (uint64_t)1 << c;
+      }
+    }
+    std::stable_sort(S.fac_order.begin(), S.fac_order.end(), [&](int32_t a, int32_t b) {
+      return height[a] != height[b] ? height[a] < height[b] : color[a] < color[b];
+    });
     std::vector<int32_t> seq(ns);
     for (int32_t i = 0; i < ns; ++i) seq[S.fac_order[i]] = i;
     S.fac_child.assign(ns, -1);

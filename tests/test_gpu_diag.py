@@ -47,3 +47,33 @@ def test_dense_pencil(n, panel, hermitian):
     eps = np.concatenate([[ev[0] - 0.1, ev[-1] + 0.1], 0.5 * (ev[1:] + ev[:-1])[:6]])
     neg, info = (B.inertia_hermitian if hermitian else B.inertia)(a, Hd, Sd, eps)
     assert np.array_equal(neg, [int(np.sum(ev < e)) for e in eps]) and np.all(info == 0)
+
+
+@pytest.mark.parametrize("dims,orb,akw", [
+    (40, 4, dict(leaf_cols=64)), (33, 3, dict(leaf_cols=20, panel_width=7)), (50, 13, dict(leaf_cols=100)),
+    (30, 13, dict(leaf_cols=128, panel_width=48)), (20, 1, dict(leaf_cols=4)), (25, 17, dict(leaf_cols=64))])
+@pytest.mark.parametrize("fused", [1, -1])
+def test_chains_of_small_supernodes(dims, orb, akw, fused):
+    """Panels with at most 64 rows below (their rows and their selected
+    inverse in one workgroup), and supernodes just over that."""
+    import torch
+    from paper_1405_0194_amd import binding as B
+    from paper_1405_0194_amd import lattice
+    s = lattice.make_system("chain", dims, orb, 2.0, 9)
+    Hd, Sd = s.dense()
+    rng = np.random.default_rng(dims)
+    w = rng.uniform(-0.6, 0.6, 11) + 1j * rng.uniform(0.02, 0.5, 11)
+    print("case: chain", dims, orb, akw, "fused", fused, flush=True)
+    a = B.Analysis.from_system(s, fused_lanes=fused, **akw)
+    H, S = torch.from_numpy(s.hval).cuda(), torch.from_numpy(s.sval).cuda()
+    f = B.Factorization(a, H, S, w)
+    assert np.all(f.info == 0)
+    f.selinv()
+    cols = s.entry_cols()
+    for l in (0, 5, 10):
+        Z = odense.shifted_inverse(Hd, Sd, w[l])
+        assert float(np.max(odense.entry_error(f.selected(l).cpu().numpy(), Z[s.rowind, cols]))) <= TOL
+    ev = np.sort(odense.gen_eigh(Hd, Sd)[0])
+    eps = 0.5 * (ev[1:] + ev[:-1])[:: max(1, len(ev) // 7)]
+    neg, info = B.inertia(a, H, S, eps)
+    assert np.array_equal(neg, [int(np.sum(ev < e)) for e in eps]) and np.all(info == 0)
