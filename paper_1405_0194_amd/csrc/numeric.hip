@@ -400,13 +400,14 @@ __device__ __forceinline__ void commit_rt(double* re, double* im, const cplx (&v
 // on the same XCD and share its L2.  Returns the logical (x, y) of the
 // caller in a grid of nx x ny.
 constexpr int NXCD = 8;
-__device__ __forceinline__ void xcd_remap(int& x, int& y) {
-  const int nx = gridDim.x, ny = gridDim.y;
-  const int total = nx * ny;
-  const int b = blockIdx.x + nx * blockIdx.y;
+__device__ __forceinline__ int xcd_logical(int b, int total) {
   const int xcd = b % NXCD, idx = b / NXCD;
   const int q = total / NXCD, r = total % NXCD;
-  const int logical = (xcd < r) ? xcd * (q + 1) + idx : r * (q + 1) + (xcd - r) * q + idx;
+  return (xcd < r) ? xcd * (q + 1) + idx : r * (q + 1) + (xcd - r) * q + idx;
+}
+__device__ __forceinline__ void xcd_remap(int& x, int& y) {
+  const int nx = gridDim.x, ny = gridDim.y;
+  const int logical = xcd_logical(blockIdx.x + nx * blockIdx.y, nx * ny);
   x = logical % nx;
   y = logical / nx;
 }
@@ -1075,8 +1076,7 @@ __device__ __forceinline__ double* shift_base(const Common& c, int sh) {
 // launch (kernel argument), grid = (tiles, shifts).  PanelGroup: a table of
 // panels of several systems launched as one grid of sum(tiles x shifts)
 // workgroups (the fused execution of a batch of systems); each item's
-// workgroups are a contiguous range of logical ids, so after the XCD-aware
-// remap the tiles of one item share an XCD as in a single launch.
+// workgroups are a contiguous range of ids, with the XCD-aware order inside it.
 struct OnePanel {
   Common c;
   PanelK p;
@@ -1109,6 +1109,7 @@ struct LaneItem {
   double* G;
   int64_t gstride;
   int32_t tiles;     // workgroups per shift
+  int32_t nsh;       // shifts
 };
 template <int N>
 struct LaneGroup {
@@ -1131,9 +1132,11 @@ __device__ __forceinline__ void locate(const OnePanel& src, Common& c, PanelK& p
 }
 
 __device__ __forceinline__ void locate(const PanelGroup& src, Common& c, PanelK& p, int& bx, int& by, bool remap) {
-  int lx = (int)blockIdx.x, ly = 0;
-  if (remap) xcd_remap(lx, ly);   // grid (total, 1): ly stays 0
-  const int64_t lid = lx;
+  // the item by the plain id, the XCD-aware order within it: items differ in
+  // the work of their tiles, and every XCD gets a share of each (a remap over
+  // the whole grid gave whole items to an XCD: a sheet of N=7956 fused took
+  // 236 ms against 214 panel by panel)
+  const int64_t lid = blockIdx.x;
   int lo = 0, hi = src.n - 1;     // the last item starting at or before lid
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
@@ -1143,16 +1146,16 @@ __device__ __forceinline__ void locate(const PanelGroup& src, Common& c, PanelK&
   const GroupItem& it = src.items[lo];
   c = it.c;
   p = it.p;
-  const int64_t local = lid - it.start;
-  bx = (int)(local % it.tiles);
-  by = (int)(local / it.tiles);
+  int local = (int)(lid - it.start);
+  if (remap) local = xcd_logical(local, it.tiles * it.nsh);
+  bx = local % it.tiles;
+  by = local / it.tiles;
 }
 
 template <int N>
 __device__ __forceinline__ void locate(const LaneGroup<N>& src, Common& c, PanelK& p, int& bx, int& by, bool remap) {
-  int lx = (int)blockIdx.x, ly = 0;
-  if (remap) xcd_remap(lx, ly);   // grid (total, 1)
-  int i = -1;                     // the last item starting at or before lx
+  const int lx = (int)blockIdx.x;
+  int i = -1;   // the last item starting at or before lx
 #pragma unroll
   for (int q = 0; q < N; ++q) i += src.start[q] <= lx ? 1 : 0;
   const LaneItem& it = src.it[i];
@@ -1161,7 +1164,8 @@ __device__ __forceinline__ void locate(const LaneGroup<N>& src, Common& c, Panel
   c.G = it.G;
   c.gstride = it.gstride;
   p = it.p;
-  const int local = lx - src.start[i];
+  int local = lx - src.start[i];
+  if (remap) local = xcd_logical(local, it.tiles * it.nsh);   // within the item, as for PanelGroup
   bx = local % it.tiles;
   by = local / it.tiles;
 }
@@ -2040,6 +2044,7 @@ __global__ void __launch_bounds__(NT, ROWS <= 16 ? 2 : 1) k_selinv_small(Src src
 // pole sums, extraction
 // --------------------------------------------------------------------------
 // out[g][k] = sum_l Im(omega_{g,l} Z_l[k]); per-block partial traces.
+constexpr int PS = 8;
 __global__ void __launch_bounds__(NT) k_pole_sum(const double* __restrict__ L, int64_t stride,
                                                  int nshift, const double* __restrict__ wts,
                                                  int nsets, const int64_t* __restrict__ eoff,
@@ -2053,11 +2058,23 @@ __global__ void __launch_bounds__(NT) k_pole_sum(const double* __restrict__ L, i
   for (int64_t k = (int64_t)blockIdx.x * NT + threadIdx.x; k < nnz; k += (int64_t)gridDim.x * NT) {
     const int64_t e = eoff[k];
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int l = 0; l < nshift; ++l) {
-      const double2 z = *reinterpret_cast<const double2*>(L + 2 * (stride * l + e));
-      for (int g = 0; g < nsets; ++g) {
-        const double wr = wts[2 * (g * nshift + l)], wi = wts[2 * (g * nshift + l) + 1];
-        acc[g] += wr * z.y + wi * z.x;
+    // PS poles' values in flight (one at a time, a small system's sum took 40
+    // dependent loads: 23 us for 2,640 entries)
+    for (int l0 = 0; l0 < nshift; l0 += PS) {
+      double2 z[PS];
+#pragma unroll
+      for (int i = 0; i < PS; ++i)
+        z[i] = *reinterpret_cast<const double2*>(L + 2 * (stride * min(l0 + i, nshift - 1) + e));
+#pragma unroll
+      for (int i = 0; i < PS; ++i) {
+        const int l = l0 + i;
+        if (l >= nshift) break;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          if (g >= nsets) break;
+          const double wr = wts[2 * (g * nshift + l)], wi = wts[2 * (g * nshift + l) + 1];
+          acc[g] += wr * z[i].y + wi * z[i].x;
+        }
       }
     }
     const double mult = ediag[k] == 1 ? 1.0 : 2.0;
@@ -2425,6 +2442,7 @@ static bool with_group(const Common& c, const std::vector<LaneItem>& items, int 
       if (q >= (int)items.size()) continue;
       g.start[q] = (int32_t)at;
       g.it[q] = items[q];
+      g.it[q].nsh = nsh;
       at += (int64_t)items[q].tiles * nsh;
     }
   };
@@ -2530,7 +2548,11 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
   // the subtree streams are used or not.  Inside a stream capture, or with
   // one subtree stream, everything runs on the caller's stream.
   int err = 0;
-  if (S.fused_lanes && NS > 1) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  hipError_t he = hipStreamIsCapturing(st, &cap);
+  if (he != hipSuccess) return (int)he;
+  const bool one_stream = cap != hipStreamCaptureStatusNone || inorder;
+  if (NS > 1 && (S.fused_lanes || (S.fuse_one_stream && one_stream))) {
     // Fused launches (no library streams or events, so also on the in-order
     // paths): a launch takes the next panel operation of up to MAX_ITEMS
     // supernodes, of the kind that most of them wait for; a supernode is ready
@@ -2612,7 +2634,7 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
         for (size_t q = 0; q < take.size(); ++q) {
           const int J = take[q];
           const FOp& o = ops[J][pos[J]];
-          items.push_back(LaneItem{o.p, c.wfix, c.G, c.gstride, kind == FK_DIAG ? 1 : tiles_of(o.rows, tn)});
+          items.push_back(LaneItem{o.p, c.wfix, c.G, c.gstride, kind == FK_DIAG ? 1 : tiles_of(o.rows, tn), 0});
           w += o.work;
           b += o.bytes;
           s += o.stored;
@@ -2662,7 +2684,7 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
         });
         for (size_t q = 0; q < take.size(); ++q) {
           const int J = take[q];
-          items.push_back(LaneItem{panel_args(S, S.panels[plast[J]]), c.wfix, c.G, c.gstride, 0});
+          items.push_back(LaneItem{panel_args(S, S.panels[plast[J]]), c.wfix, c.G, c.gstride, 0, 0});
           LaneItem& it = items.back();
           PanelK& u = it.p;
           const int32_t wj = S.sfirst[J + 1] - S.sfirst[J], bl = below(J);
@@ -2689,10 +2711,7 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
     }
     return 0;
   }
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  hipError_t he = hipStreamIsCapturing(st, &cap);
-  if (he != hipSuccess) return (int)he;
-  if (cap != hipStreamCaptureStatusNone || NS <= 1 || inorder) {
+  if (one_stream || NS <= 1) {
     for (int J : S.fac_order) {
       if (pfirst[J] < 0) continue;
       for (int ip = pfirst[J]; ip <= plast[J]; ++ip)
@@ -2948,7 +2967,7 @@ int run_selinv_lanes(const Symbolic& S, int nshift, void* L, void* work, hipStre
         const int J = take[q];
         const LaneOp& o = ops[J][pos[J]];
         const Common& cq = cs[S.sel_stream[J]];
-        items.push_back(LaneItem{o.p, cq.wfix, cq.G, cq.gstride, tiles(J, tn)});
+        items.push_back(LaneItem{o.p, cq.wfix, cq.G, cq.gstride, tiles(J, tn), 0});
         w += o.work;
         b += o.bytes;
         s += o.stored;
@@ -2976,11 +2995,12 @@ int run_selinv_lanes(const Symbolic& S, int nshift, void* L, void* work, hipStre
 
 int run_selinv(const Symbolic& S, int nshift, void* L, void* work, hipStream_t st,
                hipEvent_t* events, bool inorder) {
-  if (S.fused_lanes && !inorder && S.sel_nstreams > 1) return run_selinv_lanes(S, nshift, L, work, st);
   // inside a stream capture everything runs on the capturing stream: the
   // subtree streams are used by eager runs only
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   PXS_HIP(hipStreamIsCapturing(st, &cap));
+  const bool fuse = S.fused_lanes || (S.fuse_one_stream && cap != hipStreamCaptureStatusNone);
+  if (fuse && !inorder && S.sel_nstreams > 1) return run_selinv_lanes(S, nshift, L, work, st);
   const bool single = inorder || (cap != hipStreamCaptureStatusNone) || S.sel_nstreams == 1;
   const int NS = single ? 1 : S.sel_nstreams;
   const int ns = S.nsuper;

@@ -108,7 +108,8 @@ struct Symbolic {
   // when they are on different streams.  Each stream has its own per-shift
   // region (work_per_shift) and dense Z_CC region (gather_bytes[s] per shift).
   int32_t sel_nstreams = 1;
-  int32_t fused_lanes = 0;   // factor panel work and SelInv: the sel_stream lanes fused on one stream
+  int32_t fused_lanes = 0;   // factor and SelInv always in fused launches on one stream
+  int32_t fuse_one_stream = 1;   // fused launches where only one stream may be used (captures, in-order runs)
   std::vector<int32_t> sel_stream;
   std::vector<int64_t> gather_bytes;
   std::vector<uint8_t> cross_child;  // J has a child on another stream

@@ -755,6 +755,11 @@ int analyze(int32_t n, const int64_t* colptr, const int32_t* rowind, int32_t nbl
   // and latency-bound: one fused grid per step halves their density-matrix
   // time, while systems of a few large supernodes run at the same speed or
   // 1-3% slower (measured over 64 chain, sheet and bulk systems)
+  // Where only the caller's stream may be used (stream captures, in-order
+  // runs) the subtree streams are no alternative, and fused launches fill the
+  // chip better than one panel at a time: sheets of N = 2,106 and 7,956 in
+  // graph plans 21.9 -> 21.2 and 215.0 -> 207.5 ms, bulk of N = 7,488 537 -> 534.
+  S.fuse_one_stream = opt.fused_lanes >= 0 ? 1 : 0;
   if (opt.fused_lanes != 0) {
     S.fused_lanes = opt.fused_lanes > 0 ? 1 : 0;
   } else {
