@@ -84,8 +84,7 @@ typedef struct {
                            batch); bounds the dense Z_CC workspace */
   double pivot_tol;     /* |d_k| < pivot_tol * (max|H| + |w| max|S|) flags a
                            tiny pivot (0: 1e-14) */
-  int32_t tile_rows;    /* rows per workgroup tile of the real panel products
-                           (inertia): 64 or 128 (0: 64); the complex ones
+  int32_t tile_rows;    /* 0, 64 or 128, without effect: the panel products
                            pick 64, 32 or 16 by the size of each launch */
   int32_t selinv_streams; /* streams for independent subtrees in selected
                            inversion, 1..8 (0: 4); the library creates them

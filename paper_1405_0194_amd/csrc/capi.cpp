@@ -123,7 +123,6 @@ pxs_status pxs_analyze(int32_t n, const int64_t* colptr, const int32_t* rowind, 
     if (opt->selinv_chunk < 0) return PXS_EINVAL;
     o.selinv_chunk = opt->selinv_chunk;
     if (opt->tile_rows != 0 && opt->tile_rows != 64 && opt->tile_rows != 128) return PXS_EINVAL;
-    if (opt->tile_rows) o.tile_rows = opt->tile_rows;
     if (opt->selinv_streams < 0 || opt->selinv_streams > 8) return PXS_EINVAL;
     if (opt->selinv_streams) o.selinv_streams = opt->selinv_streams;
     if (opt->fused_lanes < -1 || opt->fused_lanes > 1) return PXS_EINVAL;

@@ -46,7 +46,6 @@ typedef double dbl4 __attribute__((ext_vector_type(4)));
 
 constexpr int NT = 256;   // threads per workgroup (4 wave64)
 constexpr int TM = 64;    // tile rows (m) and columns (n)
-constexpr int KC = 16;    // k-chunk staged in LDS
 constexpr int LDP = 65;   // padded LDS row (doubles)
 
 struct cplx {
@@ -78,28 +77,13 @@ __device__ __forceinline__ void st_elem(double* base, int64_t e, cplx v) {
   }
 }
 
-// An operand element, or zero where ok is false: lanes outside the operand
-// read a zero block instead of skipping the load, so every lane issues its
-// load without a branch.  The compiler can then count the loads in flight
-// exactly and the K loop's two-deep prefetch waits only for the older chunk.
+// What operand lanes outside their matrix read through a pointer of their own.
 __device__ __align__(16) double kZeroElem[2] = {0.0, 0.0};   // never written
 
-template <bool CPLX>
-__device__ __forceinline__ cplx ld_or_zero(const double* base, int64_t e, bool ok) {
-  const double* q = ok ? base + (CPLX ? 2 : 1) * e : kZeroElem;
-  if (CPLX) {
-    const double2 v = *reinterpret_cast<const double2*>(q);
-    return {v.x, v.y};
-  }
-  return {*q, 0.0};
-}
-
 // --------------------------------------------------------------------------
-// MFMA tile engine: a 256-thread workgroup accumulates a 64 x NTILE tile
-// P[m][n] = sum_k A[m][k] B[k][n] (NTILE = 64 or 128).  The 4 waves are laid
+// MFMA tiles: a 256-thread workgroup accumulates a 64 x NTILE tile
+// P[m][n] = sum_k A[m][k] B[k][n] (NTILE = 64, 32 or 16).  The 4 waves are laid
 // out WM x WN over the tile, each owning BM x BN blocks of 16 x 16.
-// Operands are staged in LDS as As[k][m], Bs[k][n] (real and imaginary
-// parts split, rows padded by one double).
 // v_mfma_f64_16x16x4f64 lane layout (lane l, 0..63):
 //   A operand: A[l % 16][l / 16];  B operand: B[l / 16][l % 16];
 //   result register r: D[l / 16 + 4 r][l % 16].
@@ -117,8 +101,6 @@ struct Geo {
   static constexpr int WM = 4 / WN;            // waves along m
   static constexpr int BM = TALL ? (NTILE == 64 ? 3 : NTILE == 32 ? 2 : 1) : 64 / WM / 16;   // 16-blocks per wave along m
   static constexpr int BN = TALL || NTILE < 32 ? 1 : 2;    // 16-blocks per wave along n
-  static constexpr int XA = 64 * KC / NT;      // A transfers per thread and chunk
-  static constexpr int XB = NTILE * KC / NT;   // B transfers per thread and chunk
 };
 
 template <bool CPLX, int NTILE, bool TALL = false>
@@ -137,21 +119,6 @@ struct Acc {
   }
 };
 
-template <bool CPLX, int NTILE>
-struct Stage {
-  double a_re[KC][LDP];
-  double a_im[CPLX ? KC : 1][LDP];
-  double b_re[KC][NTILE + 1];
-  double b_im[CPLX ? KC : 1][NTILE + 1];
-  double d_re[KC];                 // per-k scale of the A operand (optional)
-  double d_im[CPLX ? KC : 1];
-};
-
-// No per-k scaling of the A operand.
-struct NoScale {};
-
-// SCALE: A[m][k] is multiplied by the chunk's d_k (staged with the chunk)
-// as it is read for the matrix cores.
 // Row of the 16-row block a (column of the 16-column block b) of wave w:
 // blocks in order, or, with bit 0 (bit 1) of SWZ on a 64 x 64 tile, the
 // first wave row (column) taking blocks {0, 3} and the second {1, 2}, so that
@@ -179,70 +146,6 @@ __device__ __forceinline__ int block_col(int w, int b) {
     return 16 * (b == 0 ? wc : 3 - wc);
   } else {
     return (w % G::WN) * (G::BN * 16) + b * 16;
-  }
-}
-
-// MASK >= 0: only the block pairs (a, b) with bit 2a + b set are multiplied
-// (the others are zero in this chunk, or not needed).
-template <bool CPLX, int NTILE, bool SCALE = false, int MASK = -1, int SWZ = 0>
-__device__ __forceinline__ void mfma_chunk(Acc<CPLX, NTILE>& acc, const Stage<CPLX, NTILE>& s) {
-  using G = Geo<NTILE>;
-  // the compiler's single-wave small-GEMM schedule (interleaves the LDS
-  // operand reads with the MFMAs): 1-2% over the default schedule
-  __builtin_amdgcn_iglp_opt(1);
-  static_assert(MASK < 0 || (G::BM == 2 && G::BN == 2), "block masks need 2 x 2 blocks per wave");
-  const int lane = threadIdx.x & 63;
-  const int w = threadIdx.x >> 6;
-  const int li = lane & 15, lk = lane >> 4;
-  // a row block is read if any of its pairs is live, a column block likewise
-  auto row_live = [](int t) { return MASK < 0 || ((MASK >> (2 * t)) & 3) != 0; };
-  auto col_live = [](int t) { return MASK < 0 || ((MASK >> t) & 5) != 0; };
-  auto live = [](int a, int b) { return MASK < 0 || ((MASK >> (2 * a + b)) & 1) != 0; };
-#pragma unroll
-  for (int ks = 0; ks < KC / 4; ++ks) {
-    const int k = ks * 4 + lk;
-    double ar[G::BM], ai[G::BM], br[G::BN], bi[G::BN];
-#pragma unroll
-    for (int t = 0; t < G::BM; ++t) {
-      if (!row_live(t)) continue;
-      ar[t] = s.a_re[k][block_row<NTILE, SWZ>(w, t) + li];
-      if (CPLX) ai[t] = s.a_im[k][block_row<NTILE, SWZ>(w, t) + li];
-    }
-    if (SCALE) {
-      const double dr = s.d_re[k];
-      if (CPLX) {
-        const double di = s.d_im[k];
-#pragma unroll
-        for (int t = 0; t < G::BM; ++t) {
-          if (!row_live(t)) continue;
-          const cplx v = cmul(cplx{dr, di}, cplx{ar[t], ai[t]});
-          ar[t] = v.re;
-          ai[t] = v.im;
-        }
-      } else {
-#pragma unroll
-        for (int t = 0; t < G::BM; ++t)
-          if (row_live(t)) ar[t] *= dr;
-      }
-    }
-#pragma unroll
-    for (int t = 0; t < G::BN; ++t) {
-      if (!col_live(t)) continue;
-      br[t] = s.b_re[k][block_col<NTILE, SWZ>(w, t) + li];
-      if (CPLX) bi[t] = s.b_im[k][block_col<NTILE, SWZ>(w, t) + li];
-    }
-#pragma unroll
-    for (int a = 0; a < G::BM; ++a)
-#pragma unroll
-      for (int b = 0; b < G::BN; ++b) {
-        if (!live(a, b)) continue;
-        acc.re[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[a], br[b], acc.re[a][b], 0, 0, 0);
-        if (CPLX) {
-          acc.re[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai[a], bi[b], acc.re[a][b], 0, 0, 1);   // -ai bi
-          acc.im[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[a], bi[b], acc.im[a][b], 0, 0, 0);
-          acc.im[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai[a], br[b], acc.im[a][b], 0, 0, 0);
-        }
-      }
   }
 }
 
@@ -291,9 +194,9 @@ __device__ __forceinline__ void acc_at(const Acc<CPLX, NTILE, TALL>& acc, int id
 template <bool CPLX, int NTILE, bool TALL, class AF>
 __device__ __forceinline__ void acc_sub_into(const Acc<CPLX, NTILE, TALL>& acc, double* target, AF addr) {
   constexpr int NE = acc_elems<NTILE, TALL>();
-  // complex: at most 8 elements at a time, so positions and old values fit
+  // at most 8 elements at a time, so positions and old values fit
   // beside the accumulators in the 128 registers of four waves per SIMD
-  constexpr int NH = CPLX && NE > 8 ? (NE % 8 ? 4 : 8) : NE;
+  constexpr int NH = NE > 8 ? (NE % 8 ? 4 : 8) : NE;
 #pragma unroll
   for (int h = 0; h < NE; h += NH) {
     int64_t e[NH];
@@ -320,80 +223,6 @@ __device__ __forceinline__ void acc_sub_into(const Acc<CPLX, NTILE, TALL>& acc, 
   }
 }
 
-// Staging of one k-chunk of an operand with ROWS rows (64 or NTILE).
-// slot(j) gives the (row, k) pair thread t moves in its j-th transfer:
-// FAST_K = false puts consecutive threads on consecutive rows (memory
-// contiguous along the rows), FAST_K = true on consecutive k.  fetch() reads
-// global memory into registers and commit() writes them to LDS, so the next
-// chunk's loads are in flight while the current chunk runs on the matrix
-// cores.
-template <int ROWS, bool FAST_K>
-__device__ __forceinline__ void slot(int j, int& ii, int& kk) {
-  const int t = threadIdx.x;
-  if (!FAST_K) {
-    ii = t % ROWS;
-    kk = t / ROWS + (NT / ROWS) * j;
-  } else {
-    kk = t % KC;
-    ii = t / KC + (NT / KC) * j;
-  }
-}
-
-template <int ROWS, int X, bool FAST_K, class Gt>
-__device__ __forceinline__ void fetch(cplx (&v)[X], int k0, Gt get) {
-#pragma unroll
-  for (int j = 0; j < X; ++j) {
-    int ii, kk;
-    slot<ROWS, FAST_K>(j, ii, kk);
-    v[j] = get(ii, k0 + kk);
-  }
-}
-
-template <bool CPLX, int ROWS, int X, bool FAST_K>
-__device__ __forceinline__ void commit(double* re, double* im, const cplx (&v)[X]) {
-#pragma unroll
-  for (int j = 0; j < X; ++j) {
-    int ii, kk;
-    slot<ROWS, FAST_K>(j, ii, kk);
-    re[kk * (ROWS + 1) + ii] = v[j].re;
-    if (CPLX) im[kk * (ROWS + 1) + ii] = v[j].im;
-  }
-}
-
-// Runtime choice of the staging order for operands whose memory order
-// changes from chunk to chunk (a symmetric operand read through one
-// triangle).  The flag is uniform across the workgroup; the two slot maps
-// are blended with selects, so fetch and commit stay branch-free and the
-// pipeline below remains one basic block per chunk.
-template <int ROWS>
-__device__ __forceinline__ void slot_sel(int j, bool fast, int& ii, int& kk) {
-  const int t = threadIdx.x;
-  const int ir = t % ROWS, kr = t / ROWS + (NT / ROWS) * j;
-  const int kf = t % KC, jf = t / KC + (NT / KC) * j;
-  ii = fast ? jf : ir;
-  kk = fast ? kf : kr;
-}
-
-template <int ROWS, int X, class Gt>
-__device__ __forceinline__ void fetch_rt(cplx (&v)[X], int k0, Gt get, bool fast) {
-#pragma unroll
-  for (int j = 0; j < X; ++j) {
-    int ii, kk;
-    slot_sel<ROWS>(j, fast, ii, kk);
-    v[j] = get(ii, k0 + kk);
-  }
-}
-template <bool CPLX, int ROWS, int X>
-__device__ __forceinline__ void commit_rt(double* re, double* im, const cplx (&v)[X], bool fast) {
-#pragma unroll
-  for (int j = 0; j < X; ++j) {
-    int ii, kk;
-    slot_sel<ROWS>(j, fast, ii, kk);
-    re[kk * (ROWS + 1) + ii] = v[j].re;
-    if (CPLX) im[kk * (ROWS + 1) + ii] = v[j].im;
-  }
-}
-
 // XCD-aware tile order.  Workgroups are dispatched round-robin over the 8
 // XCDs in linear-id order; this bijection gives each XCD a contiguous range
 // of logical ids, so the tiles of one shift (which share the A operand) run
@@ -411,136 +240,6 @@ __device__ __forceinline__ void xcd_remap(int& x, int& y) {
   x = logical % nx;
   y = logical / nx;
 }
-
-// Double-buffered LDS (two stages) with a two-chunk-deep register
-// prefetch: two register sets alternate, so a chunk's global loads have two
-// chunks of matrix-core time to land, and one barrier per chunk orders both
-// "commit before use" and "use before overwrite" (each stage is rewritten
-// one chunk after its use).
-//   prologue: R0 <- c0, R1 <- c1, commit R0 -> buf0, R0 <- c2
-//   even c:   mfma(buf0); commit R1 (c+1) -> buf1; R1 <- c+3
-//   odd  c:   mfma(buf1); commit R0 (c+1) -> buf0; R0 <- c+3
-// Chunks past the end are fetched as the last chunk again (clamped index,
-// same memory, never used) and committed to the idle stage, so the loop body
-// has no data-dependent branches and the wait counts stay exact.
-template <bool CPLX, int NTILE>
-struct Stage2 {
-  Stage<CPLX, NTILE> buf[2];
-};
-
-// K loop over [kb, ke): P += A[:, k] B[k, :].  ga(m, k) and gb(n, k) return
-// the operands (zero outside the matrices); bfast(k0) picks the B staging
-// order per chunk.  gd(k), unless NoScale, returns a factor d_k applied to
-// column k of A on its way to the matrix cores (one load per k and chunk
-// instead of one per element); it must accept any k of the last chunk.
-// Which block pairs (a, b) of the wave take part in a chunk, as a mask of
-// bits 2a + b (evaluated per chunk, uniform over the wave): all (AllLive), or
-// for a triangular A operand on a 64-row tile (TriLive, swizzled block rows)
-// both pairs of each row block whose rows meet the chunk's k range in the
-// nonzero triangle.
-struct AllLive {
-  static constexpr bool kAll = true;
-  static constexpr int kSwz = 0;
-  __device__ int operator()(int) const { return 15; }
-};
-template <bool LOWER>   // LOWER: A[m][k] = 0 for k > m; else A[m][k] = 0 for k < m
-struct TriLive {
-  static constexpr bool kAll = false;
-  static constexpr int kSwz = 1;
-  __device__ int operator()(int k0) const {
-    static_assert(KC == 16, "a chunk spans one 16-row block");
-    const int wr = (threadIdx.x >> 6) / Geo<64>::WN;
-    const int c = k0 / KC;
-    const int mb0 = wr, mb1 = 3 - wr;
-    const bool l0 = LOWER ? c <= mb0 : c >= mb0;
-    const bool l1 = LOWER ? c <= mb1 : c >= mb1;
-    return __builtin_amdgcn_readfirstlane((l0 ? 3 : 0) | (l1 ? 12 : 0));   // both column blocks of a live row block
-  }
-};
-
-// The masks these functors return (15, 12, 3; 0 when no pair is live) each
-// have an instance below; a functor returning another mask would skip its
-// chunk, so a new one adds its masks here.
-template <bool CPLX, int NTILE, bool SC, class LV>
-__device__ __forceinline__ void run_chunk(Acc<CPLX, NTILE>& acc, const Stage<CPLX, NTILE>& st, LV lv, int k0) {
-  if constexpr (LV::kAll) {
-    mfma_chunk<CPLX, NTILE, SC>(acc, st);
-  } else {
-    const int m = lv(k0);
-    if (m == 15) mfma_chunk<CPLX, NTILE, SC, 15, LV::kSwz>(acc, st);
-    else if (m == 12) mfma_chunk<CPLX, NTILE, SC, 12, LV::kSwz>(acc, st);
-    else if (m == 3) mfma_chunk<CPLX, NTILE, SC, 3, LV::kSwz>(acc, st);
-  }
-}
-
-template <bool CPLX, int NTILE, bool AFAST, class GA, class GB, class BF, class GD = NoScale, class LV = AllLive>
-__device__ __forceinline__ void gemm_pipe(Acc<CPLX, NTILE>& acc, Stage2<CPLX, NTILE>& s, int kb, int ke,
-                                          GA ga, GB gb, BF bfast, GD gd = GD(), LV lv = LV()) {
-  using G = Geo<NTILE>;
-  constexpr bool SC = !std::is_same<GD, NoScale>::value;
-  if (kb >= ke) return;
-  const int nc = (ke - kb + KC - 1) / KC;
-  auto kat = [&](int c) { return kb + min(c, nc - 1) * KC; };
-  const int t = threadIdx.x;
-  auto dfetch = [&](cplx& r, int k0) {
-    // every thread loads (the lanes of a wave share KC addresses), so the
-    // load is not under a branch; threads t < KC commit it
-    if constexpr (SC) r = gd(k0 + (t & (KC - 1)));
-  };
-  auto dcommit = [&](Stage<CPLX, NTILE>& st, const cplx& r) {
-    if constexpr (SC) {
-      if (t < KC) {
-        st.d_re[t] = r.re;
-        if (CPLX) st.d_im[t] = r.im;
-      }
-    }
-  };
-  cplx ra0[G::XA], rb0[G::XB], ra1[G::XA], rb1[G::XB];
-  cplx rd0{1.0, 0.0}, rd1{1.0, 0.0};
-  bool fb0 = bfast(kat(0)), fb1 = bfast(kat(1));
-  fetch<64, G::XA, AFAST>(ra0, kat(0), ga);
-  fetch_rt<NTILE, G::XB>(rb0, kat(0), gb, fb0);
-  dfetch(rd0, kat(0));
-  fetch<64, G::XA, AFAST>(ra1, kat(1), ga);
-  fetch_rt<NTILE, G::XB>(rb1, kat(1), gb, fb1);
-  dfetch(rd1, kat(1));
-  commit<CPLX, 64, G::XA, AFAST>(&s.buf[0].a_re[0][0], &s.buf[0].a_im[0][0], ra0);
-  commit_rt<CPLX, NTILE, G::XB>(&s.buf[0].b_re[0][0], &s.buf[0].b_im[0][0], rb0, fb0);
-  dcommit(s.buf[0], rd0);
-  fb0 = bfast(kat(2));
-  fetch<64, G::XA, AFAST>(ra0, kat(2), ga);
-  fetch_rt<NTILE, G::XB>(rb0, kat(2), gb, fb0);
-  dfetch(rd0, kat(2));
-  __syncthreads();
-  for (int c = 0; c < nc; c += 2) {
-    run_chunk<CPLX, NTILE, SC>(acc, s.buf[0], lv, kb + c * KC);
-    commit<CPLX, 64, G::XA, AFAST>(&s.buf[1].a_re[0][0], &s.buf[1].a_im[0][0], ra1);
-    commit_rt<CPLX, NTILE, G::XB>(&s.buf[1].b_re[0][0], &s.buf[1].b_im[0][0], rb1, fb1);
-    dcommit(s.buf[1], rd1);
-    fb1 = bfast(kat(c + 3));
-    fetch<64, G::XA, AFAST>(ra1, kat(c + 3), ga);
-    fetch_rt<NTILE, G::XB>(rb1, kat(c + 3), gb, fb1);
-    dfetch(rd1, kat(c + 3));
-    __syncthreads();
-    if (c + 1 >= nc) break;
-    run_chunk<CPLX, NTILE, SC>(acc, s.buf[1], lv, kb + (c + 1) * KC);
-    commit<CPLX, 64, G::XA, AFAST>(&s.buf[0].a_re[0][0], &s.buf[0].a_im[0][0], ra0);
-    commit_rt<CPLX, NTILE, G::XB>(&s.buf[0].b_re[0][0], &s.buf[0].b_im[0][0], rb0, fb0);
-    dcommit(s.buf[0], rd0);
-    fb0 = bfast(kat(c + 4));
-    fetch<64, G::XA, AFAST>(ra0, kat(c + 4), ga);
-    fetch_rt<NTILE, G::XB>(rb0, kat(c + 4), gb, fb0);
-    dfetch(rd0, kat(c + 4));
-    __syncthreads();
-  }
-}
-
-struct RowsFast {
-  __device__ bool operator()(int) const { return false; }
-};
-struct KFast {
-  __device__ bool operator()(int) const { return true; }
-};
 
 // Which 16 x 16 blocks of a complex tile take part in the 16 columns c of the
 // product: all, those of a triangular A operand that meet the columns in its
@@ -566,8 +265,7 @@ struct UpperBlocks {
 };
 
 // --------------------------------------------------------------------------
-// Complex tile engine: the same 64 x NTILE products (NTILE = 64, 32 or 16)
-// with the operands loaded straight from global memory into LDS.
+// Tile engine: the operands go straight from global memory into LDS.
 //
 // What bounds these products is the issue of everything that is not an MFMA:
 // with the operands staged through registers (loads with 64-bit per-lane
@@ -595,20 +293,33 @@ struct UpperBlocks {
 //   k fast     slot = row 8 + (k ^ ((row / 2) % 8))   (contiguous along k)
 // The 16 lanes of an MFMA operand row read 16 consecutive slots, or 16 slots
 // that differ modulo 16 (the exclusive or sees to that): no bank conflicts.
+//
+// Real products (inertia) take stages of 16 columns, always rows fast.  Their
+// 8-byte elements start at any multiple of 8, so they move as two 4-byte words
+// by a lane pair each; on 64- and 32-row operands odd columns swap their 16-row
+// halves, which keeps two columns read together on different banks.  An inertia
+// of a sheet of N=7956 with 16 shifts took 12.15 ms with real tiles staged
+// through registers (64 or 128 rows, 1 to 3 workgroups per CU), 11.5 so.
 // --------------------------------------------------------------------------
 typedef double dbl2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) void* lds_ptr;
 typedef const __attribute__((address_space(1))) void* glb_ptr;
 
-constexpr int KD = 8;                        // columns per stage
+constexpr int KD = 8, KR = 16;               // columns per stage, complex and real
 constexpr unsigned LANE_OUT = 0x80000000u;   // lane offset past every descriptor's range: reads zeros
 __device__ __align__(16) double kUnitElem[2] = {1.0, 0.0};   // never written
 
-template <int NTILE, bool SCALE>
-struct CStage {
-  dbl2 a[2][KD * 64];
-  dbl2 b[2][KD * NTILE];
-  dbl2 d[SCALE ? 2 : 1][SCALE ? KD : 1];
+template <bool CPLX>
+using elem_t = std::conditional_t<CPLX, dbl2, double>;
+template <bool CPLX>
+constexpr int kDepth = CPLX ? KD : KR;
+
+template <bool CPLX, int NTILE, bool SCALE>
+struct TileStage {
+  static constexpr int D = kDepth<CPLX>;
+  elem_t<CPLX> a[2][D * 64];
+  elem_t<CPLX> b[2][D * NTILE];
+  elem_t<CPLX> d[SCALE ? 2 : 1][SCALE ? D : 1];
 };
 
 // The wave's index and a pointer the compiler may not know to be uniform.
@@ -629,6 +340,14 @@ __device__ __forceinline__ void load_lds(const double* base, unsigned off, dbl2*
 __device__ __forceinline__ void load_lds_ptr(const double* p, dbl2* lds) {
   __builtin_amdgcn_global_load_lds((glb_ptr)p, (lds_ptr)lds, 16, 0, 0);
 }
+// 4 bytes per lane into LDS at lds + 4 lane
+__device__ __forceinline__ void load_lds4(const double* base, unsigned off, double* lds) {
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, LANE_OUT, 0x00020000);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr)lds, 4, off, 0, 0, 0);
+}
+__device__ __forceinline__ void load_lds4_ptr(const double* p, int half, double* lds) {
+  __builtin_amdgcn_global_load_lds((glb_ptr)((const char*)p + 4 * half), (lds_ptr)lds, 4, 0, 0);
+}
 
 // Operand slot of lane `lane` in the wave load q of a stage: (row, k).
 template <int ROWS>
@@ -641,20 +360,32 @@ __device__ __forceinline__ void slot_k(int q, int lane, int& m, int& k) {
   k = (lane & 7) ^ ((m >> 1) & 7);
 }
 
+// The same of a real operand: 32 elements of a wave load, two lanes each.
+template <int ROWS>
+__device__ __forceinline__ int real_slot(int k, int row) {
+  return k * ROWS + (ROWS >= 32 ? row ^ ((k & 1) << 4) : row);
+}
+template <int ROWS>
+__device__ __forceinline__ void slot_real(int q, int lane, int& m, int& k) {
+  const int e = q * 32 + (lane >> 1);
+  k = e / ROWS;
+  m = ROWS >= 32 ? (e % ROWS) ^ ((k & 1) << 4) : e % ROWS;
+}
+
 // Operands of gemm_lds.  issue(k0, lds) starts the loads of columns
-// [k0, k0 + KD) (k relative to the product's first column; columns from K on
+// [k0, k0 + D) (k relative to the product's first column; columns from K on
 // and rows from nrows on read zeros); fast(k0) is the layout it uses (true: k
 // fast).  Wave w makes the loads q = w, w + 4, ...
-template <int ROWS>
+template <bool CPLX, int ROWS>
 struct LoadCount {
-  static constexpr int N = KD * ROWS / 64, J = (N + 3) / 4;
+  static constexpr int N = CPLX ? KD * ROWS / 64 : KR * ROWS / 32, J = (N + 3) / 4;
 };
 
 // Element (row, k) at base + k ld + row.
-template <int ROWS>
-struct ColsOp : LoadCount<ROWS> {
-  using LoadCount<ROWS>::N;
-  using LoadCount<ROWS>::J;
+template <bool CPLX, int ROWS>
+struct ColsOp : LoadCount<CPLX, ROWS> {
+  using LoadCount<CPLX, ROWS>::N;
+  using LoadCount<CPLX, ROWS>::J;
   const double* base;
   int64_t ld;
   int K, w;
@@ -662,18 +393,23 @@ struct ColsOp : LoadCount<ROWS> {
   int kk[J];
   __device__ __forceinline__ ColsOp(const double* b, int ld_, int nrows, int K_)
       : base(uniform(b)), ld(ld_), K(K_), w(wave_id()) {
+    const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int j = 0; j < J; ++j) {
       int m;
-      slot_rows<ROWS>(w + 4 * j, threadIdx.x & 63, m, kk[j]);
-      v[j] = m < nrows ? (unsigned)(kk[j] * ld_ + m) * 16u : LANE_OUT;
+      if (CPLX) slot_rows<ROWS>(w + 4 * j, lane, m, kk[j]);
+      else slot_real<ROWS>(w + 4 * j, lane, m, kk[j]);
+      const unsigned e = (unsigned)(kk[j] * ld_ + m);
+      v[j] = m >= nrows ? LANE_OUT : CPLX ? e * 16u : e * 8u + 4u * (lane & 1);
     }
   }
-  __device__ __forceinline__ void issue(int k0, dbl2* lds) const {
+  __device__ __forceinline__ void issue(int k0, elem_t<CPLX>* lds) const {
 #pragma unroll
     for (int j = 0; j < J; ++j) {
       if (N < 4 && w >= N) continue;
-      load_lds(base + 2 * (ld * k0), k0 + kk[j] < K ? v[j] : LANE_OUT, lds + (w + 4 * j) * 64);
+      const unsigned o = k0 + kk[j] < K ? v[j] : LANE_OUT;
+      if constexpr (CPLX) load_lds(base + 2 * (ld * k0), o, lds + (w + 4 * j) * 64);
+      else load_lds4(base + ld * k0, o, lds + (w + 4 * j) * 32);
     }
   }
   __device__ __forceinline__ static constexpr bool fast(int) { return false; }
@@ -681,9 +417,9 @@ struct ColsOp : LoadCount<ROWS> {
 
 // Element (row, k) at base + row ld + k.
 template <int ROWS>
-struct RowsOp : LoadCount<ROWS> {
-  using LoadCount<ROWS>::N;
-  using LoadCount<ROWS>::J;
+struct RowsOp : LoadCount<true, ROWS> {
+  using LoadCount<true, ROWS>::N;
+  using LoadCount<true, ROWS>::J;
   const double* base;
   int K, w;
   int rows16;   // rows rounded up to blocks of 16: the slots behind them are never read
@@ -711,23 +447,28 @@ struct RowsOp : LoadCount<ROWS> {
 // The unit lower triangular n x n block T (n <= 64; strict part stored, T(r,
 // q) at base + q ld + r) as the A operand: A[m][k] = T[m][k], or T[k][m] when
 // TRANS.
-template <bool TRANS>
-struct TriOp : LoadCount<64> {
+template <bool CPLX, bool TRANS>
+struct TriOp : LoadCount<CPLX, 64> {
+  static_assert(CPLX || !TRANS, "real operands are rows fast");
+  using LoadCount<CPLX, 64>::J;
   const double* base;
   int ld, n, w;
   __device__ __forceinline__ TriOp(const double* b, int ld_, int n_) : base(b), ld(ld_), n(n_), w(wave_id()) {}
-  __device__ __forceinline__ void issue(int k0, dbl2* lds) const {
+  __device__ __forceinline__ void issue(int k0, elem_t<CPLX>* lds) const {
+    const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int j = 0; j < J; ++j) {
       int m, k;
-      if (TRANS) slot_k(w + 4 * j, threadIdx.x & 63, m, k);
-      else slot_rows<64>(w + 4 * j, threadIdx.x & 63, m, k);
+      if (!CPLX) slot_real<64>(w + 4 * j, lane, m, k);
+      else if (TRANS) slot_k(w + 4 * j, lane, m, k);
+      else slot_rows<64>(w + 4 * j, lane, m, k);
       k += k0;
       const int r = TRANS ? k : m, q = TRANS ? m : k;
       const double* p = r == q ? kUnitElem : kZeroElem;
-      if (r > q) p = base + 2 * ((int64_t)q * ld + r);
+      if (r > q) p = base + (CPLX ? 2 : 1) * ((int64_t)q * ld + r);
       if (max(r, q) >= n) p = kZeroElem;
-      load_lds_ptr(p, lds + (w + 4 * j) * 64);
+      if constexpr (CPLX) load_lds_ptr(p, lds + (w + 4 * j) * 64);
+      else load_lds4_ptr(p, lane & 1, lds + (w + 4 * j) * 32);
     }
   }
   __device__ __forceinline__ static constexpr bool fast(int) { return TRANS; }
@@ -746,9 +487,9 @@ struct TriOp : LoadCount<64> {
 // of arrays and those above it from another (utown / utg elements further);
 // side 0 reads Z(i, k), side 1 Z(k, i).
 template <int ROWS, bool HERM>
-struct SymOp : LoadCount<ROWS> {
-  using LoadCount<ROWS>::N;
-  using LoadCount<ROWS>::J;
+struct SymOp : LoadCount<true, ROWS> {
+  using LoadCount<true, ROWS>::N;
+  using LoadCount<true, ROWS>::J;
   const double *own, *g;
   int ld, c, gw, i0, nb, w, side;
   int64_t utown, utg;
@@ -807,20 +548,24 @@ struct SymOp : LoadCount<ROWS> {
 };
 
 // Per-column factors of the A operand: d_k at base + k stride (elements).
+template <bool CPLX>
 struct DiagOp {
   const double* base;
   int64_t stride;
   int K;
   __device__ __forceinline__ DiagOp(const double* b, int64_t st, int K_) : base(uniform(b)), stride(st), K(K_) {}
-  __device__ __forceinline__ void issue(int k0, dbl2* lds) const {
-    if (threadIdx.x < KD) {
-      const int k = threadIdx.x;
-      load_lds(base + 2 * (stride * k0), k0 + k < K ? (unsigned)(k * stride) * 16u : LANE_OUT, lds);
-    }
+  __device__ __forceinline__ void issue(int k0, elem_t<CPLX>* lds) const {
+    if (threadIdx.x >= (CPLX ? KD : 2 * KR)) return;
+    const int k = CPLX ? threadIdx.x : threadIdx.x >> 1;
+    const unsigned e = (unsigned)(k * stride);
+    const unsigned o = k0 + k >= K ? LANE_OUT : CPLX ? e * 16u : e * 8u + 4u * (threadIdx.x & 1);
+    if constexpr (CPLX) load_lds(base + 2 * (stride * k0), o, lds);
+    else load_lds4(base + stride * k0, o, lds);
   }
 };
 struct NoDiag {
   __device__ __forceinline__ void issue(int, dbl2*) const {}
+  __device__ __forceinline__ void issue(int, double*) const {}
 };
 
 // One stage on the matrix cores.  MASKED: only the block pairs (a, b) with bit
@@ -885,6 +630,35 @@ __device__ __forceinline__ void mfma_stage(Acc<true, NTILE, TALL>& acc, const db
   }
 }
 
+template <int NTILE, bool TALL, bool SCALE, bool MASKED, int SWZ>
+__device__ __forceinline__ void mfma_stage(Acc<false, NTILE, TALL>& acc, const double* as, bool, const double* bs, bool,
+                                           const double* ds, int mask) {
+  using G = Geo<NTILE, TALL>;
+  const int lane = threadIdx.x & 63;
+  const int w = threadIdx.x >> 6;
+  const int li = lane & 15, lk = lane >> 4;
+#pragma unroll
+  for (int ks = 0; ks < KR / 4; ++ks) {
+    const int k = ks * 4 + lk;
+    double av[G::BM], bv[G::BN];
+#pragma unroll
+    for (int t = 0; t < G::BM; ++t) av[t] = as[real_slot<64>(k, block_row<NTILE, SWZ, TALL>(w, t) + li)];
+#pragma unroll
+    for (int t = 0; t < G::BN; ++t) bv[t] = bs[real_slot<NTILE>(k, block_col<NTILE, SWZ, TALL>(w, t) + li)];
+    if constexpr (SCALE) {
+      const double d = ds[k];
+#pragma unroll
+      for (int t = 0; t < G::BM; ++t) av[t] *= d;
+    }
+#pragma unroll
+    for (int a = 0; a < G::BM; ++a)
+#pragma unroll
+      for (int b = 0; b < G::BN; ++b)
+        if (!MASKED || ((mask >> (G::BN * a + b)) & 1))
+          acc.re[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc.re[a][b], 0, 0, 0);
+  }
+}
+
 // Waits for the caller's loads into LDS and its LDS reads, then for every
 // wave of the workgroup.
 __device__ __forceinline__ void stage_barrier() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
@@ -894,11 +668,12 @@ __device__ __forceinline__ void stage_barrier() { asm volatile("s_waitcnt vmcnt(
 // buffer and have the other stage's MFMAs (and three other workgroups') to
 // land.  The result has mrows rows (64, or fewer: the blocks behind them are
 // not multiplied).
-template <class LV, int NTILE, bool TALL, class OA, class OB, class OD>
-__device__ __forceinline__ void gemm_lds(Acc<true, NTILE, TALL>& acc,
-                                         CStage<NTILE, !std::is_same<OD, NoDiag>::value>& s, int mrows, int K, const OA& oa,
-                                         const OB& ob, const OD& od, LV lv) {
+template <class LV, bool CPLX, int NTILE, bool TALL, class OA, class OB, class OD>
+__device__ __forceinline__ void gemm_lds(Acc<CPLX, NTILE, TALL>& acc,
+                                         TileStage<CPLX, NTILE, !std::is_same<OD, NoDiag>::value>& s, int mrows, int K,
+                                         const OA& oa, const OB& ob, const OD& od, LV lv) {
   constexpr bool SC = !std::is_same<OD, NoDiag>::value;
+  constexpr int KD = kDepth<CPLX>;
   using G = Geo<NTILE, TALL>;
   constexpr int SWZ = NTILE == 64 && !TALL ? LV::kSwz : 0;
   constexpr bool MASKED = TALL || NTILE == 16 || !LV::kAll;
@@ -938,14 +713,14 @@ __device__ __forceinline__ void gemm_lds(Acc<true, NTILE, TALL>& acc,
 // f(acc) with the accumulators of a tile of mrows rows: the square wave layout,
 // or the tall one where at most three of the four 16-row blocks are live.  (16
 // columns have one block per wave: one layout.)
-template <int NTILE, class F>
+template <bool CPLX, int NTILE, class F>
 __device__ __forceinline__ void with_layout(int mrows, F f) {
   if (NTILE == 16 || mrows > 48) {
-    Acc<true, NTILE, false> acc;
+    Acc<CPLX, NTILE, false> acc;
     acc.zero();
     f(acc);
   } else if constexpr (NTILE != 16) {
-    Acc<true, NTILE, true> acc;
+    Acc<CPLX, NTILE, true> acc;
     acc.zero();
     f(acc);
   }
@@ -1217,8 +992,6 @@ constexpr int NTD = 256;
 constexpr int SMALL_ROWS = 80;   // rows below a panel that k_diag and k_selinv_small take along
 constexpr int LDD = 65;   // row stride of a[][]: 16-byte elements rotate over the banks
 
-template <bool CPLX>
-using elem_t = std::conditional_t<CPLX, dbl2, double>;
 __device__ __forceinline__ cplx to_cplx(dbl2 v) { return {v.x, v.y}; }
 __device__ __forceinline__ cplx to_cplx(double v) { return {v, 0.0}; }
 template <bool CPLX>
@@ -1486,13 +1259,12 @@ __global__ void __launch_bounds__(NTD, 2) k_diag(Src src) {
 }
 
 // L_Bp = A_Bp L_pp^{-T} D^{-1}: P[c][i] = sum_k Linv[c][k] A[i][k], then / d_c.
-// Complex panel products run on tiles of 64 x TNv (TNv = 64, 32 or 16 rows,
-// pick_tile), at most 33 KB of LDS and 128 registers: four workgroups per CU.
-// Real ones on 64 or 128 rows (a runtime option).
-#define PXS_LB(CPLXv, TNv) __launch_bounds__(NT, (CPLXv) ? 4 : (TNv) == 64 ? 2 : 1)
+// Panel products run on tiles of 64 x TN (TN = 64, 32 or 16 rows, pick_tile), at
+// most 33 KB of LDS and 128 registers: four workgroups per CU.
+#define PXS_LB __launch_bounds__(NT, 4)
 
 template <bool CPLX, int TN, class Src>
-__global__ void PXS_LB(CPLX, TN) k_trsm(Src src) {
+__global__ void PXS_LB k_trsm(Src src) {
   __shared__ cplx dinv[64];
   Common c;
   PanelK p;
@@ -1507,45 +1279,25 @@ __global__ void PXS_LB(CPLX, TN) k_trsm(Src src) {
     const cplx d = ld_elem<CPLX>(Ls, dbase + (int64_t)threadIdx.x * p.ld + threadIdx.x);
     dinv[threadIdx.x] = CPLX ? cinv(d) : cplx{1.0 / d.re, 0.0};
   }
-  // P[m][n] / d_m into row n of the panel
-  auto store = [&](int m, int n, cplx v) {
-    const int ig = i0 + n;
-    if (m < p.wp && ig < p.nb) st_elem<CPLX>(Ls, rbase + (int64_t)m * p.ld + ig, cmul(v, dinv[m]));
-  };
-  // L^{-1} is lower triangular: the all-zero blocks of a chunk are not
-  // multiplied (on the real 128-row tiles they are)
-  if constexpr (CPLX) {
-    __shared__ CStage<TN, false> s;
-    with_layout<TN>(p.wp, [&](auto& acc) {
-      gemm_lds(acc, s, p.wp, p.wp, TriOp<false>(Ls + 2 * dbase, p.ld, p.wp),
-               ColsOp<TN>(Ls + 2 * (rbase + i0), p.ld, p.nb - i0, p.wp), NoDiag(), TriBlocks<true>());
-      acc_foreach<true, TN, swz_of<decltype(acc), TriBlocks<true>>>(acc, store);
+  constexpr int E = CPLX ? 2 : 1;   // doubles per element
+  // L^{-1} is lower triangular: the all-zero blocks of a stage are not
+  // multiplied
+  __shared__ TileStage<CPLX, TN, false> s;
+  with_layout<CPLX, TN>(p.wp, [&](auto& acc) {
+    gemm_lds(acc, s, p.wp, p.wp, TriOp<CPLX, false>(Ls + E * dbase, p.ld, p.wp),
+             ColsOp<CPLX, TN>(Ls + E * (rbase + i0), p.ld, p.nb - i0, p.wp), NoDiag(), TriBlocks<true>());
+    acc_foreach<CPLX, TN, swz_of<decltype(acc), TriBlocks<true>>>(acc, [&](int m, int n, cplx v) {
+      const int ig = i0 + n;
+      if (m < p.wp && ig < p.nb) st_elem<CPLX>(Ls, rbase + (int64_t)m * p.ld + ig, mul<CPLX>(v, dinv[m]));
     });
-  } else {
-    __shared__ Stage2<false, TN> s;
-    using LV = std::conditional_t<TN == 64, TriLive<true>, AllLive>;
-    Acc<false, TN> acc;
-    acc.zero();
-    gemm_pipe<false, TN, false>(
-        acc, s, 0, p.wp,
-        [&](int m, int kg) -> cplx {   // Linv[c][k]: column k of the diagonal block
-          const cplx v = ld_or_zero<false>(Ls, dbase + (int64_t)kg * p.ld + m, m < p.wp && kg < p.wp && m > kg);
-          return (m == kg && m < p.wp) ? cplx{1.0, 0.0} : v;
-        },
-        [&](int n, int kg) -> cplx {   // A[i][k]
-          const int ig = i0 + n;
-          return ld_or_zero<false>(Ls, rbase + (int64_t)kg * p.ld + ig, kg < p.wp && ig < p.nb);
-        },
-        RowsFast(), NoScale(), LV());
-    acc_foreach<false, TN, LV::kSwz>(acc, store);
-  }
+  });
 }
 
 // Left-looking update of panel p from the earlier columns of its own
 // supernode: A[r][c] -= sum_{k < p0} L[r][k] d_k L[c][k] for rows r >= p0 of
 // the row list and the panel's columns c.  P[c][r] = sum_k (d_k L[c][k]) L[r][k].
 template <bool CPLX, int TN, class Src>
-__global__ void PXS_LB(CPLX, TN) k_int_update(Src src) {
+__global__ void PXS_LB k_int_update(Src src) {
   Common c;
   PanelK p;
   int bx, by;
@@ -1561,34 +1313,15 @@ __global__ void PXS_LB(CPLX, TN) k_int_update(Src src) {
     e = cbase + (int64_t)(p.p0 + min(m, p.wp - 1)) * p.ld + min(rg, nrows - 1);
     return m < p.wp && rg < nrows && rg >= m;
   };
-  if constexpr (CPLX) {
-    // A: L[p0 + c][k], scaled by d_k on the way to the MFMAs; B: L[p0 + r][k]
-    __shared__ CStage<TN, true> s;
-    with_layout<TN>(p.wp, [&](auto& acc) {
-      gemm_lds(acc, s, p.wp, p.p0, ColsOp<64>(Ls + 2 * cbase, p.ld, p.wp, p.p0),
-               ColsOp<TN>(Ls + 2 * (cbase + r0), p.ld, nrows - r0, p.p0),
-               DiagOp(Ls + 2 * p.off, (int64_t)p.ld + 1, p.p0), AllBlocks());
-      acc_sub_into(acc, Ls, at);
-    });
-  } else {
-    __shared__ Stage2<false, TN> s;
-    Acc<false, TN> acc;
-    acc.zero();
-    gemm_pipe<false, TN, false>(
-        acc, s, 0, p.p0,
-        [&](int m, int kg) -> cplx {   // L[p0 + c][k] (times d_k on the way to the MFMAs)
-          return ld_or_zero<false>(Ls, cbase + (int64_t)kg * p.ld + m, m < p.wp && kg < p.p0);
-        },
-        [&](int n, int kg) -> cplx {   // L[p0 + r][k]
-          const int rg = r0 + n;
-          return ld_or_zero<false>(Ls, cbase + (int64_t)kg * p.ld + rg, kg < p.p0 && rg < nrows);
-        },
-        RowsFast(),
-        [&](int kg) -> cplx {          // d_k
-          return ld_or_zero<false>(Ls, p.off + (int64_t)kg * p.ld + kg, kg < p.p0);
-        });
+  // A: L[p0 + c][k], scaled by d_k on the way to the MFMAs; B: L[p0 + r][k]
+  constexpr int E = CPLX ? 2 : 1;
+  __shared__ TileStage<CPLX, TN, true> s;
+  with_layout<CPLX, TN>(p.wp, [&](auto& acc) {
+    gemm_lds(acc, s, p.wp, p.p0, ColsOp<CPLX, 64>(Ls + E * cbase, p.ld, p.wp, p.p0),
+             ColsOp<CPLX, TN>(Ls + E * (cbase + r0), p.ld, nrows - r0, p.p0),
+             DiagOp<CPLX>(Ls + E * p.off, (int64_t)p.ld + 1, p.p0), AllBlocks());
     acc_sub_into(acc, Ls, at);
-  }
+  });
 }
 
 __device__ __forceinline__ void tri_index(int b, int& ti, int& tj) {
@@ -1606,7 +1339,7 @@ __device__ __forceinline__ void tri_index(int b, int& ti, int& tj) {
 // with K = all of its columns (p0 = 0, wp = w_J, B = the rows below it).
 // P[j][i] = sum_k (d_k L[j][k]) L[i][k].
 template <bool CPLX, int TN, class Src>
-__global__ void PXS_LB(CPLX, TN) k_update(Src src) {
+__global__ void PXS_LB k_update(Src src) {
   Common c;
   PanelK p;
   int bx, by;
@@ -1634,35 +1367,15 @@ __global__ void PXS_LB(CPLX, TN) k_update(Src src) {
     e = cmap[base + jc] + c.relpos[cseg[base + jc] + base + ic];
     return jg < p.nb && ig < p.nb && ig >= jg;
   };
-  if constexpr (CPLX) {
-    __shared__ CStage<TN, true> s;
-    const int64_t k0 = rbase + (int64_t)kb * p.ld;
-    with_layout<TN>(min(64, p.nb - j0), [&](auto& acc) {
-      gemm_lds(acc, s, p.nb - j0, ke - kb, ColsOp<64>(Ls + 2 * (k0 + j0), p.ld, p.nb - j0, ke - kb),
-               ColsOp<TN>(Ls + 2 * (k0 + i0), p.ld, p.nb - i0, ke - kb),
-               DiagOp(Ls + 2 * (p.off + (int64_t)kb * (p.ld + 1)), (int64_t)p.ld + 1, ke - kb), AllBlocks());
-      acc_sub_into(acc, Ls, at);
-    });
-  } else {
-    __shared__ Stage2<false, TN> s;
-    Acc<false, TN> acc;
-    acc.zero();
-    gemm_pipe<false, TN, false>(
-        acc, s, kb, ke,
-        [&](int m, int kg) -> cplx {   // L[j][k] (times d_k on the way to the MFMAs)
-          const int jg = j0 + m;
-          return ld_or_zero<false>(Ls, rbase + (int64_t)kg * p.ld + jg, kg < ke && jg < p.nb);
-        },
-        [&](int n, int kg) -> cplx {
-          const int ig = i0 + n;
-          return ld_or_zero<false>(Ls, rbase + (int64_t)kg * p.ld + ig, kg < ke && ig < p.nb);
-        },
-        RowsFast(),
-        [&](int kg) -> cplx {          // d_k
-          return ld_or_zero<false>(Ls, p.off + (int64_t)kg * p.ld + kg, kg < ke);
-        });
+  constexpr int E = CPLX ? 2 : 1;
+  __shared__ TileStage<CPLX, TN, true> s;
+  const int64_t k0 = rbase + (int64_t)kb * p.ld;
+  with_layout<CPLX, TN>(min(64, p.nb - j0), [&](auto& acc) {
+    gemm_lds(acc, s, p.nb - j0, ke - kb, ColsOp<CPLX, 64>(Ls + E * (k0 + j0), p.ld, p.nb - j0, ke - kb),
+             ColsOp<CPLX, TN>(Ls + E * (k0 + i0), p.ld, p.nb - i0, ke - kb),
+             DiagOp<CPLX>(Ls + E * (p.off + (int64_t)kb * (p.ld + 1)), (int64_t)p.ld + 1, ke - kb), AllBlocks());
     acc_sub_into(acc, Ls, at);
-  }
+  });
 }
 
 // --------------------------------------------------------------------------
@@ -1674,8 +1387,8 @@ __device__ __forceinline__ double* wbase(const Common& c, int sh) {
 
 // W = L_Bp Linv: P[c][i] = sum_k Linv[k][c] L[i][k]; W stored W[c * nb + i].
 template <int TN, class Src>
-__global__ void PXS_LB(true, TN) k_lhat(Src src) {
-  __shared__ CStage<TN, false> s;
+__global__ void PXS_LB k_lhat(Src src) {
+  __shared__ TileStage<true, TN, false> s;
   Common c;
   PanelK p;
   int bx, by;
@@ -1687,9 +1400,9 @@ __global__ void PXS_LB(true, TN) k_lhat(Src src) {
   const int64_t dbase = p.off + (int64_t)p.p0 * p.ld + p.p0;
   const int64_t rbase = dbase + p.wp;
   // A[m][k] = L^{-1}[k][m] vanishes for k < m (see k_trsm)
-  with_layout<TN>(p.wp, [&](auto& acc) {
-    gemm_lds(acc, s, p.wp, p.wp, TriOp<true>(Ls + 2 * dbase, p.ld, p.wp),
-             ColsOp<TN>(Ls + 2 * (rbase + i0), p.ld, p.nb - i0, p.wp), NoDiag(), TriBlocks<false>());
+  with_layout<true, TN>(p.wp, [&](auto& acc) {
+    gemm_lds(acc, s, p.wp, p.wp, TriOp<true, true>(Ls + 2 * dbase, p.ld, p.wp),
+             ColsOp<true, TN>(Ls + 2 * (rbase + i0), p.ld, p.nb - i0, p.wp), NoDiag(), TriBlocks<false>());
     acc_foreach<true, TN, swz_of<decltype(acc), TriBlocks<false>>>(acc, [&](int m, int n, cplx v) {
       const int ig = i0 + n;
       if (m < p.wp && ig < p.nb) st_elem<true>(W, (int64_t)m * p.nb + ig, v);
@@ -1702,8 +1415,8 @@ __global__ void PXS_LB(true, TN) k_lhat(Src src) {
 // storage (column min(i, k), row max(i, k)), the part in the rows below it
 // from the dense copy G of Z_CC made by k_gather_cc.
 template <int TN, class Src>
-__global__ void PXS_LB(true, TN) k_selinv_off(Src src) {
-  __shared__ CStage<TN, false> s;
+__global__ void PXS_LB k_selinv_off(Src src) {
+  __shared__ TileStage<true, TN, false> s;
   Common c;
   PanelK p;
   int bx, by;
@@ -1716,7 +1429,7 @@ __global__ void PXS_LB(true, TN) k_selinv_off(Src src) {
   const int base = p.p0 + p.wp;
   const int gw = p.w - base;   // rows of B inside the supernode
   const int64_t rbase = p.off + (int64_t)p.p0 * p.ld + base;
-  with_layout<TN>(p.wp, [&](auto& acc) {
+  with_layout<true, TN>(p.wp, [&](auto& acc) {
     gemm_lds(acc, s, p.wp, p.nb, RowsOp<64>(W, p.nb, p.wp, p.nb),
              SymOp<TN, false>(Ls + 2 * (p.off + (int64_t)base * (p.ld + 1)), p.ld, G - 2 * (int64_t)gw * (p.c + 1), p.c, gw,
                               i0, p.nb),
@@ -1774,8 +1487,8 @@ __global__ void __launch_bounds__(NT) k_gather_cc(Src src) {
 // Partial W^T Z_Bp over k in [split * SPLIT_ROWS, ...): P[c][r] = sum_k Z[k][c] W[k][r],
 // in tiles of TN of its columns r (tile bx = split x columns).
 template <int TN, class Src>
-__global__ void PXS_LB(true, TN) k_selinv_diag_partial(Src src) {
-  __shared__ CStage<TN, false> s;
+__global__ void PXS_LB k_selinv_diag_partial(Src src) {
+  __shared__ TileStage<true, TN, false> s;
   Common c;
   PanelK p;
   int bx, by;
@@ -1792,7 +1505,7 @@ __global__ void PXS_LB(true, TN) k_selinv_diag_partial(Src src) {
   double* out = part + 2 * (int64_t)sp * 64 * 64;
   // Z_pp is symmetric and stored by its lower triangle: only P[c][r], r >= c,
   // is summed by k_selinv_diag_final, so the blocks below that are skipped
-  with_layout<TN>(p.wp, [&](auto& acc) {
+  with_layout<true, TN>(p.wp, [&](auto& acc) {
     const UpperBlocks lv{n0 / 16};
     gemm_lds(acc, s, p.wp, ke - kb, RowsOp<64>(Ls + 2 * (rbase + kb), p.ld, p.wp, ke - kb),
              RowsOp<TN>(W + 2 * ((int64_t)n0 * p.nb + kb), p.nb, p.wp - n0, ke - kb), NoDiag(), lv);
@@ -2226,7 +1939,7 @@ Common make_common(const Symbolic& S, void* L, void* work) {
   return c;
 }
 
-// Tile width of a complex panel product: of 64, 32 and 16 columns the one
+// Tile width of a panel product: of 64, 32 and 16 columns the one
 // whose rounds over the compute units take least time.  tiles(tn) is the
 // number of workgroups at width tn.  A round of narrower tiles is shorter in
 // proportion, but the operand loads weigh more: 69.0, 68.1 and 60.7 TFLOP/s
@@ -2271,18 +1984,6 @@ void with_tile(int tn, F f) {
   else if (tn == 32) f(std::integral_constant<int, 32>());
   else f(std::integral_constant<int, 64>());
 }
-// the same for the real kernels: 64 or 128 rows (pxs_options.tile_rows)
-template <class F>
-void with_tile_real(int tn, F f) {
-  if (tn == 128) f(std::integral_constant<int, 128>());
-  else f(std::integral_constant<int, 64>());
-}
-template <bool CPLX, class F>
-void with_tile_of(int tn, F f) {
-  if constexpr (CPLX) with_tile(tn, f);
-  else with_tile_real(tn, f);
-}
-
 #define PXS_CHECK_LAUNCH()                         \
   do {                                             \
     hipError_t e_ = hipGetLastError();             \
@@ -2472,12 +2173,11 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
     if (e) return e;
   }
   Common c = make_common(S, L, work);
-  const int TR = S.tile_rows;
   const double fm = CPLX ? 8.0 : 2.0;   // flops per multiply-add
   const double eb = CPLX ? 16.0 : 8.0;  // bytes per element
   // tile width of a product over `rows` rows
   auto tile = [&](int rows, int m) {
-    return CPLX ? pick_tile(m, [&](int tn) { return (int64_t)tiles_of(rows, tn) * nshift; }) : TR;
+    return pick_tile(m, [&](int tn) { return (int64_t)tiles_of(rows, tn) * nshift; });
   };
   // the panel work of one panel: left-looking update from the earlier
   // columns of its supernode, LDL^T of the diagonal block, the rows below
@@ -2488,7 +2188,7 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
       const int nrows = k.ld - k.p0;
       ProfScope ps(KC_UPDATE, s, fm * nshift * xm.intu, eb * nshift * ((double)nrows * k.p0 + 2.0 * nrows * k.wp),
                    fm * nshift * ((double)nrows * k.wp - 0.5 * k.wp * (k.wp - 1)) * k.p0);
-      with_tile_of<CPLX>(tile(nrows, k.wp), [&](auto t) {
+      with_tile(tile(nrows, k.wp), [&](auto t) {
         constexpr int TN = decltype(t)::value;
         hipLaunchKernelGGL((k_int_update<CPLX, TN, OnePanel>), dim3(tiles_of(nrows, TN), nshift), dim3(NT), 0, s, OnePanel{c, k});
       });
@@ -2503,7 +2203,7 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
     if (k.nb > SMALL_ROWS) {
       ProfScope ps(KC_TRSM, s, fm * nshift * xm.trsm, eb * nshift * (2.0 * k.nb * k.wp + 0.5 * k.wp * (k.wp + 1)),
                    fm * nshift * (double)k.nb * k.wp * (k.wp + 1) / 2.0);
-      with_tile_of<CPLX>(tile(k.nb, k.wp), [&](auto t) {
+      with_tile(tile(k.nb, k.wp), [&](auto t) {
         constexpr int TN = decltype(t)::value;
         hipLaunchKernelGGL((k_trsm<CPLX, TN, OnePanel>), dim3(tiles_of(k.nb, TN), nshift), dim3(NT), 0, s, OnePanel{c, k});
       });
@@ -2521,11 +2221,11 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
     u.p0 = 0;
     u.wp = w;
     u.nb = below;
-    const int tn = CPLX ? pick_tile(below, [&](int q) { return update_tiles(below, q) * nshift; }) : TR;
+    const int tn = pick_tile(below, [&](int q) { return update_tiles(below, q) * nshift; });
     ProfScope ps(KC_UPDATE, s, fm * nshift * S.xm_update[P.J],
                  eb * nshift * ((double)below * w + (double)below * (below + 1)),
                  fm * nshift * (double)below * (below + 1) / 2.0 * w);
-    with_tile_of<CPLX>(tn, [&](auto t) {
+    with_tile(tn, [&](auto t) {
       constexpr int TN = decltype(t)::value;
       hipLaunchKernelGGL((k_update<CPLX, TN, OnePanel>), dim3(tiles_of(below, TM) * tiles_of(below, TN), nshift), dim3(NT), 0,
                          s, OnePanel{c, u});
@@ -2626,7 +2326,7 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
           m = std::max(m, ops[J][pos[J]].p.wp);
         }
         auto rows = [&](int J) { return ops[J][pos[J]].rows; };
-        const int tn = !CPLX ? TR : pick_tile(m, [&](int tq) {
+        const int tn = pick_tile(m, [&](int tq) {
           int64_t n = 0;
           for (int J : take) n += (int64_t)tiles_of(rows(J), tq) * nshift;
           return n;
@@ -2643,7 +2343,7 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
         }
         if (kind == FK_INT) {
           ProfScope ps(KC_UPDATE, st, w, b, s);
-          with_tile_of<CPLX>(tn, [&](auto t) {
+          with_tile(tn, [&](auto t) {
             constexpr int TN = decltype(t)::value;
             ok = with_group(c, items, nshift, [&](const auto& g, dim3 grid) {
               hipLaunchKernelGGL((k_int_update<CPLX, TN, std::decay_t<decltype(g)>>), grid, dim3(NT), 0, st, g);
@@ -2656,7 +2356,7 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
           });
         } else {
           ProfScope ps(KC_TRSM, st, w, b, s);
-          with_tile_of<CPLX>(tn, [&](auto t) {
+          with_tile(tn, [&](auto t) {
             constexpr int TN = decltype(t)::value;
             ok = with_group(c, items, nshift, [&](const auto& g, dim3 grid) {
               hipLaunchKernelGGL((k_trsm<CPLX, TN, std::decay_t<decltype(g)>>), grid, dim3(NT), 0, st, g);
@@ -2677,7 +2377,7 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
         if (take.empty()) return (int)hipErrorUnknown;   // unreachable: the first unscattered supernode is ready
         auto below = [&](int J) { return S.ld[J] - (S.sfirst[J + 1] - S.sfirst[J]); };
         for (int J : take) m = std::max(m, below(J));
-        const int tn = !CPLX ? TR : pick_tile(m, [&](int tq) {
+        const int tn = pick_tile(m, [&](int tq) {
           int64_t n = 0;
           for (int J : take) n += update_tiles(below(J), tq) * nshift;
           return n;
@@ -2699,7 +2399,7 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
           for (int64_t t = S.tgt_ptr[J]; t < S.tgt_ptr[J + 1]; ++t) --need[S.tgt[t]];
         }
         ProfScope ps(KC_UPDATE, st, w, b, s);
-        with_tile_of<CPLX>(tn, [&](auto t) {
+        with_tile(tn, [&](auto t) {
           constexpr int TN = decltype(t)::value;
           ok = with_group(c, items, nshift, [&](const auto& g, dim3 grid) {
             hipLaunchKernelGGL((k_update<CPLX, TN, std::decay_t<decltype(g)>>), grid, dim3(NT), 0, st, g);

@@ -101,7 +101,6 @@ struct Symbolic {
   // of a SelInv chunk (selinv_chunk shifts, 0 = the whole batch).
   int64_t work_fixed = 0, work_per_shift = 0, gather_per_shift = 0;
   int32_t selinv_chunk = 0;
-  int32_t tile_rows = 64;           // rows per workgroup tile of the real panel products (64 or 128)
 
   // Selected inversion runs independent subtrees on separate streams:
   // sel_stream[J] in [0, sel_nstreams); a supernode waits for its parent
@@ -132,7 +131,6 @@ struct Symbolic {
 struct AnalyzeOptions {
   int selinv_streams = 4;
   int selinv_chunk = 0;
-  int tile_rows = 64;
   int ordering = 0;
   int leaf_cols = 128;
   int sep_cols = 0;        // 0: every separator is one supernode

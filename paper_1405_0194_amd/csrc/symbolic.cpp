@@ -766,7 +766,6 @@ int analyze(int32_t n, const int64_t* colptr, const int32_t* rowind, int32_t nbl
     const double per = (S.flops_factor + S.flops_selinv) / std::max(1, ns);
     S.fused_lanes = per < FUSE_FLOPS_PER_SUPER ? 1 : 0;
   }
-  S.tile_rows = (opt.tile_rows == 128) ? 128 : 64;
   return 0;
 }
 

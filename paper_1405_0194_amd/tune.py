@@ -30,7 +30,7 @@ from . import binding as B
 HERE = os.path.dirname(os.path.abspath(__file__))
 DEFAULT_CACHE = os.path.join(HERE, "tuned.json")
 DEFAULTS = dict(leaf_cols=128, panel_width=64, tile_rows=64)
-CANDIDATES = dict(leaf_cols=(64, 128, 256), panel_width=(32, 64), tile_rows=(64, 128))
+CANDIDATES = dict(leaf_cols=(64, 128, 256), panel_width=(32, 64), tile_rows=(64,))
 
 
 def bucket(analysis, P):
