@@ -46,7 +46,6 @@ typedef double dbl4 __attribute__((ext_vector_type(4)));
 
 constexpr int NT = 256;   // threads per workgroup (4 wave64)
 constexpr int TM = 64;    // tile rows (m) and columns (n)
-constexpr int LDP = 65;   // padded LDS row (doubles)
 
 struct cplx {
   double re, im;
