@@ -59,7 +59,7 @@ int selinv_event_count(const Symbolic& S);
 int selinv_streams_ready(const Symbolic& S);
 // workspace bytes a batch of nshift complex shifts needs (factor + SelInv)
 int64_t selinv_work_bytes(const Symbolic& S, int nshift);
-// the same when every launch runs on one stream (inorder, or a capture)
+// the same for an in-order run (one workspace region)
 int64_t selinv_work_bytes_inorder(const Symbolic& S, int nshift);
 
 // Workspace of the allocation-free density matrix: a device array of this

@@ -26,8 +26,9 @@
 //   selinv:  k_lhat   W = L_Bp L_pp^{-1}                       (workspace)
 //            k_selinv_off   Z_Bp = -Z_BB W   (Z_BB gathered, symmetric)
 //            k_selinv_diag_* Z_pp = L_pp^{-T} D_p^{-1} L_pp^{-1} - W^T Z_Bp
-// The products run on FP64 MFMA (v_mfma_f64_16x16x4f64): a complex product
-// is four real MFMAs on split real/imaginary LDS tiles.
+//            k_selinv_small  all of these for a panel with few rows below it
+// The products run on FP64 MFMA (v_mfma_f64_16x16x4f64): a complex product is
+// four real MFMAs on elements loaded straight into LDS.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -1607,21 +1608,22 @@ __global__ void __launch_bounds__(NTF, 2) k_selinv_diag_final(Src src) {
 
 // The whole selected inversion of one panel with at most SMALL_ROWS rows below
 // its diagonal block: W = L_Bp Linv, Z_Bp = -Z_BB W and Z_pp in one workgroup
-// per shift, Z_BB read through the maps.  A tree of small supernodes (a 1D chain: 64 columns, 16
-// rows below) is bound by the latency of its launches; as five launches per
-// level (Z_CC gather, W, Z_Bp, partials, final) it took 5.5 + 7.4 + 11.4 + 7.4 +
-// 6.2 us with 8 lanes x 60 shifts.  Per panel: all loads first (Linv, the first
+// per shift, Z_BB read through the maps.  A tree of small supernodes (a 1D
+// chain: 64 columns, 16 rows below) is bound by the latency of its launches; as
+// five launches per level (Z_CC gather, W, Z_Bp, partials, final) it took 5.5 +
+// 7.4 + 11.4 + 7.4 + 6.2 us with 8 lanes x 60 shifts, now 9.8 (8 panels x 40
+// shifts; 26 with 64 rows below).  Per panel: all loads first (Linv, the first
 // blocks of L_Bp and Z_BB), W in LDS, the diagonal product, Z_Bp over Linv's
 // place in LDS, the second diagonal product.
-
 //
 // ROWS = 16 for panels of at most that many rows: 80 KB of LDS, two workgroups
 // per CU.
 template <int ROWS, class Src>
 __global__ void __launch_bounds__(NT, ROWS <= 16 ? 2 : 1) k_selinv_small(Src src) {
-  // all 160 KB of LDS (ROWS = 80): Linv (column, row) with D^{-1} on its diagonal, then
-  // Z_Bp (row, column), and W (row, column); 64 slots a line, permuted by the
-  // line so that 16 lines are read or written without bank conflicts
+  // all 160 KB of LDS (ROWS = 80): Linv (column, row) with D^{-1} on its
+  // diagonal, then Z_Bp (row, column), and W (row, column); 64 slots a line,
+  // permuted by the line so that 16 lines are read or written without bank
+  // conflicts
   __shared__ dbl2 xs[(ROWS > 64 ? ROWS : 64) * 64], wl[ROWS * 64];
   auto at = [](int line, int q) { return line * 64 + (q ^ (line & 15)); };
   Common c;
@@ -2193,7 +2195,8 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
                    fm * nshift * ((double)nrows * k.wp - 0.5 * k.wp * (k.wp - 1)) * k.p0);
       with_tile(tile(nrows, k.wp), [&](auto t) {
         constexpr int TN = decltype(t)::value;
-        hipLaunchKernelGGL((k_int_update<CPLX, TN, OnePanel>), dim3(tiles_of(nrows, TN), nshift), dim3(NT), 0, s, OnePanel{c, k});
+        hipLaunchKernelGGL((k_int_update<CPLX, TN, OnePanel>), dim3(tiles_of(nrows, TN), nshift), dim3(NT), 0, s,
+                           OnePanel{c, k});
       });
     }
     {
@@ -2254,6 +2257,9 @@ int run_factor_kernels(const Symbolic& S, const double* H, const double* Sv, int
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   hipError_t he = hipStreamIsCapturing(st, &cap);
   if (he != hipSuccess) return (int)he;
+  // Where the caller's stream is the only one, large trees run fused as well
+  // (panel by panel a sheet of N=7956 x 60 shifts replays in 215 ms, fused in
+  // 207.5); with the subtree streams they do not (208.8 ms against 211.1).
   const bool one_stream = cap != hipStreamCaptureStatusNone || inorder;
   if (NS > 1 && (S.fused_lanes || (S.fuse_one_stream && one_stream))) {
     // Fused launches (no library streams or events, so also on the in-order
@@ -2796,7 +2802,8 @@ int run_selinv(const Symbolic& S, int nshift, void* L, void* work, hipStream_t s
                          8.0 * nsh * (double)k.nb * k.nb * k.wp);
             with_tile(tn, [&](auto t) {
               constexpr int TN = decltype(t)::value;
-              hipLaunchKernelGGL((k_selinv_off<TN, OnePanel>), dim3(tiles_of(k.nb, TN), nsh), dim3(NT), 0, sj, OnePanel{c, k});
+              hipLaunchKernelGGL((k_selinv_off<TN, OnePanel>), dim3(tiles_of(k.nb, TN), nsh), dim3(NT), 0, sj,
+                                 OnePanel{c, k});
             });
           }
           {
