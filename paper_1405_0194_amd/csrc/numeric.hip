@@ -2133,12 +2133,20 @@ int factor_prologue(const Symbolic& S, const double* H, const double* Sv, int ns
 }
 
 // launch(group, grid) with a fused launch's items (nsh shifts each) in the
-// shortest form that holds them; false when they pass the grid's range.
+// shortest form that holds them; false without items.  A grid dimension holds
+// fewer than 2^32 threads: more workgroups than GROUP_BLOCKS go as several
+// launches (the items are independent), a single panel as tiles x shifts.
+constexpr int64_t GROUP_BLOCKS = 1 << 22;
 template <class F>
 static bool with_group(const Common& c, const std::vector<LaneItem>& items, int nsh, F launch) {
   int64_t total = 0;
   for (const LaneItem& it : items) total += (int64_t)it.tiles * nsh;
-  if (items.empty() || total > (int64_t)INT32_MAX - 1) return false;
+  if (items.empty()) return false;
+  if (items.size() > 1 && total > GROUP_BLOCKS) {
+    const auto mid = items.begin() + items.size() / 2;
+    return with_group(c, std::vector<LaneItem>(items.begin(), mid), nsh, launch) &&
+           with_group(c, std::vector<LaneItem>(mid, items.end()), nsh, launch);
+  }
   auto fill = [&](auto& g) {
     constexpr int N = sizeof(g.start) / sizeof(g.start[0]);
     g.c = c;
