@@ -738,14 +738,17 @@ constexpr int swz_of = AccLayout<std::decay_t<A>>::kSquare64 ? LV::kSwz : 0;
 // --------------------------------------------------------------------------
 // small kernels
 // --------------------------------------------------------------------------
-// One 16-byte store per thread up to FILL_BLOCKS workgroups (32 GiB): 2 GiB fill
-// at 6.8 TB/s so, and at 4.3 with 8192 workgroups that step through it (a wave's
-// stores 32 MB apart).
+// p[0 .. n) = 0, p aligned to 16 bytes.  One 16-byte store per thread up to
+// FILL_BLOCKS workgroups (32 GiB): 2 GiB fill at 6.8 TB/s so, and at 4.3 with
+// 8192 workgroups that step through it (a wave's stores 32 MB apart).  An odd
+// last double is one thread's 8-byte store.
 constexpr int FILL_BLOCKS = 1 << 23;
-__global__ void k_fill_zero(double2* p, int64_t n2) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void k_fill_zero(double* p, int64_t n) {
+  const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (; i < n2; i += stride) p[i] = make_double2(0.0, 0.0);
+  double2* p2 = (double2*)p;
+  for (int64_t i = first; i < n / 2; i += stride) p2[i] = make_double2(0.0, 0.0);
+  if (first == 0 && (n & 1)) p[n - 1] = 0.0;
 }
 
 // Real shifts eps_q as the complex shifts (eps_q, 0) of an inertia batch.
@@ -2116,10 +2119,7 @@ int factor_prologue(const Symbolic& S, const double* H, const double* Sv, int ns
                      nbm, (double*)(w + WK_ABSMAX));
   PXS_CHECK_LAUNCH();
   const int64_t total_d = (CPLX ? 2 : 1) * S.nnzL_store * (int64_t)nshift;   // doubles
-  hipLaunchKernelGGL(k_fill_zero, dim3(blocks_for(total_d / 2, FILL_BLOCKS)), dim3(NT), 0, st,
-                     (double2*)L, total_d / 2);
-  if (total_d & 1)
-    hipLaunchKernelGGL(k_fill_zero, dim3(1), dim3(64), 0, st, (double2*)((double*)L + total_d - 2), (int64_t)1);
+  hipLaunchKernelGGL(k_fill_zero, dim3(blocks_for(total_d / 2, FILL_BLOCKS)), dim3(NT), 0, st, (double*)L, total_d);
   PXS_CHECK_LAUNCH();
   {
     // bytes: H, S, offsets read once per shift block; one element written per entry and shift
