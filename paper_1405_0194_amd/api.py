@@ -127,11 +127,16 @@ def _is_complex(v):
     return np.iscomplexobj(v) if isinstance(v, np.ndarray) else v.is_complex()
 
 
+_NUMPY_TYPES = {"torch." + t for t in ("float64", "float32", "float16", "complex128", "complex64", "int64", "int32",
+                                       "int16", "int8", "uint8", "bool")}
+
+
 def _index_arrays(M):
     """The index tensors of a torch sparse matrix on the device (coalesced
     coordinates, compressed rows or columns) and its values; None for any
-    other input, and for values the host path refuses (with gradients, or
-    lazily conjugated)."""
+    other input, and for values that the host path refuses or may refuse (with
+    gradients, lazily conjugated, or of a type numpy does not have), so that
+    they are refused whether or not their pattern has been seen."""
     try:
         import torch
     except ImportError:          # pragma: no cover
@@ -148,7 +153,9 @@ def _index_arrays(M):
     else:
         return None
     v = out[-1]
-    return None if v.requires_grad or v.is_conj() or v.is_neg() or v.dim() != 1 else out
+    if v.requires_grad or v.is_conj() or v.is_neg() or v.dim() != 1 or str(v.dtype) not in _NUMPY_TYPES:
+        return None
+    return out
 
 
 class _ValueMap:
