@@ -107,8 +107,9 @@ def _take(src, vals, dt):
         out[:] = vals[src]
         return out
     out[low] = vals[src[low]]
-    up = vals[-2 - src[mir]]
-    out[mir] = np.conj(up) if np.iscomplexobj(out) else up
+    out[mir] = vals[-2 - src[mir]]
+    if np.iscomplexobj(out):
+        out[mir] = np.conj(out[mir])
     return out
 
 
