@@ -21,6 +21,7 @@ Every numerical step runs in the HIP library.
 """
 import contextlib
 import hashlib
+import threading
 
 import numpy as np
 
@@ -159,6 +160,14 @@ def _index_arrays(M):
     return out
 
 
+# What a solver keeps of the patterns it has seen on the device: the value maps of
+# the MAPS_KEPT most recently used ones and at most MAPS_BYTES of device memory
+# (one map where that alone is larger).  A map takes 24 to 50 bytes per entry of
+# H (0.2 GB for a sheet of N = 26,624 in compressed rows).
+MAPS_KEPT = 16
+MAPS_BYTES = 1 << 30
+
+
 class _ValueMap:
     """The device-side part of lower_csc for one pair of input patterns:
     copies of their index arrays, compared in full with those of a later
@@ -174,6 +183,10 @@ class _ValueMap:
             none = torch.from_numpy(src == -1).to(device) if np.any(src == -1) else None
             mir = torch.from_numpy(src < -1).to(device) if np.any(src < -1) else None
             self.maps.append((low, none, mir))
+        held = [*self.index, *(t for m in self.maps for t in m if t is not None)]
+        self.bytes = sum(t.numel() * t.element_size() for t in held)
+        # complete before another stream or thread can find it
+        torch.cuda.current_stream(device).synchronize()
 
     def matches(self, key, index):
         import torch
@@ -241,6 +254,8 @@ class Solver:
         self.device = device
         self.options = analysis_options
         self._cache = {}
+        self._maps = []              # (cache entry, value map), most recently used first
+        self._lock = threading.Lock()
 
     def _entry(self, n, colptr, rowind, blocks, coords):
         h = hashlib.sha1()
@@ -260,11 +275,31 @@ class Solver:
             self._cache[key] = e
         return e
 
+    def _keep(self, e, m):
+        """Makes m the most recently used map and drops those over the bounds:
+        more than two of one entry, MAPS_KEPT or MAPS_BYTES in all."""
+        with self._lock:
+            if self._maps and self._maps[0][1] is m:
+                return
+            kept, here, held = [], 0, 0
+            for q, x in [(e, m)] + [(q, x) for q, x in self._maps if x is not m]:
+                here += q is e
+                held += x.bytes
+                if not kept or (len(kept) < MAPS_KEPT and held <= MAPS_BYTES and not (q is e and here > 2)):
+                    kept.append((q, x))
+                else:
+                    held -= x.bytes
+            self._maps = kept
+            for q in list(self._cache.values()):
+                q["maps"] = [x for r, x in kept if r is q]
+
     def _pencil(self, H, S, blocks, coords):
-        """(cache entry, H values, S values on the device).  Sparse tensors on
-        the device whose index arrays equal those of an earlier call (compared
-        in full there) have their values gathered on the device; everything
-        else goes through the host."""
+        """(cache entry, H values, S values on the device, value map or None).
+        Sparse tensors on the device whose index arrays equal those of an
+        earlier call (compared in full there, the latest first) have their
+        values gathered on the device; everything else goes through the host.
+        The caller holds the map until its work on the values is done: another
+        thread may drop it here."""
         import torch
         hi, si = _index_arrays(H), _index_arrays(S)
         index = key = None
@@ -272,18 +307,18 @@ class Solver:
             index = [*hi[:-1], *si[:-1]]
             key = (H.layout, S.layout, tuple(H.shape), H.device, *(t.dtype for t in index))
             cplx = hi[-1].is_complex() or si[-1].is_complex()
-            for e in list(self._cache.values()):
-                for m in e["maps"]:
-                    if m.matches(key, index):
-                        return e, m.values(0, hi[-1], cplx), m.values(1, si[-1], cplx)
+            for e, m in list(self._maps):
+                if m.matches(key, index):
+                    self._keep(e, m)
+                    return e, m.values(0, hi[-1], cplx), m.values(1, si[-1], cplx), m
         n, colptr, rowind, h, s = _union(H, S)
         dt = np.complex128 if _is_complex(h[1]) or _is_complex(s[1]) else np.float64
         e = self._entry(n, colptr, rowind, blocks, coords)
         Hd, Sd = (torch.from_numpy(_take(*x, dt)).to(self.device) for x in (h, s))
         # (entries summed into one position have other values than the input's)
         if index is not None and Hd.device == H.device and h[1].shape == hi[-1].shape and s[1].shape == si[-1].shape:
-            e["maps"] = [*e["maps"][-1:], _ValueMap(key, index, h, s, Hd.device)]   # the last two input patterns
-        return e, Hd, Sd
+            self._keep(e, _ValueMap(key, index, h, s, Hd.device))
+        return e, Hd, Sd, None
 
     def _buffers(self, e, kind, P):
         import torch
@@ -350,7 +385,7 @@ class Solver:
             if not ok:
                 raise ValueError(f"S is not positive definite: {bad} non-positive pivots, tiny pivot at {info}")
         nsets = 1 + max(SETS.index(o) for o in outputs)
-        e, Hd, Sd = self._pencil(H, S, blocks, coords)
+        e, Hd, Sd, held = self._pencil(H, S, blocks, coords)   # held: see _pencil
         a = e["analysis"]
         n = a.n
         herm = Hd.is_complex()
