@@ -3,12 +3,13 @@
 The tunable knobs are options of the symbolic analysis: the largest
 nested-dissection leaf (leaf_cols, which sets how small the supernodes at
 the bottom of the tree get), the panel width (columns per factor/SelInv
-panel, the K-depth of the in-panel products) and the tile height of the
-panel products (64 or 128 rows per workgroup).  Shapes are grouped into
+panel, the K-depth of the in-panel products); tile_rows, which tuned options
+may name, has no effect.  Shapes are grouped into
 buckets by structural features only (matrix size, fill of L, pole count), so
 any input -- not just the synthetic lattices -- maps to a bucket.  For each
 bucket the tuner times one density matrix per candidate (graph-captured plan,
-median of a few replays) and keeps the fastest in a JSON cache.  On top of
+median of a few replays) and keeps the fastest in a JSON cache, or the defaults
+where none is MIN_GAIN faster.  On top of
 the tuned shape, wide nested-dissection separators are cut into several
 supernodes when that removes enough stored zeros (a structural rule, no
 timing; see with_separator_cut).
@@ -30,6 +31,10 @@ from . import binding as B
 HERE = os.path.dirname(os.path.abspath(__file__))
 DEFAULT_CACHE = os.path.join(HERE, "tuned.json")
 DEFAULTS = dict(leaf_cols=128, panel_width=64, tile_rows=64)
+# What a candidate has to be faster than the defaults to be chosen: other shapes
+# cost every tuned_analysis of the bucket a second symbolic analysis (11 ms at
+# N = 1,872), and replays of one plan differ by about 1%.
+MIN_GAIN = 0.02
 CANDIDATES = dict(leaf_cols=(64, 128, 256), panel_width=(32, 64), tile_rows=(64,))
 
 
@@ -140,7 +145,8 @@ def B_BETA():
 
 
 def tune_system(system, P, cache, candidates=CANDIDATES, reps=3, log=sys.stderr):
-    """Tunes the bucket of one system (skips buckets already in the cache)."""
+    """Tunes the bucket of one system (skips buckets already in the cache):
+    the fastest candidate, or the defaults if it is less than MIN_GAIN faster."""
     a0 = B.Analysis.from_system(system)
     key = bucket(a0, P)
     if key in cache:
@@ -157,6 +163,8 @@ def tune_system(system, P, cache, candidates=CANDIDATES, reps=3, log=sys.stderr)
         print(f"# tune {key} {opts}: {t * 1e3:.2f} ms", file=log, flush=True)
     d0 = next(tr["seconds"] for tr in trials if tr["options"] == DEFAULTS) if any(
         tr["options"] == DEFAULTS for tr in trials) else None
+    if d0 is not None and d0 < (1.0 + MIN_GAIN) * best[0]:
+        best = (d0, dict(DEFAULTS))
     cache[key] = dict(options=best[1], seconds=round(best[0], 6), default_seconds=d0,
                       example=dict(kind=system.kind, n=system.n, poles=P), trials=trials)
     return key, cache[key]
