@@ -253,7 +253,7 @@ def chain_leg(reps=200):
 
     # the pole table on the device (as the serving loop keeps it): replays
     # queue back to back; from host arrays each replay first copies the
-    # table from pageable memory, which waits for the stream
+    # table from pageable memory
     sh_d = torch.from_numpy(np.ascontiguousarray(sh, dtype=np.complex128)).cuda()
     wt_d = torch.from_numpy(np.ascontiguousarray(wt, dtype=np.complex128).reshape(-1)).cuda()
     plan_us = timed(lambda: plan.run_device(sh_d, wt_d), reps)
@@ -553,7 +553,7 @@ def main():
     ap.add_argument("--no-chain", action="store_true", help="skip the chain-workload leg")
     ap.add_argument("--pole-groups", type=int, default=4,
                     help="also time the poles in this many graph-plan groups on separate streams (0: skip)")
-    ap.add_argument("--tile-rows", type=int, default=0, help="rows per tile of the panel products (64/128)")
+    ap.add_argument("--tile-rows", type=int, default=0, help="0, 64 or 128: without effect (the library picks 64, 32 or 16 by launch)")
     ap.add_argument("--panel-width", type=int, default=0)
     ap.add_argument("--leaf-cols", type=int, default=0)
     ap.add_argument("--selinv-streams", type=int, default=0)

@@ -407,7 +407,8 @@ void pxs_plan_free(pxs_plan plan);
  * and caller buffers as for pxs_plan_create (Lbuf[i], work[i], out[i]:
  * device nsets * nnz_lower doubles), run as one sequence of launches: each
  * launch takes the next panel operation of every system whose next
- * operation uses the same kernel, as one grid.  Every system's operations
+ * operation uses the same kernel, as one grid (several above 2^22
+ * workgroups).  Every system's operations
  * keep the order of its single-stream run, so its factors, selected
  * inverses and pole sums are the same bits as an eager run of it alone.
  * pxs_batch_create plans the launches (host only); pxs_batch_info reports

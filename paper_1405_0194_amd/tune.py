@@ -58,8 +58,10 @@ def load_cache(path=DEFAULT_CACHE):
 # stored entries of L: in 3D the columns of a separator plane reach different
 # parts of the ancestors, and one supernode over the plane stores the widest
 # structure for all of them (cubic bulk N = 22,464: 2.6% fewer stored entries,
-# 22% less factor storage, 3.9% faster; 1,664 columns 2.8% faster, 416
-# slower).  In 2D the separators' columns share their structure and a cut
+# 22% less factor storage, 3.9% faster; 1,664 columns 2.8% faster, 416 2%
+# slower: 13.1 s a density matrix against 12.8).  One width for every bulk is a
+# compromise: at N = 7,488 x 40 poles 208, 416, 576, 832, 1,152 columns and no cut
+# take 539, 522, 537, 539, 555 and 567 ms.  In 2D the separators' columns share their structure and a cut
 # only adds supernodes (honeycomb N = 26,624: 0.02% fewer entries, 0.3%
 # slower), so it is not taken.
 SEP_COLS = 832
